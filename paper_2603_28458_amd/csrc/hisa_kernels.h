@@ -51,7 +51,7 @@ struct ScoreArgs {
   long ld;
   int t_begin, t_count;
   int tiles_per_wave;        // score_ranges: 32-key tiles each wave handles
-  int groups;                // score_ranges: workgroups per query (the grid holds t_count * groups)
+  int groups;                // workgroups per query (score_ranges) or per 8 queries (score_prefill)
 };
 
 // Position and sequence of query t, clamped so that no key row past the sequence is visible.
@@ -734,13 +734,17 @@ __global__ __launch_bounds__(256, 2) void k_score_ranges(ScoreArgs a) {
 // requested one sub-tile early: +2 % and +4 % on the flat indexer, -3 % on short Stage 1 rows.
 // With the DMA, the stores and the barrier all removed the loop itself runs at 1.34 PFLOP/s:
 // what is left is the issue-slot limit of the MFMA / epilogue mix, not memory.)
+// a.groups > 1 cuts the key tiles of 8 queries into that many equal ranges, one workgroup each: a CU
+// holds one workgroup, so a few thousand queries alone leave CUs idle (1024 queries at 64K keys: 128
+// workgroups for 256 CUs, 1.33 ms; in two ranges 0.83 ms).
 template <int HG, int KDT>
 __global__ __launch_bounds__(512) void k_score_prefill(ScoreArgs a) {
   constexpr int BB = TileGeom<KDT>::kBufBytes;
   constexpr int SUBS = 4;                       // 32-key sub-tiles per staged tile (one barrier per tile)
   constexpr int TK = 32 * SUBS;                 // keys per tile
   __shared__ __align__(16) unsigned char tiles[2 * SUBS * BB];   // [buffer][sub-tile]
-  const int g = gridDim.x - 1 - blockIdx.x;
+  const RowGroup rg = row_group(a.groups);
+  const int g = (int)gridDim.x / a.groups - 1 - rg.row;
   const int th = threadIdx.x, lane = th & 63;
   const int wave = __builtin_amdgcn_readfirstlane(th >> 6);
   const int tl = g * 8 + wave;
@@ -752,7 +756,9 @@ __global__ __launch_bounds__(512) void k_score_prefill(ScoreArgs a) {
   const int tl_last = (g * 8 + 7) < a.t_count ? (g * 8 + 7) : a.t_count - 1;
   int seq_last;
   const int n_max = visible_rows(a, query_pos(a, a.t_begin + tl_last, seq_last));
-  const int n_iter = (n_max + TK - 1) / TK;
+  const int n_tiles = (n_max + TK - 1) / TK;
+  const int it0 = (int)((long)n_tiles * rg.x / a.groups);   // this workgroup's key tiles: it0 .. it0 + n_iter - 1
+  const int n_iter = (int)((long)n_tiles * (rg.x + 1) / a.groups) - it0;
   float* out = a.out + (long)(active ? tl : 0) * a.ld;
 
   QFrag<HG> fq;
@@ -777,7 +783,7 @@ __global__ __launch_bounds__(512) void k_score_prefill(ScoreArgs a) {
   }
   auto dma_tile = [&](int it, int buf) {
     const uint32_t dst = tiles_addr + (buf * SUBS + sub_w) * BB;
-    const int row0 = it * TK + sub_w * 32 + part_w * 16;
+    const int row0 = (it0 + it) * TK + sub_w * 32 + part_w * 16;
     if constexpr (KDT == DT_BF16) {
 #pragma unroll
       for (int i = 0; i < 4; ++i)
@@ -790,7 +796,7 @@ __global__ __launch_bounds__(512) void k_score_prefill(ScoreArgs a) {
                                                  voff[i], (row0 + i * 8) * 128, 0, 0);
       if (part_w == 0)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(srsrc, (lds_void*)(uintptr_t)(dst + 4096), 4, lane * 4,
-                                                 (it * TK + sub_w * 32) * 4, 0, 0);
+                                                 ((it0 + it) * TK + sub_w * 32) * 4, 0, 0);
     }
   };
   using Tile = typename Operands<HG, KDT>::Tile;
@@ -804,9 +810,9 @@ __global__ __launch_bounds__(512) void k_score_prefill(ScoreArgs a) {
       return lds_read_tile_fp8_raw(addr);
     }
   };
-  // sub-tile u covers rows 32u .. 32u+31
+  // sub-tile u of this workgroup covers the 32 rows from it0 * TK + 32u
   auto finish = [&](int u, float s) {
-    const int row = u * 32 + (lane & 31);
+    const int row = it0 * TK + u * 32 + (lane & 31);
     if (lane < 32 && row < n_vis) out[row] = s;
   };
 
