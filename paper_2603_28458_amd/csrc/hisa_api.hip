@@ -102,6 +102,7 @@ ScoreArgs base_args(const hisa_queries* q, const hisa_keys* k) {
   a.B = 1;
   a.tiles_per_wave = 1;
   a.groups = 1;
+  a.whole_rows = -1;
   return a;
 }
 
@@ -223,6 +224,7 @@ SelectArgs select_base(const hisa_queries* q, const hisa_keys* k) {
   s.q_pos0 = q->q_pos0;
   s.n_seq = k->n_seq;
   s.pos_div = 1;
+  s.whole_rows = -1;
   s.seg_len = 1 << 30;
   s.n_seg = 1;
   return s;
@@ -547,6 +549,8 @@ int hisa_block_score_topk(const hisa_queries* queries, const hisa_keys* keys, co
   a.ld = M;
   a.t_begin = 0;
   a.t_count = T;
+  // a query that sees at most m blocks keeps them all: its block scores are only computed if asked for
+  a.whole_rows = block_scores ? -1 : m;
   if (block_scores) {
     const long n = (long)T * M;
     hipLaunchKernelGGL(k_fill_f32, dim3((unsigned)((n + 255) / 256 > 4096 ? 4096 : (n + 255) / 256)),
@@ -558,6 +562,7 @@ int hisa_block_score_topk(const hisa_queries* queries, const hisa_keys* keys, co
   sa.scores = J;
   sa.ld = M;
   sa.pos_div = B;
+  sa.whole_rows = a.whole_rows;
   sa.t_begin = 0;
   sa.k = m;
   sa.out_idx = block_idx;
@@ -612,6 +617,8 @@ static int token_refine_impl(const hisa_queries* queries, const hisa_keys* keys,
   a.t_begin = 0;
   a.t_count = T;
   a.ld = n_slots;
+  // a query that sees at most k tokens selects them all: scored only if the scores are asked for
+  a.whole_rows = (topk_scores || cand_scores) ? -1 : k;
 
   const bool fused = path == PATH_MFMA && !cand_scores && T >= 256 && n_slots <= 16384;
   if (fused) {
@@ -652,6 +659,8 @@ static int token_refine_impl(const hisa_queries* queries, const hisa_keys* keys,
   sa.block_idx = block_idx;
   sa.m = m;
   sa.B = B;
+  sa.n_blocks = keys->s_max / B;
+  sa.whole_rows = a.whole_rows;
   sa.t_begin = 0;
   sa.k = k;
   sa.out_idx = topk_idx;

@@ -52,6 +52,7 @@ struct ScoreArgs {
   int t_begin, t_count;
   int tiles_per_wave;        // score_ranges: 32-key tiles each wave handles
   int groups;                // workgroups per query (score_ranges) or per 8 queries (score_prefill)
+  int whole_rows;            // a query that sees at most this many rows keeps them all: not scored (-1: score all)
 };
 
 // Position and sequence of query t, clamped so that no key row past the sequence is visible.
@@ -398,14 +399,15 @@ __global__ __launch_bounds__(256) void k_score_ranges_f32(ScoreArgs a, int keys_
   int seq;
   const int pos = query_pos(a, t, seq);
   const int H = a.H, d = a.d;
-  const float* q = (const float*)a.q + (long)t * H * d;
-  for (int i = tid; i < H * d; i += 256) qs[i] = q[i];
-  for (int i = tid; i < H; i += 256) qs[H * d + i] = a.w[(long)t * H + i];
-  __syncthreads();
   const bool gather = a.block_idx != nullptr;
   const int n_total = gather ? a.m * a.B : visible_rows(a, pos);
   const int lo = query_lo(a.q_lo, t, pos);
   const int lo_row = lo / a.pos_div;   // first visible row when the rows are blocks or tokens in order
+  if (visible_rows(a, pos) - lo_row <= a.whole_rows) return;
+  const float* q = (const float*)a.q + (long)t * H * d;
+  for (int i = tid; i < H * d; i += 256) qs[i] = q[i];
+  for (int i = tid; i < H; i += 256) qs[H * d + i] = a.w[(long)t * H + i];
+  __syncthreads();
   const int c0 = rg.x * keys_per_wg;
   const int c1 = (c0 + keys_per_wg) < n_total ? (c0 + keys_per_wg) : n_total;
   const float* kbase = (const float*)a.keys + (long)seq * a.rows_per_seq * d;
@@ -660,7 +662,7 @@ __global__ __launch_bounds__(256, 2) void k_score_ranges(ScoreArgs a) {
   // first visible row: a token when gathering, else a row of the array in order (token or block)
   const int lo_row = gather ? query_lo(a.q_lo, t, pos) : query_lo(a.q_lo, t, pos) / a.pos_div;
   const int v0 = rg.x * 4 * a.tiles_per_wave;
-  if (v0 >= n_tiles) return;
+  if (v0 >= n_tiles || n_vis - lo_row <= a.whole_rows) return;
   // in-order rows below the first visible one are neither scored nor written: the select starts
   // at the first visible row (rounded down to four)
   if (!gather && (v0 + 4 * a.tiles_per_wave) * 32 <= lo_row) return;
@@ -756,6 +758,7 @@ __global__ __launch_bounds__(512) void k_score_prefill(ScoreArgs a) {
   const int tl_last = (g * 8 + 7) < a.t_count ? (g * 8 + 7) : a.t_count - 1;
   int seq_last;
   const int n_max = visible_rows(a, query_pos(a, a.t_begin + tl_last, seq_last));
+  if (n_max <= a.whole_rows) return;            // (positions grow with the query index: nor do the other seven)
   const int n_tiles = (n_max + TK - 1) / TK;
   const int it0 = (int)((long)n_tiles * rg.x / a.groups);   // this workgroup's key tiles: it0 .. it0 + n_iter - 1
   const int n_iter = (int)((long)n_tiles * (rg.x + 1) / a.groups) - it0;
@@ -882,6 +885,7 @@ __global__ __launch_bounds__(512) void k_score_resident(ScoreArgs a) {
   const int tl_last = (t0 + 8 * NQ - 1) < a.t_count ? (t0 + 8 * NQ - 1) : a.t_count - 1;
   int seq_last;
   const int n_max = visible_rows(a, query_pos(a, a.t_begin + tl_last, seq_last));
+  if (n_max <= a.whole_rows) return;
   const int n_sub = (n_max + 31) >> 5;
   __amdgpu_buffer_rsrc_t krsrc, srsrc;
   key_buffers<DT_BF16>(a, 0, krsrc, srsrc);
@@ -899,7 +903,7 @@ __global__ __launch_bounds__(512) void k_score_resident(ScoreArgs a) {
     int seq;
     const int n_vis = visible_rows(a, query_pos(a, t, seq));
     const int nu = (n_vis + 31) >> 5;    // <= n_sub: positions grow with the query index
-    if (nu <= 0) continue;
+    if (n_vis <= a.whole_rows) continue;
     float* out = a.out + (long)tl * a.ld;
     QFrag<HG> f;
     load_qfrag<HG>(f, (const uint16_t*)a.q + (long)t * a.H * kD, a.w + (long)t * a.H);
@@ -927,6 +931,35 @@ __global__ __launch_bounds__(512) void k_score_resident(ScoreArgs a) {
   }
 }
 
+// Section 4.1, boundary behaviour: a query that sees at most k tokens selects all of them, and no score
+// decides anything.  Writes the visible tokens (lo .. pos) of the kept blocks, ascending, then -1: the ids
+// are ascending, so only the first and the last kept block can be cut.
+template <int THREADS>
+__device__ __forceinline__ void take_all_visible(const int32_t* __restrict__ blk_ids, int m, int B, int n_blocks,
+                                                 int pos, int lo, int k, int32_t* __restrict__ out) {
+  int n_used = 0;
+  for (int i = threadIdx.x & 63; i < m; i += 64) {
+    const int blk = blk_ids[i];
+    if (blk >= 0 && blk < n_blocks) n_used = i + 1;
+  }
+  n_used = (int)wave_max((uint32_t)n_used);
+  auto first_of = [&](int slot) { const int r = blk_ids[slot] * B; return r > lo ? r : lo; };
+  auto end_of = [&](int slot) { const int r = (blk_ids[slot] + 1) * B; return r < pos + 1 ? r : pos + 1; };
+  const int head = n_used > 0 ? first_of(0) : 0;
+  const int c0 = n_used > 0 ? end_of(0) - head : 0;
+  const int total = n_used > 1 ? c0 + (n_used - 2) * B + (end_of(n_used - 1) - first_of(n_used - 1)) : c0;
+  for (int p = threadIdx.x; p < k; p += THREADS) {
+    int tok = -1;
+    if (p < c0) {
+      tok = head + p;
+    } else if (p < total) {
+      const int slot = (p - c0) / B;
+      tok = blk_ids[slot + 1] * B + (p - c0 - slot * B);
+    }
+    out[p] = tok;
+  }
+}
+
 // Row-wise exact top-k over scores in global memory (Eqs. 2, 6, 9).
 enum : int { MAP_FLAT = 0, MAP_BLOCKS = 1, MAP_CAND = 2, MAP_PAIRS = 3 };
 
@@ -942,7 +975,8 @@ struct SelectArgs {
   int t_begin;               // global query index of row 0
   int n_fixed;               // CAND / PAIRS: elements per row
   const int32_t* block_idx;  // MAP_CAND: [T, m] (global query indexing)
-  int m, B;
+  int m, B, n_blocks;
+  int whole_rows;            // as ScoreArgs::whole_rows: such a row was not scored, all it sees is selected
   int seg_len, n_seg;        // FLAT: the row is cut into n_seg segments of seg_len (grid.x)
   int k;
   int32_t* out_idx;          // [rows * n_seg, k]
@@ -964,23 +998,39 @@ __global__ __launch_bounds__(THREADS) void k_select(SelectArgs a) {
   int n = a.n_fixed;
   int base = 0;
   int first_vis = 0;   // MAP_BLOCKS: entry of the first visible block (0 unless sequences are packed)
-  if (MAP == MAP_FLAT || MAP == MAP_BLOCKS) {
+  if (MAP != MAP_PAIRS) {
     int s = a.q_seq ? a.q_seq[t] : 0;
     s = s < 0 ? 0 : (s >= a.n_seq ? a.n_seq - 1 : s);
     int pos = a.q_pos ? a.q_pos[t] : a.q_pos0 + t;
     const int sl = a.seq_len[s];
     pos = pos < sl ? pos : sl - 1;
-    int n_vis = pos < 0 ? 0 : pos / a.pos_div + 1;
-    n_vis = n_vis < a.ld ? n_vis : (int)a.ld;   // never past the score row, whatever seq_len says
-    // this segment's rows, cut at the first visible one rounded down to four (16-byte loads; the
-    // up to three rows in between were written as -inf by the scoring kernel)
-    const int lo_row = query_lo(a.q_lo, t, pos) / a.pos_div;
-    const int seg_end = (seg + 1) * a.seg_len < n_vis ? (seg + 1) * a.seg_len : n_vis;
-    base = seg * a.seg_len;
-    base = base > (lo_row & ~3) ? base : (lo_row & ~3);
-    n = seg_end - base;
-    n = (n < 0 || lo_row >= n_vis) ? 0 : n;     // (first visible row past the last: the query sees nothing)
-    first_vis = lo_row - base;                  // < 0 in later segments: no forced entry there
+    if constexpr (MAP == MAP_CAND) {
+      const int cap = a.n_blocks * a.B;
+      pos = pos < cap ? pos : cap - 1;          // (whatever seq_len says)
+      const int lo = query_lo(a.q_lo, t, pos);
+      if (pos + 1 - lo <= a.whole_rows) {
+        take_all_visible<THREADS>(a.block_idx + (long)t * a.m, a.m, a.B, a.n_blocks, pos, lo, a.k,
+                                  a.out_idx + (long)row * a.k);
+        return;
+      }
+    } else {
+      int n_vis = pos < 0 ? 0 : pos / a.pos_div + 1;
+      n_vis = n_vis < a.ld ? n_vis : (int)a.ld;   // never past the score row, whatever seq_len says
+      // this segment's rows, cut at the first visible one rounded down to four (16-byte loads; the
+      // up to three rows in between were written as -inf by the scoring kernel)
+      const int lo_row = query_lo(a.q_lo, t, pos) / a.pos_div;
+      if (MAP == MAP_BLOCKS && n_vis - lo_row <= a.whole_rows) {
+        for (int p = threadIdx.x; p < a.k; p += THREADS)
+          a.out_idx[(long)row * a.k + p] = p < n_vis - lo_row ? lo_row + p : -1;
+        return;
+      }
+      const int seg_end = (seg + 1) * a.seg_len < n_vis ? (seg + 1) * a.seg_len : n_vis;
+      base = seg * a.seg_len;
+      base = base > (lo_row & ~3) ? base : (lo_row & ~3);
+      n = seg_end - base;
+      n = (n < 0 || lo_row >= n_vis) ? 0 : n;     // (first visible row past the last: the query sees nothing)
+      first_vis = lo_row - base;                  // < 0 in later segments: no forced entry there
+    }
   }
   const long orow = (long)row * a.n_seg + seg;
   int32_t* oi = a.out_idx + orow * a.k;
@@ -1461,6 +1511,11 @@ __device__ __forceinline__ void stage1_in_workgroup(const QFrag<HG>& f, const Sc
   const int lane = threadIdx.x & 63;
   const int n_bvis = pos < 0 ? 0 : pos / a.B + 1;
   const int b_first = lo / a.B;   // first visible block (0 unless sequences are packed)
+  if (n_bvis - b_first <= a.m) {  // every visible block fits the budget
+    for (int p = threadIdx.x; p < a.m; p += NT) blk_lds[p] = p < n_bvis - b_first ? b_first + p : -1;
+    __syncthreads();
+    return;
+  }
   const int nt1 = (n_bvis + 31) >> 5;
   const int nj1 = nt1 > wave ? (nt1 - wave + NW - 1) / NW : 0;
   const __amdgpu_buffer_rsrc_t prsrc =
@@ -1518,6 +1573,13 @@ __global__ __launch_bounds__(512) void k_stage1_query(ScoreArgs a, const void* p
   const int pos = query_pos(a, t, seq);
   const int lo = query_lo(a.q_lo, t, pos);
   const int n_blocks = (int)(a.rows_per_seq / a.B);
+  {
+    const int b_first = lo / a.B, n_bvis = pos < 0 ? 0 : pos / a.B + 1;
+    if (n_bvis - b_first <= a.m) {   // every visible block fits the budget: nothing to score
+      for (int p = threadIdx.x; p < a.m; p += NT) block_idx_out[(long)t * a.m + p] = p < n_bvis - b_first ? b_first + p : -1;
+      return;
+    }
+  }
   // the query fragment is staged in an area of its own, so that every wave's first tile of pooled
   // keys can be requested right behind it: one memory latency for both
   QFrag<HG> f;
@@ -1574,13 +1636,18 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_refine_fused(Score
   // scratch of the top-k's fast path, behind everything else (shared with nothing: see select_topk_fine)
   FineSelSmem<NT, E>& fs = *reinterpret_cast<FineSelSmem<NT, E>*>(
       smem + kStageBytes + (E1 > 0 ? (size_t)sc_floats * 4 + (size_t)((a.m + 3) / 4 * 4) * 4 : (size_t)a.m * a.B * 4));
-  fine_select_prepare<NT, E>(fs);
   const int t = a.t_begin + (gridDim.x - 1 - blockIdx.x);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   int seq;
   const int pos = query_pos(a, t, seq);
   const int n_vis = pos + 1;
   const int lo = query_lo(a.q_lo, t, pos);   // first visible token (0 unless sequences are packed)
+  if (E1 == 0 && n_vis - lo <= a.whole_rows) {
+    take_all_visible<NT>(a.block_idx + (long)t * a.m, a.m, a.B, (int)(a.rows_per_seq / a.B), pos, lo, k,
+                         topk_idx + (long)t * k);
+    return;
+  }
+  fine_select_prepare<NT, E>(fs);
 
   // fp8 keys without Stage 1 in this launch: no wave needs the bf16 fragment, and the two-term
   // e4m3 fragment is built once for the workgroup (below) instead of once per wave

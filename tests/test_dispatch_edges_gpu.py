@@ -23,3 +23,17 @@ def test_key_ranges_of_the_prefill_scoring_kernel(T, L, k_dtype):
     wl = W.make_workload(f"ranges{T}", seq_len=L, T=T, H=64, d=128, B=32, m=20, k=512, q_dtype="bf16",
                          k_dtype=k_dtype, seed=400 + T)
     _run(wl)
+
+
+@pytest.mark.parametrize("k_dtype,H,d", [("bf16", 64, 128), ("fp8_e4m3", 32, 128), ("f32", 4, 64)])
+@pytest.mark.parametrize("packed", [False, True])
+def test_queries_that_keep_everything(k_dtype, H, d, packed):
+    # visible blocks around the block budget and visible tokens around the token budget, with sequences of
+    # their own (two-kernel Stage 2 below 256 queries, fused above) and in a packed stream whose starts are
+    # no multiples of the block; a sequence of one token, one of exactly k, one of exactly m * B
+    B, m, k = 32, 8, 130
+    qd = "f32" if k_dtype == "f32" else "bf16"
+    for lens in ([1, 130, 70], [256, 1, 131, 130, 400, 33]):
+        wl = W.make_workload(f"all_{k_dtype}_{packed}_{len(lens)}", n_seq=len(lens), seq_len=lens, T=sum(lens), H=H, d=d,
+                             B=B, m=m, k=k, q_dtype=qd, k_dtype=k_dtype, mode="varlen", seed=420)
+        _run(W.pack(wl) if packed else wl, n=10000)
