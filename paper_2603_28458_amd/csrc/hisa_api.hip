@@ -563,6 +563,8 @@ int hisa_block_score_topk(const hisa_queries* queries, const hisa_keys* keys, co
   sa.ld = M;
   sa.pos_div = B;
   sa.whole_rows = a.whole_rows;
+  sa.w = a.w;
+  sa.H = a.H;
   sa.t_begin = 0;
   sa.k = m;
   sa.out_idx = block_idx;
@@ -661,6 +663,9 @@ static int token_refine_impl(const hisa_queries* queries, const hisa_keys* keys,
   sa.B = B;
   sa.n_blocks = keys->s_max / B;
   sa.whole_rows = a.whole_rows;
+  sa.w = a.w;
+  sa.H = a.H;
+  sa.k_scale = a.k_scale;
   sa.t_begin = 0;
   sa.k = k;
   sa.out_idx = topk_idx;

@@ -52,7 +52,9 @@ struct ScoreArgs {
   int t_begin, t_count;
   int tiles_per_wave;        // score_ranges: 32-key tiles each wave handles
   int groups;                // workgroups per query (score_ranges) or per 8 queries (score_prefill)
-  int whole_rows;            // a query that sees at most this many rows keeps them all: not scored (-1: score all)
+  // A query that sees at most this many rows keeps them all and is not scored (-1: score all), unless a
+  // score of -inf could drop one of them or its block list is not Stage 1's (never_neg_inf, blocks_ascending).
+  int whole_rows;
 };
 
 // Position and sequence of query t, clamped so that no key row past the sequence is visible.
@@ -80,6 +82,30 @@ __device__ __forceinline__ int query_lo(const int32_t* q_lo, int t, int pos) {
   int lo = q_lo ? q_lo[t] : 0;
   lo = lo < 0 ? 0 : lo;
   return lo > pos + 1 ? pos + 1 : lo;
+}
+
+// Wave-uniform: no score of this query can be -inf, the one value the selects drop although its row is
+// visible.  With gates and key scales >= 0 every term of the sum is, so a score is >= 0, +inf or NaN.
+// scale: the per-token scales of the query's sequence (fp8 keys), of which lo .. pos count, or null.
+__device__ __forceinline__ bool never_neg_inf(const float* __restrict__ w, int H, const float* __restrict__ scale,
+                                              int lo, int pos) {
+  const int lane = threadIdx.x & 63;
+  bool ok = true;
+  for (int j = lane; j < H; j += 64) ok = ok && w[j] >= 0.f;
+  if (scale)
+    for (int r = (lo > 0 ? lo : 0) + lane; r <= pos; r += 64) ok = ok && scale[r] >= 0.f;
+  return __ballot(!ok) == 0ull;
+}
+
+// Wave-uniform: the m block ids are as Stage 1 writes them, strictly ascending visible blocks and then -1.
+__device__ __forceinline__ bool blocks_ascending(const int32_t* __restrict__ blk_ids, int m, int B, int lo, int pos) {
+  const int b_lo = lo / B, b_hi = pos / B;
+  bool ok = true;
+  for (int i = threadIdx.x & 63; i < m; i += 64) {
+    const int b = blk_ids[i], prev = i > 0 ? blk_ids[i - 1] : 0;
+    ok = ok && (b < 0 || (b >= b_lo && b <= b_hi && (i == 0 || (prev >= 0 && prev < b))));
+  }
+  return __ballot(!ok) == 0ull;
 }
 
 // Grids whose second dimension would be the query (row) index are launched one-dimensional, as
@@ -403,7 +429,9 @@ __global__ __launch_bounds__(256) void k_score_ranges_f32(ScoreArgs a, int keys_
   const int n_total = gather ? a.m * a.B : visible_rows(a, pos);
   const int lo = query_lo(a.q_lo, t, pos);
   const int lo_row = lo / a.pos_div;   // first visible row when the rows are blocks or tokens in order
-  if (visible_rows(a, pos) - lo_row <= a.whole_rows) return;
+  if (visible_rows(a, pos) - lo_row <= a.whole_rows && never_neg_inf(a.w + (long)t * H, H, nullptr, lo, pos) &&
+      (!gather || blocks_ascending(a.block_idx + (long)t * a.m, a.m, a.B, lo, pos)))
+    return;
   const float* q = (const float*)a.q + (long)t * H * d;
   for (int i = tid; i < H * d; i += 256) qs[i] = q[i];
   for (int i = tid; i < H; i += 256) qs[H * d + i] = a.w[(long)t * H + i];
@@ -662,7 +690,11 @@ __global__ __launch_bounds__(256, 2) void k_score_ranges(ScoreArgs a) {
   // first visible row: a token when gathering, else a row of the array in order (token or block)
   const int lo_row = gather ? query_lo(a.q_lo, t, pos) : query_lo(a.q_lo, t, pos) / a.pos_div;
   const int v0 = rg.x * 4 * a.tiles_per_wave;
-  if (v0 >= n_tiles || n_vis - lo_row <= a.whole_rows) return;
+  if (v0 >= n_tiles) return;
+  if (n_vis - lo_row <= a.whole_rows &&
+      never_neg_inf(a.w + (long)t * a.H, a.H, a.k_scale ? a.k_scale + (long)seq * a.rows_per_seq : nullptr, lo_row, pos) &&
+      (!gather || blocks_ascending(a.block_idx + (long)t * a.m, a.m, a.B, lo_row, pos)))
+    return;
   // in-order rows below the first visible one are neither scored nor written: the select starts
   // at the first visible row (rounded down to four)
   if (!gather && (v0 + 4 * a.tiles_per_wave) * 32 <= lo_row) return;
@@ -758,7 +790,10 @@ __global__ __launch_bounds__(512) void k_score_prefill(ScoreArgs a) {
   const int tl_last = (g * 8 + 7) < a.t_count ? (g * 8 + 7) : a.t_count - 1;
   int seq_last;
   const int n_max = visible_rows(a, query_pos(a, a.t_begin + tl_last, seq_last));
-  if (n_max <= a.whole_rows) return;            // (positions grow with the query index: nor do the other seven)
+  if (n_max <= a.whole_rows) {                  // (positions grow with the query index: nor do the other seven see more)
+    const int n_q = tl_last - g * 8 + 1;
+    if (never_neg_inf(a.w + (long)(a.t_begin + g * 8) * a.H, n_q * a.H, nullptr, 0, 0)) return;
+  }
   const int n_tiles = (n_max + TK - 1) / TK;
   const int it0 = (int)((long)n_tiles * rg.x / a.groups);   // this workgroup's key tiles: it0 .. it0 + n_iter - 1
   const int n_iter = (int)((long)n_tiles * (rg.x + 1) / a.groups) - it0;
@@ -885,7 +920,6 @@ __global__ __launch_bounds__(512) void k_score_resident(ScoreArgs a) {
   const int tl_last = (t0 + 8 * NQ - 1) < a.t_count ? (t0 + 8 * NQ - 1) : a.t_count - 1;
   int seq_last;
   const int n_max = visible_rows(a, query_pos(a, a.t_begin + tl_last, seq_last));
-  if (n_max <= a.whole_rows) return;
   const int n_sub = (n_max + 31) >> 5;
   __amdgpu_buffer_rsrc_t krsrc, srsrc;
   key_buffers<DT_BF16>(a, 0, krsrc, srsrc);
@@ -903,7 +937,7 @@ __global__ __launch_bounds__(512) void k_score_resident(ScoreArgs a) {
     int seq;
     const int n_vis = visible_rows(a, query_pos(a, t, seq));
     const int nu = (n_vis + 31) >> 5;    // <= n_sub: positions grow with the query index
-    if (n_vis <= a.whole_rows) continue;
+    if (nu <= 0 || (n_vis <= a.whole_rows && never_neg_inf(a.w + (long)t * a.H, a.H, nullptr, 0, 0))) continue;
     float* out = a.out + (long)tl * a.ld;
     QFrag<HG> f;
     load_qfrag<HG>(f, (const uint16_t*)a.q + (long)t * a.H * kD, a.w + (long)t * a.H);
@@ -932,15 +966,13 @@ __global__ __launch_bounds__(512) void k_score_resident(ScoreArgs a) {
 }
 
 // Section 4.1, boundary behaviour: a query that sees at most k tokens selects all of them, and no score
-// decides anything.  Writes the visible tokens (lo .. pos) of the kept blocks, ascending, then -1: the ids
-// are ascending, so only the first and the last kept block can be cut.
+// decides anything.  Writes the visible tokens (lo .. pos) of the kept blocks, ascending, then -1.  The ids
+// are ascending and visible (blocks_ascending), so only the first and the last kept block can be cut.
 template <int THREADS>
-__device__ __forceinline__ void take_all_visible(const int32_t* __restrict__ blk_ids, int m, int B, int n_blocks,
-                                                 int pos, int lo, int k, int32_t* __restrict__ out) {
+__device__ __forceinline__ void take_all_visible(const int32_t* __restrict__ blk_ids, int m, int B, int pos, int lo, int k, int32_t* __restrict__ out) {
   int n_used = 0;
   for (int i = threadIdx.x & 63; i < m; i += 64) {
-    const int blk = blk_ids[i];
-    if (blk >= 0 && blk < n_blocks) n_used = i + 1;
+    if (blk_ids[i] >= 0) n_used = i + 1;
   }
   n_used = (int)wave_max((uint32_t)n_used);
   auto first_of = [&](int slot) { const int r = blk_ids[slot] * B; return r > lo ? r : lo; };
@@ -976,7 +1008,12 @@ struct SelectArgs {
   int n_fixed;               // CAND / PAIRS: elements per row
   const int32_t* block_idx;  // MAP_CAND: [T, m] (global query indexing)
   int m, B, n_blocks;
-  int whole_rows;            // as ScoreArgs::whole_rows: such a row was not scored, all it sees is selected
+  // as ScoreArgs::whole_rows: such a row was not scored, all it sees is selected (BLOCKS / CAND); the rest
+  // is what never_neg_inf asks for
+  int whole_rows;
+  const float* w;            // [T, H]
+  int H;
+  const float* k_scale;      // [n_seq, n_blocks * B] (CAND with fp8 keys) or null
   int seg_len, n_seg;        // FLAT: the row is cut into n_seg segments of seg_len (grid.x)
   int k;
   int32_t* out_idx;          // [rows * n_seg, k]
@@ -1008,9 +1045,11 @@ __global__ __launch_bounds__(THREADS) void k_select(SelectArgs a) {
       const int cap = a.n_blocks * a.B;
       pos = pos < cap ? pos : cap - 1;          // (whatever seq_len says)
       const int lo = query_lo(a.q_lo, t, pos);
-      if (pos + 1 - lo <= a.whole_rows) {
-        take_all_visible<THREADS>(a.block_idx + (long)t * a.m, a.m, a.B, a.n_blocks, pos, lo, a.k,
-                                  a.out_idx + (long)row * a.k);
+      const int32_t* blk_ids = a.block_idx + (long)t * a.m;
+      if (pos + 1 - lo <= a.whole_rows &&
+          never_neg_inf(a.w + (long)t * a.H, a.H, a.k_scale ? a.k_scale + (long)s * cap : nullptr, lo, pos) &&
+          blocks_ascending(blk_ids, a.m, a.B, lo, pos)) {
+        take_all_visible<THREADS>(blk_ids, a.m, a.B, pos, lo, a.k, a.out_idx + (long)row * a.k);
         return;
       }
     } else {
@@ -1019,7 +1058,8 @@ __global__ __launch_bounds__(THREADS) void k_select(SelectArgs a) {
       // this segment's rows, cut at the first visible one rounded down to four (16-byte loads; the
       // up to three rows in between were written as -inf by the scoring kernel)
       const int lo_row = query_lo(a.q_lo, t, pos) / a.pos_div;
-      if (MAP == MAP_BLOCKS && n_vis - lo_row <= a.whole_rows) {
+      if (MAP == MAP_BLOCKS && n_vis - lo_row <= a.whole_rows &&
+          never_neg_inf(a.w + (long)t * a.H, a.H, nullptr, 0, 0)) {
         for (int p = threadIdx.x; p < a.k; p += THREADS)
           a.out_idx[(long)row * a.k + p] = p < n_vis - lo_row ? lo_row + p : -1;
         return;
@@ -1505,13 +1545,14 @@ __global__ __launch_bounds__(StreamSelect::kThreads, 8) void k_select_stream(Sel
 // ring slot 0, and that DMA has completed.
 template <int HG, int NW, int NB, int E1, int TILE>
 __device__ __forceinline__ void stage1_in_workgroup(const QFrag<HG>& f, const ScoreArgs& a, const void* pooled,
-                                                    int seq, int pos, int lo, int n_blocks, unsigned char* smem,
-                                                    float* sc, int32_t* blk_lds, int wave, bool primed = false) {
+                                                    int t, int seq, int pos, int lo, int n_blocks,
+                                                    unsigned char* smem, float* sc, int32_t* blk_lds, int wave,
+                                                    bool primed = false) {
   constexpr int NT = NW * 64;
   const int lane = threadIdx.x & 63;
   const int n_bvis = pos < 0 ? 0 : pos / a.B + 1;
   const int b_first = lo / a.B;   // first visible block (0 unless sequences are packed)
-  if (n_bvis - b_first <= a.m) {  // every visible block fits the budget
+  if (n_bvis - b_first <= a.m && never_neg_inf(a.w + (long)t * a.H, a.H, nullptr, 0, 0)) {   // all fit the budget
     for (int p = threadIdx.x; p < a.m; p += NT) blk_lds[p] = p < n_bvis - b_first ? b_first + p : -1;
     __syncthreads();
     return;
@@ -1575,7 +1616,7 @@ __global__ __launch_bounds__(512) void k_stage1_query(ScoreArgs a, const void* p
   const int n_blocks = (int)(a.rows_per_seq / a.B);
   {
     const int b_first = lo / a.B, n_bvis = pos < 0 ? 0 : pos / a.B + 1;
-    if (n_bvis - b_first <= a.m) {   // every visible block fits the budget: nothing to score
+    if (n_bvis - b_first <= a.m && never_neg_inf(a.w + (long)t * a.H, a.H, nullptr, 0, 0)) {   // nothing to score
       for (int p = threadIdx.x; p < a.m; p += NT) block_idx_out[(long)t * a.m + p] = p < n_bvis - b_first ? b_first + p : -1;
       return;
     }
@@ -1592,7 +1633,7 @@ __global__ __launch_bounds__(512) void k_stage1_query(ScoreArgs a, const void* p
   }
   qfrag_shared_complete<HG>(f, lds_address(q_lds));
   qfrag_ready<HG>(f);
-  stage1_in_workgroup<HG, NW, NB, E1, TILE>(f, a, pooled, seq, pos, lo, n_blocks, smem, sc, blk_lds, wave, true);
+  stage1_in_workgroup<HG, NW, NB, E1, TILE>(f, a, pooled, t, seq, pos, lo, n_blocks, smem, sc, blk_lds, wave, true);
   for (int p = threadIdx.x; p < a.m; p += NT) block_idx_out[(long)t * a.m + p] = blk_lds[p];
 }
 
@@ -1642,9 +1683,9 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_refine_fused(Score
   const int pos = query_pos(a, t, seq);
   const int n_vis = pos + 1;
   const int lo = query_lo(a.q_lo, t, pos);   // first visible token (0 unless sequences are packed)
-  if (E1 == 0 && n_vis - lo <= a.whole_rows) {
-    take_all_visible<NT>(a.block_idx + (long)t * a.m, a.m, a.B, (int)(a.rows_per_seq / a.B), pos, lo, k,
-                         topk_idx + (long)t * k);
+  // (the select below takes a score of -inf like any other: only the block list has to be Stage 1's)
+  if (E1 == 0 && n_vis - lo <= a.whole_rows && blocks_ascending(a.block_idx + (long)t * a.m, a.m, a.B, lo, pos)) {
+    take_all_visible<NT>(a.block_idx + (long)t * a.m, a.m, a.B, pos, lo, k, topk_idx + (long)t * k);
     return;
   }
   fine_select_prepare<NT, E>(fs);
@@ -1679,7 +1720,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_refine_fused(Score
     int32_t* blk_lds = reinterpret_cast<int32_t*>(sc + sc_floats);
     blk_ids = blk_lds;
     qfrag_ready<HG>(f);
-    stage1_in_workgroup<HG, NW, NB, E1, kTileBytes>(f, a, pooled, seq, pos, lo, n_blocks, smem, sc, blk_lds, wave);
+    stage1_in_workgroup<HG, NW, NB, E1, kTileBytes>(f, a, pooled, t, seq, pos, lo, n_blocks, smem, sc, blk_lds, wave);
     if (block_idx_out)
       for (int p = threadIdx.x; p < a.m; p += NT) block_idx_out[(long)t * a.m + p] = blk_lds[p];
   }

@@ -37,3 +37,60 @@ def test_queries_that_keep_everything(k_dtype, H, d, packed):
         wl = W.make_workload(f"all_{k_dtype}_{packed}_{len(lens)}", n_seq=len(lens), seq_len=lens, T=sum(lens), H=H, d=d,
                              B=B, m=m, k=k, q_dtype=qd, k_dtype=k_dtype, mode="varlen", seed=420)
         _run(W.pack(wl) if packed else wl, n=10000)
+
+
+def _routes_agree(Q, K, blocks, B, m, k):
+    """The ids must not depend on whether the scores are asked for (which scores and selects every row)."""
+    from paper_2603_28458_amd import hisa
+
+    short = hisa.hisa_token_refine_topk(Q, K, B, m, blocks, k)[0].cpu().numpy()
+    general = hisa.hisa_token_refine_topk(Q, K, B, m, blocks, k, want_topk_scores=True)[0].cpu().numpy()
+    assert np.array_equal(short, general), np.nonzero((short != general).any(1))[0]
+
+
+@pytest.mark.parametrize("T", [200, 300])        # two-kernel and fused Stage 2 (fp32: two-kernel)
+@pytest.mark.parametrize("k_dtype,H,d", [("bf16", 64, 128), ("fp8_e4m3", 32, 128), ("f32", 4, 64)])
+def test_rows_kept_whole_equal_the_scored_rows(k_dtype, H, d, T):
+    # visible tokens and blocks below the budgets, but block lists that Stage 1 does not write (any order,
+    # gaps, repeats, blocks out of sight or out of range), and scores of -inf, which drop a block in Stage 1
+    # and a token in the two-kernel Stage 2
+    import torch
+    from paper_2603_28458_amd import hisa
+
+    B, m, k = 32, 12, 320
+    f32 = k_dtype == "f32"
+    wl = W.make_workload(f"whole_{k_dtype}_{T}", seq_len=T, T=T, H=H, d=d, B=B, m=m, k=k,
+                         q_dtype="f32" if f32 else "bf16", k_dtype=k_dtype, seed=430)
+    print(f"\n[routes] {wl.name}", flush=True)
+    Q, K = hisa.to_device(wl)
+    pd = hisa.HISA_F32 if f32 else hisa.HISA_BF16
+    rng = np.random.default_rng(431)
+    nb = -(-T // B)
+    lists = np.full((T, m), -1, dtype=np.int32)
+    for t in range(T):
+        n = int(rng.integers(1, m + 1))
+        kind = t % 4
+        if kind == 0:
+            lists[t, :n] = rng.integers(-1, nb, n)                  # repeats, gaps, any order
+        elif kind == 1:
+            lists[t, :n] = rng.permutation(m)[:n]                   # blocks past the query and past the array
+        elif kind == 2:
+            p = rng.permutation(t // B + 1)[:n]
+            lists[t, :p.size] = np.sort(p)                          # ascending, not all of them
+        else:
+            p = np.arange(min(m, t // B + 3))
+            lists[t, :p.size] = p                                   # ascending, past the query's own block
+    _routes_agree(Q, K, torch.from_numpy(lists).cuda(), B, m, k)
+
+    Q.w[::3, 1] = -np.inf
+    Q.w[1::5, 0] *= -1.0
+    pooled = hisa.hisa_pool_blocks(K, B, pooled_dtype=pd)
+    short = hisa.hisa_block_score_topk(Q, K, pooled, pd, B, m)[0]
+    general = hisa.hisa_block_score_topk(Q, K, pooled, pd, B, m, want_scores=True)[0]
+    assert torch.equal(short, general)
+    _routes_agree(Q, K, short, B, m, k)
+    if k_dtype == "fp8_e4m3":
+        Q.w.abs_()
+        Q.w.clamp_(max=2.0)
+        K.k_scale[:, ::7] = -np.inf
+        _routes_agree(Q, K, short, B, m, k)
