@@ -240,7 +240,7 @@ int launch_fused_hg(const ScoreArgs& a, int k, int32_t* topk_idx, float* topk_sc
   constexpr int NW = EC > 32 ? 8 : kFusedWaves;
   constexpr int E = ((EC * 4 + NW - 1) / NW + 3) / 4 * 4;
   const size_t sh = (size_t)NW * kNBuf * TileGeom<KDT>::kBufBytes + (size_t)a.m * a.B * 4 +
-                    sizeof(FineSelSmem<NW * 64, E>);
+                    (kHistInRing<HG, KDT, NW, E, 0> ? 0 : FineSelSmem<NW * 64, E>::kHistBytes) + sizeof(FineSelSmem<NW * 64, E>);
   constexpr auto kern = k_refine_fused<HG, KDT, NW, kNBuf, E>;
   if (raise_lds_limit<kern>(sh)) return HISA_ERR_LAUNCH;
   hipLaunchKernelGGL(kern, dim3(a.t_count), dim3(NW * 64), sh, st, a, k, topk_idx, topk_scores,
@@ -265,7 +265,7 @@ int launch_indexer_hg(const ScoreArgs& a, const void* pooled, int k, int32_t* bl
   const int sc_floats = (int)round_up(a.m * a.B > M ? a.m * a.B : M, 32);
   const size_t tile = TileGeom<KDT>::kBufBytes < 8192 ? 8192 : TileGeom<KDT>::kBufBytes;
   const size_t sh = (size_t)NW * kNBuf * tile + (size_t)sc_floats * 4 + (size_t)round_up(a.m, 4) * 4 +
-                    sizeof(FineSelSmem<NW * 64, E>);
+                    FineSelSmem<NW * 64, E>::kHistBytes + sizeof(FineSelSmem<NW * 64, E>);
   constexpr auto kern = k_refine_fused<HG, KDT, NW, kNBuf, E, E1>;
   if (raise_lds_limit<kern>(sh)) return HISA_ERR_LAUNCH;
   hipLaunchKernelGGL(kern, dim3(a.t_count), dim3(NW * 64), sh, st, a, k, topk_idx, topk_scores, pooled,

@@ -1051,10 +1051,11 @@ __device__ __forceinline__ int select_topk(SelectSmem<THREADS, E>& sm, int n, in
 // k whatever the binning did (ties at tau are either all in or the check fails).  On any doubt -- a
 // crowded bin, the k-th among the masked entries, ties across the threshold, a count that does not
 // come out -- it returns false BEFORE writing anything, and the caller runs select_topk.
-// Its scratch is NOT shared with anything else in the kernel, so that the bins can be zeroed at
+// Its scratch is not shared with anything else in the kernel, so that the bins can be zeroed at
 // kernel start and the row's score range can be collected by the scoring waves as they go: the
-// select itself then needs five workgroup barriers (the general select: about sixteen).
-//   fine_select_prepare      at kernel start, every thread;
+// select itself then needs five workgroup barriers (the general select: about sixteen).  Only the
+// bins may lie in memory that is dead by then; they are zeroed there, and one more barrier follows.
+//   fine_select_prepare      every thread, before a barrier that precedes select_topk_fine;
 //   fine_select_range        after a wave's last score, every lane (x_max / x_min: the largest and
 //                            smallest score the lane has produced, NaN entries ignored), BEFORE the
 //                            barrier that ends scoring;
@@ -1067,7 +1068,7 @@ __device__ __forceinline__ int select_topk(SelectSmem<THREADS, E>& sm, int n, in
 template <int NT, int E>
 struct FineSelSmem {
   static constexpr int NBIN = NT <= 512 ? 2048 : 4 * NT, LCAP = 64, NW = NT / 64;   // >= 4 bins per thread
-  uint32_t hist[NBIN];
+  static constexpr int kHistBytes = NBIN * 4;   // the bins, uint32 [NBIN], passed on their own
   float row_max[NW], row_min[NW];
   uint32_t tot_a[NW], tot_b[NW];
   uint32_t n_list;
@@ -1096,8 +1097,8 @@ __device__ __forceinline__ float wave_max_f32(float v) {
 }
 
 template <int NT, int E>
-__device__ __forceinline__ void fine_select_prepare(FineSelSmem<NT, E>& sm) {
-  uint4* h4 = reinterpret_cast<uint4*>(sm.hist);
+__device__ __forceinline__ void fine_select_prepare(FineSelSmem<NT, E>& sm, uint32_t* hist) {
+  uint4* h4 = reinterpret_cast<uint4*>(hist);
   for (int b = threadIdx.x; b < FineSelSmem<NT, E>::NBIN / 4; b += NT) h4[b] = make_uint4(0u, 0u, 0u, 0u);
   if (threadIdx.x == 0) sm.n_list = 0u;
 }
@@ -1113,7 +1114,8 @@ __device__ __forceinline__ void fine_select_range(FineSelSmem<NT, E>& sm, float 
 }
 
 template <int NT, int E, class Vals, class Emit>
-__device__ __forceinline__ bool select_topk_fine(FineSelSmem<NT, E>& sm, int n, int k, Vals vals, Emit emit) {
+__device__ __forceinline__ bool select_topk_fine(FineSelSmem<NT, E>& sm, uint32_t* hist, int n, int k, Vals vals,
+                                                 Emit emit) {
   static_assert(E % 4 == 0, "elements per thread come in groups of four");
   using S = FineSelSmem<NT, E>;
   constexpr int NW = S::NW, NBIN = S::NBIN, BPT = NBIN / NT;
@@ -1166,7 +1168,7 @@ __device__ __forceinline__ bool select_topk_fine(FineSelSmem<NT, E>& sm, int n, 
   // the LDS byte address of its bin (4 * bin + the histogram's base): one multiply-add, one
   // conversion that rounds down (negative and NaN give 0), one mask.
   const float scale4 = 4.0f * (float)(NBIN - 2) * (1.0f - 0x1p-18f) / (hi - lo);
-  const uint32_t hist_base = lds_address(sm.hist);
+  const uint32_t hist_base = lds_address(hist);
   const float bias4 = 4.0f + (float)hist_base - lo * scale4;
   typedef uint32_t binvec __attribute__((ext_vector_type(E)));
   binvec bin;
@@ -1193,7 +1195,7 @@ __device__ __forceinline__ bool select_topk_fine(FineSelSmem<NT, E>& sm, int n, 
     uint32_t sum = 0;
 #pragma unroll
     for (int g = 0; g < BPT / 4; ++g) {
-      const uint4 c4 = *reinterpret_cast<const uint4*>(&sm.hist[t * BPT + 4 * g]);
+      const uint4 c4 = *reinterpret_cast<const uint4*>(&hist[t * BPT + 4 * g]);
       c[4 * g + 0] = c4.x;
       c[4 * g + 1] = c4.y;
       c[4 * g + 2] = c4.z;
@@ -1287,7 +1289,7 @@ __device__ __forceinline__ bool select_topk_fine(FineSelSmem<NT, E>& sm, int n, 
     if (w < wave) pos += tw;
   }
   if (taken != (uint32_t)k) return false;                      // ties across the threshold: not this path's case
-  emit(pos, v, tau, reinterpret_cast<int32_t*>(&sm.hist[tid]));
+  emit(pos, v, tau, reinterpret_cast<int32_t*>(&hist[tid]));
   return true;
 }
 

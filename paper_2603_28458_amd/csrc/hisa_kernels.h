@@ -1128,10 +1128,11 @@ __global__ __launch_bounds__(THREADS) void k_select(SelectArgs a) {
     // are the first and the last entry of the row: they are left out of the search, which then
     // looks for k - 2 among the others, and take the first and the last output position.
     __shared__ FineSelSmem<THREADS, E> fs;
+    __shared__ __align__(16) uint32_t fs_hist[FineSelSmem<THREADS, E>::NBIN];
     constexpr int kForced = MAP == MAP_BLOCKS ? 2 : 0;
     const int k_free = a.k - kForced;
     if (k_free >= 1 && n - kForced > k_free) {
-      fine_select_prepare<THREADS, E>(fs);
+      fine_select_prepare<THREADS, E>(fs, fs_hist);
       const float qnan = __uint_as_float(0xffffffffu);
       const int i0 = (int)threadIdx.x * E;
       float4 mine[E / 4];
@@ -1165,7 +1166,7 @@ __global__ __launch_bounds__(THREADS) void k_select(SelectArgs a) {
           }
         }
       };
-      if (select_topk_fine<THREADS, E>(fs, n, k_free, vals, emit_f)) {
+      if (select_topk_fine<THREADS, E>(fs, fs_hist, n, k_free, vals, emit_f)) {
         n_out = a.k;
         if (kForced && threadIdx.x == 0) {
           emit(0, first_vis, 0xffffffffu);
@@ -1659,6 +1660,17 @@ __global__ __launch_bounds__(512) void k_stage1_query(ScoreArgs a, const void* p
 // (Measured and not kept: each workgroup, once its scoring is over, pulling the query of the
 // workgroup 512 or 1024 positions behind it into the XCD's L2: 64K prefill +2 %, 16K -1 %, fp8 keys
 // and the 1M chunk unchanged.  The first read of a query is not what a workgroup waits for.)
+//
+// With 32 heads (HG = 1) a wave needs 124-143 registers, three or four waves per SIMD, and a tile is
+// only 8 MFMAs: such a launch waits for its tiles, and LDS decides how many workgroups hide that.  The
+// top-k's bins then lie in the tile rings, dead when the top-k begins (one more barrier), which makes
+// room for a third workgroup per CU with bf16 keys and 4096 candidates (57 -> 49 KB), a fourth with
+// fp8 keys and 4096 (42 -> 34 KB), a third with fp8 and 8192 (59 -> 51 KB).  Packed 24K bf16 prefill, m 32:
+// 536 -> 474 us; 16K prefills: bf16, m 32 767 -> 728 us; fp8, m 32 538 -> 521 us; fp8, m 64 932 -> 855 us.
+// With bf16 keys and 8192 candidates it makes room for nothing (72 KB or 64 KB: two), and is not done.
+template <int HG, int KDT, int NW, int E, int E1>
+constexpr bool kHistInRing = HG == 1 && E1 == 0 && NW == 4 && (KDT == DT_FP8 || E <= 16);
+
 template <int HG, int KDT, int NW, int NB, int E, int E1 = 0>
 __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_refine_fused(ScoreArgs a, int k,
                                                                            int32_t* topk_idx,
@@ -1675,8 +1687,13 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_refine_fused(Score
   float* sc = reinterpret_cast<float*>(smem + kStageBytes);   // m*B scores (swizzled: score_slot)
   SelectSmem<NT, E>& sm = *reinterpret_cast<SelectSmem<NT, E>*>(smem);
   // scratch of the top-k's fast path, behind everything else (shared with nothing: see select_topk_fine)
-  FineSelSmem<NT, E>& fs = *reinterpret_cast<FineSelSmem<NT, E>*>(
-      smem + kStageBytes + (E1 > 0 ? (size_t)sc_floats * 4 + (size_t)((a.m + 3) / 4 * 4) * 4 : (size_t)a.m * a.B * 4));
+  using Fine = FineSelSmem<NT, E>;
+  constexpr bool kInRing = kHistInRing<HG, KDT, NW, E, E1>;
+  static_assert(Fine::kHistBytes <= kStageBytes, "the bins must fit the rings");
+  unsigned char* behind =
+      smem + kStageBytes + (E1 > 0 ? (size_t)sc_floats * 4 + (size_t)((a.m + 3) / 4 * 4) * 4 : (size_t)a.m * a.B * 4);
+  uint32_t* fs_hist = reinterpret_cast<uint32_t*>(kInRing ? smem : behind);
+  Fine& fs = *reinterpret_cast<Fine*>(behind + (kInRing ? 0 : Fine::kHistBytes));
   const int t = a.t_begin + (gridDim.x - 1 - blockIdx.x);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   int seq;
@@ -1688,7 +1705,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_refine_fused(Score
     take_all_visible<NT>(a.block_idx + (long)t * a.m, a.m, a.B, pos, lo, k, topk_idx + (long)t * k);
     return;
   }
-  fine_select_prepare<NT, E>(fs);
+  if constexpr (!kInRing) fine_select_prepare<NT, E>(fs, fs_hist);
 
   // fp8 keys without Stage 1 in this launch: no wave needs the bf16 fragment, and the two-term
   // e4m3 fragment is built once for the workgroup (below) instead of once per wave
@@ -1824,6 +1841,10 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_refine_fused(Score
   // anything -- whenever the row is not its case, and the general select takes over.
   int n_out = -1;
   if (n_cand_slots > k) {
+    if constexpr (kInRing) {
+      fine_select_prepare<NT, E>(fs, fs_hist);
+      __syncthreads();
+    }
     auto vals = [&](int q) -> float4 { return *reinterpret_cast<const float4*>(sc + score_slot(4 * q)); };
     // Without the score output the thread's E candidates are written without a branch: every
     // element is stored, the ones not selected into a dump word of the thread's own.
@@ -1859,7 +1880,8 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_refine_fused(Score
         }
       }
     };
-    if (select_topk_fine<NT, E>(fs, n_cand_slots, k, vals, emit_f)) n_out = k;
+    if (select_topk_fine<NT, E>(fs, fs_hist, n_cand_slots, k, vals, emit_f)) n_out = k;
+    else if (kInRing) __syncthreads();   // every wave is through with the bins: select_topk's scratch lies there too
   }
   if (n_out < 0) n_out = select_topk<NT, E, false, false>(sm, n_cand_slots, k, load4, load1, emit);
   for (int p = n_out + threadIdx.x; p < k; p += NT) {

@@ -94,3 +94,26 @@ def test_rows_kept_whole_equal_the_scored_rows(k_dtype, H, d, T):
         Q.w.clamp_(max=2.0)
         K.k_scale[:, ::7] = -np.inf
         _routes_agree(Q, K, short, B, m, k)
+
+
+@pytest.mark.parametrize("k_dtype,m,k", [("bf16", 128, 1024), ("fp8_e4m3", 128, 2048), ("fp8_e4m3", 200, 700)])
+def test_top_k_bins_in_the_tile_rings(k_dtype, m, k):
+    # fused Stage 2 with 32 heads, up to 4096 and 8192 candidates: the one-pass top-k's bins share the rings with
+    # the general select, which takes over for rows of tied scores (all gates zero in every third query)
+    wl = W.make_workload(f"rings_{k_dtype}_{m}", seq_len=7000, T=300, H=32, d=128, B=32, m=m, k=k, q_dtype="bf16",
+                         k_dtype=k_dtype, seed=440)
+    _run(wl, n=40)
+    import torch
+    from paper_2603_28458_amd import hisa
+
+    Q, K = hisa.to_device(wl)
+    Q.w[::3] = 0.0
+    pooled = hisa.hisa_pool_blocks(K, wl.B)
+    blocks = hisa.hisa_block_score_topk(Q, K, pooled, hisa.HISA_BF16, wl.B, m)[0]
+    got = hisa.hisa_token_refine_topk(Q, K, wl.B, m, blocks, k)[0]
+    # the two-kernel path, which keeps its bins apart
+    want = hisa.hisa_token_refine_topk(Q, K, wl.B, m, blocks, k, want_cand_scores=True)[0]
+    assert torch.equal(got, want)
+    # tied rows: the first k candidates
+    first = (blocks[::3, :, None] * wl.B + torch.arange(wl.B, device="cuda")).flatten(1)[:, :k].int()
+    assert torch.equal(got[::3], first)
