@@ -117,3 +117,13 @@ def test_top_k_bins_in_the_tile_rings(k_dtype, m, k):
     # tied rows: the first k candidates
     first = (blocks[::3, :, None] * wl.B + torch.arange(wl.B, device="cuda")).flatten(1)[:, :k].int()
     assert torch.equal(got[::3], first)
+
+
+@pytest.mark.parametrize("n_seq,m,k_dtype,H", [(1, 20, "bf16", 64), (3, 250, "fp8_e4m3", 32), (65, 33, "fp8_e4m3", 64),
+                                               (130, 66, "bf16", 32), (255, 12, "fp8_e4m3", 64)])
+def test_tiles_per_wave_of_a_decode_batch(n_seq, m, k_dtype, H):
+    # Stage 2 below 256 queries: the number of tiles a wave walks follows from the queries and the candidates
+    # (1 to 16 here, the last workgroup of a query with some of them, or with idle waves)
+    wl = W.make_workload(f"tpw{n_seq}", n_seq=n_seq, seq_len=[2500 - 7 * i for i in range(n_seq)], T=n_seq, H=H,
+                         d=128, B=32, m=m, k=min(300, 32 * m), q_dtype="bf16", k_dtype=k_dtype, mode="decode", seed=450)
+    _run(wl, n=12)
