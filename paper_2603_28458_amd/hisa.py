@@ -114,8 +114,8 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 
 
 def _stream(stream) -> Optional[int]:
-    if stream is None:
-        stream = torch.cuda.current_stream()
+    if stream is None:   # the handle alone: torch.cuda.current_stream() builds a Stream object around it on every call
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
@@ -176,10 +176,10 @@ def hisa_workspace_bytes(op: int, queries: Queries, keys: Keys, B: int = 1, m: i
     return int(lib().hisa_workspace_bytes(op, C.byref(qc), C.byref(kc), B, m, k, int(want_scores)))
 
 
-def _ws(ws: Optional[torch.Tensor], nbytes: int, device) -> Optional[torch.Tensor]:
-    if ws is not None or nbytes == 0:
-        return ws
-    return torch.empty(nbytes, dtype=torch.uint8, device=device)
+def _ws(op: int, qc: _Queries, kc: _Keys, B: int, m: int, k: int, want_scores: bool, device) -> Optional[torch.Tensor]:
+    """A workspace for a call that was not given one."""
+    nbytes = int(lib().hisa_workspace_bytes(op, qc, kc, B, m, k, int(want_scores)))
+    return torch.empty(nbytes, dtype=torch.uint8, device=device) if nbytes else None
 
 
 _POOLED_TORCH = {HISA_F32: torch.float32, HISA_BF16: torch.bfloat16}
@@ -252,9 +252,9 @@ def hisa_block_score_topk(queries: Queries, keys: Keys, pooled: torch.Tensor, po
         block_idx = torch.empty((T, m), dtype=torch.int32, device=dev)
     if want_scores and block_scores is None:
         block_scores = torch.empty((T, M), dtype=torch.float32, device=dev)
-    ws = _ws(ws, hisa_workspace_bytes(OP_BLOCK_SCORE_TOPK, queries, keys, B, m, 0,
-                                      block_scores is not None), dev)
     qc, kc = queries.c(), keys.c()
+    if ws is None:
+        ws = _ws(OP_BLOCK_SCORE_TOPK, qc, kc, B, m, 0, block_scores is not None, dev)
     st = lib().hisa_block_score_topk(C.byref(qc), C.byref(kc), _ptr(pooled), pooled_dtype, B, m,
                                      _ptr(block_idx), _ptr(block_scores), _ptr(ws),
                                      0 if ws is None else ws.numel(), _stream(stream))
@@ -276,9 +276,9 @@ def hisa_token_refine_topk(queries: Queries, keys: Keys, B: int, m: int, block_i
         topk_scores = torch.empty((T, k), dtype=torch.float32, device=dev)
     if want_cand_scores and cand_scores is None:
         cand_scores = torch.empty((T, m * B), dtype=torch.float32, device=dev)
-    ws = _ws(ws, hisa_workspace_bytes(OP_TOKEN_REFINE_TOPK, queries, keys, B, m, k,
-                                      cand_scores is not None), dev)
     qc, kc = queries.c(), keys.c()
+    if ws is None:
+        ws = _ws(OP_TOKEN_REFINE_TOPK, qc, kc, B, m, k, cand_scores is not None, dev)
     st = lib().hisa_token_refine_topk(C.byref(qc), C.byref(kc), B, m, _ptr(block_idx), k, _ptr(topk_idx),
                                       _ptr(topk_scores), _ptr(cand_scores), _ptr(ws),
                                       0 if ws is None else ws.numel(), _stream(stream))
@@ -308,8 +308,9 @@ def dsa_flat_indexer_topk(queries: Queries, keys: Keys, k: int, topk_idx: Option
         topk_idx = torch.empty((T, k), dtype=torch.int32, device=dev)
     if want_topk_scores and topk_scores is None:
         topk_scores = torch.empty((T, k), dtype=torch.float32, device=dev)
-    ws = _ws(ws, hisa_workspace_bytes(OP_FLAT_TOPK, queries, keys, 1, 0, k), dev)
     qc, kc = queries.c(), keys.c()
+    if ws is None:
+        ws = _ws(OP_FLAT_TOPK, qc, kc, 1, 0, k, False, dev)
     st = lib().dsa_flat_indexer_topk(C.byref(qc), C.byref(kc), k, _ptr(topk_idx), _ptr(topk_scores),
                                      _ptr(ws), 0 if ws is None else ws.numel(), _stream(stream))
     _check(st, "dsa_flat_indexer_topk")
