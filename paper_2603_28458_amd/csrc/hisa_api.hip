@@ -171,8 +171,34 @@ void launch_prefill_mfma(ScoreArgs a, long n_rows_max, hipStream_t st) {
     hipLaunchKernelGGL((k_score_prefill<1, KDT>), grid, dim3(512), 0, st, a);
 }
 
+constexpr int kResidentMinT = 2048;
+
+template <int HG, int NQ>
+void launch_resident_nq(const ScoreArgs& a, hipStream_t st) {
+  const size_t sh = (size_t)((a.rows_per_seq + 31) / 32) * 8192;
+  dim3 grid((a.t_count + 8 * NQ - 1) / (8 * NQ));
+  // (a refusal to raise the LDS limit makes the launch fail, which the entry point reports)
+  (void)raise_lds_limit<k_score_resident<HG, NQ>>(sh);
+  hipLaunchKernelGGL((k_score_resident<HG, NQ>), grid, dim3(512), sh, st, a);
+}
+
+// Queries per wave of k_score_resident: as many as leave three workgroups for every four CUs (more of them
+// share one staging of the rows), down to one.
+// Whole prefill with 8 -> by this rule: 2100 queries (m 8) 79 -> 50 us, 6000 (B 64, m 32) 233 -> 210 us, 9000
+// (B 32, m 64) 364 -> 339 us, 12001 715 -> 701 us; a 3000-token chunk at 64K 514 -> 460 us; packed, 3000
+// queries (B 32, m 8) 92 -> 62 us (k_score_ranges 70 us), 12000 595 -> 576 us; 16384 unchanged (8 either way).
+template <int HG>
+void launch_resident_mfma(const ScoreArgs& a, hipStream_t st) {
+  constexpr int kFill = kCUs * 3 / 4 * 8;   // queries that give as many workgroups, at one query per wave
+  if (a.t_count >= 8 * kFill) launch_resident_nq<HG, 8>(a, st);
+  else if (a.t_count >= 4 * kFill) launch_resident_nq<HG, 4>(a, st);
+  else if (a.t_count >= 2 * kFill) launch_resident_nq<HG, 2>(a, st);
+  else launch_resident_nq<HG, 1>(a, st);
+}
+
 // Scores `a.t_count` queries against up to n_rows_max rows each (flat / Stage 1: rows of the
-// key array; gather: m*B slots).  key_dt is the dtype of the rows.
+// key array; gather: m*B slots).  key_dt is the dtype of the rows.  consecutive: one sequence, positions
+// that grow by one from query to query (in a packed stream, a.q_lo, too).
 void launch_score(int path, int key_dt, ScoreArgs a, long n_rows_max, bool consecutive,
                   hipStream_t st) {
   if (path == PATH_F32) {
@@ -184,22 +210,13 @@ void launch_score(int path, int key_dt, ScoreArgs a, long n_rows_max, bool conse
     return;
   }
   const bool gather = a.block_idx != nullptr;
-  if (!gather && consecutive && a.t_count >= 2048 && key_dt == HISA_BF16 && a.rows_per_seq <= 512) {
-    // all rows fit in LDS (Stage 1 up to 512 blocks): resident tiles, 64 queries per workgroup
-    constexpr int NQ = 8;
-    const size_t sh = (size_t)((a.rows_per_seq + 31) / 32) * 8192;
-    dim3 grid((a.t_count + 8 * NQ - 1) / (8 * NQ));
-    // (a refusal to raise the LDS limit makes the launch fail, which the entry point reports)
-    if (a.H == 64) {
-      (void)raise_lds_limit<k_score_resident<2, NQ>>(sh);
-      hipLaunchKernelGGL((k_score_resident<2, NQ>), grid, dim3(512), sh, st, a);
-    } else {
-      (void)raise_lds_limit<k_score_resident<1, NQ>>(sh);
-      hipLaunchKernelGGL((k_score_resident<1, NQ>), grid, dim3(512), sh, st, a);
-    }
+  if (!gather && consecutive && a.t_count >= kResidentMinT && key_dt == HISA_BF16 && a.rows_per_seq <= 512) {
+    // all rows fit in LDS (Stage 1 up to 512 blocks): resident tiles
+    if (a.H == 64) launch_resident_mfma<2>(a, st);
+    else launch_resident_mfma<1>(a, st);
     return;
   }
-  if (!gather && consecutive && a.t_count >= 64) {
+  if (!gather && consecutive && !a.q_lo && a.t_count >= 64) {
     if (key_dt == HISA_BF16) launch_prefill_mfma<DT_BF16>(a, n_rows_max, st);
     else launch_prefill_mfma<DT_FP8>(a, n_rows_max, st);
     return;
@@ -577,7 +594,7 @@ int hisa_block_score_topk(const hisa_queries* queries, const hisa_keys* keys, co
     hipLaunchKernelGGL(k_fill_f32, dim3((unsigned)((n + 255) / 256 > 4096 ? 4096 : (n + 255) / 256)),
                        dim3(256), 0, s, J, n, -__builtin_inff());
   }
-  launch_score(path, pooled_dtype, a, M, !queries->q_seq && !queries->q_pos && !queries->q_lo, s);
+  launch_score(path, pooled_dtype, a, M, !queries->q_seq && !queries->q_pos, s);
 
   SelectArgs sa = select_base(queries, keys);
   sa.scores = J;
@@ -774,7 +791,7 @@ int dsa_flat_indexer_topk(const hisa_queries* queries, const hisa_keys* keys, in
   float* scores = (float*)ws;
   float* part_sc = (float*)((char*)ws + chunk * p.ld * 4);
   int32_t* part_id = (int32_t*)((char*)part_sc + chunk * (long)p.n_seg * k * 4);
-  const bool consecutive = !queries->q_seq && !queries->q_pos && !queries->q_lo;
+  const bool consecutive = !queries->q_seq && !queries->q_pos;
 
   for (long t0 = 0; t0 < T; t0 += chunk) {
     const int tc = (int)((T - t0) < chunk ? (T - t0) : chunk);

@@ -902,6 +902,10 @@ __global__ __launch_bounds__(512) void k_score_prefill(ScoreArgs a) {
 // what is left per query is its 16 KB fragment from HBM, and eight waves per CU with one such load
 // in flight each keep that stream busy while the others compute.  Workgroup g serves the 8 * NQ
 // consecutive queries from 8 * NQ * g, wave w the queries w, w + 8, ...; longest prefixes first.
+// With sequences packed in one stream (q_lo) only the rows from the workgroup's first visible one are
+// staged, and a query starts at the sub-tile of its own first row (rows before it in there get -inf).
+// Packed bf16 prefills against k_score_ranges, which reloads every query's tiles: 24K, 32 heads, m 32 (most
+// rows not scored) 484 -> 452 us; two sequences of 30K, 64 heads 7360 -> 7020 us, 32 heads 5650 -> 5340 us.
 // (Measured and not kept: pulling the next query's fragment towards L2 while the current one is
 // scored, by DMA into a dummy LDS area since there are no registers for a second fragment: 10 %
 // slower, the extra transfers cost more than the shorter wait.  Also measured and not kept: the
@@ -921,12 +925,22 @@ __global__ __launch_bounds__(512) void k_score_resident(ScoreArgs a) {
   int seq_last;
   const int n_max = visible_rows(a, query_pos(a, a.t_begin + tl_last, seq_last));
   const int n_sub = (n_max + 31) >> 5;
+  int sub0 = 0;                          // first staged sub-tile
+  if (a.q_lo) {
+    uint32_t lo_min = 0x7fffffffu;
+    for (int tl = t0 + lane; tl <= tl_last; tl += 64) {
+      int seq;
+      const int lo = query_lo(a.q_lo, a.t_begin + tl, query_pos(a, a.t_begin + tl, seq));
+      lo_min = (uint32_t)lo < lo_min ? (uint32_t)(lo > 0 ? lo : 0) : lo_min;
+    }
+    sub0 = __builtin_amdgcn_readfirstlane((int)wave_min(lo_min)) / a.pos_div >> 5;
+  }
   __amdgpu_buffer_rsrc_t krsrc, srsrc;
   key_buffers<DT_BF16>(a, 0, krsrc, srsrc);
   const uint32_t tiles_addr = lds_address(tiles);
   {
     const u32x8 lane_offs = tile_lane_offsets_bf16();
-    for (int u = wave; u < n_sub; u += 8) tile_dma_bf16(krsrc, tiles_addr + u * 8192, u * 32 * (kD * 2), lane_offs);
+    for (int u = sub0 + wave; u < n_sub; u += 8) tile_dma_bf16(krsrc, tiles_addr + u * 8192, u * 32 * (kD * 2), lane_offs);
     wait_vmem_le<0>();
   }
   __syncthreads();
@@ -935,20 +949,23 @@ __global__ __launch_bounds__(512) void k_score_resident(ScoreArgs a) {
     if (tl >= a.t_count) break;          // wave-uniform; no barrier below
     const int t = a.t_begin + tl;
     int seq;
-    const int n_vis = visible_rows(a, query_pos(a, t, seq));
+    const int pos = query_pos(a, t, seq);
+    const int n_vis = visible_rows(a, pos);
     const int nu = (n_vis + 31) >> 5;    // <= n_sub: positions grow with the query index
-    if (nu <= 0 || (n_vis <= a.whole_rows && never_neg_inf(a.w + (long)t * a.H, a.H, nullptr, 0, 0))) continue;
+    const int lo_row = query_lo(a.q_lo, t, pos) / a.pos_div;
+    if (nu <= 0 || (n_vis - lo_row <= a.whole_rows && never_neg_inf(a.w + (long)t * a.H, a.H, nullptr, 0, 0))) continue;
     float* out = a.out + (long)tl * a.ld;
     QFrag<HG> f;
     load_qfrag<HG>(f, (const uint16_t*)a.q + (long)t * a.H * kD, a.w + (long)t * a.H);
     qfrag_ready<HG>(f);
     auto store = [&](int u, float s) {
       const int row = u * 32 + (lane & 31);
-      if (lane < 32 && row < n_vis) out[row] = s;
+      if (lane < 32 && row < n_vis) out[row] = row < lo_row ? neg_inf() : s;
     };
     // MFMAs of sub-tile u over the epilogue of sub-tile u-1 (two accumulator sets, unrolled by two)
-    accvec<HG> acc_a = mfma_tile<HG>(f, lds_read_tile_raw(tiles_addr)), acc_b;
-    int u = 0;                           // acc_a holds sub-tile u
+    int u = lo_row >> 5;                 // acc_a holds sub-tile u
+    u = __builtin_amdgcn_readfirstlane(u < nu ? u : nu - 1);
+    accvec<HG> acc_a = mfma_tile<HG>(f, lds_read_tile_raw(tiles_addr + u * 8192)), acc_b;
     for (; u + 2 < nu; u += 2) {
       acc_b = mfma_tile<HG>(f, lds_read_tile_raw(tiles_addr + (u + 1) * 8192));
       store(u, tile_epilogue<HG>(f, acc_a));

@@ -127,3 +127,15 @@ def test_tiles_per_wave_of_a_decode_batch(n_seq, m, k_dtype, H):
     wl = W.make_workload(f"tpw{n_seq}", n_seq=n_seq, seq_len=[2500 - 7 * i for i in range(n_seq)], T=n_seq, H=H,
                          d=128, B=32, m=m, k=min(300, 32 * m), q_dtype="bf16", k_dtype=k_dtype, mode="decode", seed=450)
     _run(wl, n=12)
+
+
+@pytest.mark.parametrize("T,H", [(2051, 64), (3073, 32), (6145, 64), (12290, 32)])
+@pytest.mark.parametrize("packed", [False, True])
+def test_queries_per_wave_of_the_resident_scoring_kernel(T, H, packed):
+    # Stage 1 up to 512 blocks: 1, 2, 4 and 8 queries per wave, the last workgroup with one query or a few; in a
+    # packed stream workgroups with queries of two sequences, whose blocks start in the middle of a sub-tile
+    cut = [0, 700, 701, T // 2 + 13, T]
+    lens = [b - a for a, b in zip(cut, cut[1:])] if packed else T
+    wl = W.make_workload(f"resident{T}_{packed}", n_seq=4 if packed else 1, seq_len=lens, T=T, H=H, d=128, B=32, m=9,
+                         k=256, q_dtype="bf16", k_dtype="bf16", mode="varlen" if packed else "prefill", seed=460)
+    _run(W.pack(wl) if packed else wl, n=48)
