@@ -20,6 +20,8 @@
 
 #include <type_traits>
 
+#include "fine_bins.h"
+
 namespace hisa {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -1090,6 +1092,11 @@ __device__ __forceinline__ uint32_t cvt_u32_sat(float t) {      // floor for t >
   asm("v_cvt_u32_f32 %0, %1" : "=v"(r) : "v"(t));
   return r;
 }
+__device__ __forceinline__ uint32_t med3_u32(uint32_t a, uint32_t lo, uint32_t hi) {   // a clamped to lo .. hi
+  uint32_t r;
+  asm("v_med3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(lo), "v"(hi));
+  return r;
+}
 __device__ __forceinline__ float wave_max_f32(float v) {
   return __uint_as_float(wave_all(__float_as_uint(v), [](uint32_t a, uint32_t b) {
     return __float_as_uint(vmax_f32(__uint_as_float(a), __uint_as_float(b)));
@@ -1162,14 +1169,9 @@ __device__ __forceinline__ bool select_topk_fine(FineSelSmem<NT, E>& sm, uint32_
     lo = vmin_f32(lo, sm.row_min[w]);
   }
   if (!(hi > lo) || !(hi - lo < inf)) return false;          // empty, constant or overflowing range (uniform)
-  // bin(x) = 1 + floor((x - lo) * scale) in 1 .. NBIN-1 for lo <= x <= hi, 0 for NaN: monotone in x, so
-  // every score in a higher bin is larger than every score in a lower one.  scale stops a hair
-  // short of (NBIN - 2) / (hi - lo), so the top bin needs no clamp.  A thread keeps, per element,
-  // the LDS byte address of its bin (4 * bin + the histogram's base): one multiply-add, one
-  // conversion that rounds down (negative and NaN give 0), one mask.
-  const float scale4 = 4.0f * (float)(NBIN - 2) * (1.0f - 0x1p-18f) / (hi - lo);
+  // A thread keeps, per element, the LDS byte address of its bin (fine_bins.h); NaN is counted in bin 0.
   const uint32_t hist_base = lds_address(hist);
-  const float bias4 = 4.0f + (float)hist_base - lo * scale4;
+  const FineBins bins = fine_bins<NBIN>(lo, hi, hist_base);
   typedef uint32_t binvec __attribute__((ext_vector_type(E)));
   binvec bin;
 #pragma unroll
@@ -1179,11 +1181,8 @@ __device__ __forceinline__ bool select_topk_fine(FineSelSmem<NT, E>& sm, uint32_
     asm volatile("v_mov_b32 %0, 1" : "=v"(one));               // (kept in a register across the atomics below)
 #pragma unroll
     for (int j = 0; j < E; ++j) {
-      const uint32_t addr = cvt_u32_sat(__builtin_fmaf(v[j], scale4, bias4)) & ~3u;
-      bin[j] = addr;
-      // NaN: the conversion gives 0, below the histogram; it is counted in bin 0
-      const uint32_t a_ok = addr > hist_base ? addr : hist_base;
-      asm volatile("ds_add_u32 %0, %1" : : "v"(a_ok), "v"(one) : "memory");
+      bin[j] = fine_bin_address(v[j], bins, cvt_u32_sat, med3_u32);
+      asm volatile("ds_add_u32 %0, %1" : : "v"(bin[j]), "v"(one) : "memory");
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");         // (the compiler does not count these)
   }
