@@ -1075,10 +1075,11 @@ __global__ __launch_bounds__(THREADS) void k_select(SelectArgs a) {
       // this segment's rows, cut at the first visible one rounded down to four (16-byte loads; the
       // up to three rows in between were written as -inf by the scoring kernel)
       const int lo_row = query_lo(a.q_lo, t, pos) / a.pos_div;
-      if (MAP == MAP_BLOCKS && n_vis - lo_row <= a.whole_rows &&
+      const int first = lo_row > 0 ? lo_row : 0;    // (below 0 for a query before position 0, which sees nothing)
+      if (MAP == MAP_BLOCKS && n_vis - first <= a.whole_rows &&
           never_neg_inf(a.w + (long)t * a.H, a.H, nullptr, 0, 0)) {
         for (int p = threadIdx.x; p < a.k; p += THREADS)
-          a.out_idx[(long)row * a.k + p] = p < n_vis - lo_row ? lo_row + p : -1;
+          a.out_idx[(long)row * a.k + p] = p < n_vis - first ? first + p : -1;
         return;
       }
       const int seg_end = (seg + 1) * a.seg_len < n_vis ? (seg + 1) * a.seg_len : n_vis;
@@ -1569,7 +1570,7 @@ __device__ __forceinline__ void stage1_in_workgroup(const QFrag<HG>& f, const Sc
   constexpr int NT = NW * 64;
   const int lane = threadIdx.x & 63;
   const int n_bvis = pos < 0 ? 0 : pos / a.B + 1;
-  const int b_first = lo / a.B;   // first visible block (0 unless sequences are packed)
+  const int b_first = lo > 0 ? lo / a.B : 0;   // first visible block (0 unless sequences are packed)
   if (n_bvis - b_first <= a.m && never_neg_inf(a.w + (long)t * a.H, a.H, nullptr, 0, 0)) {   // all fit the budget
     for (int p = threadIdx.x; p < a.m; p += NT) blk_lds[p] = p < n_bvis - b_first ? b_first + p : -1;
     __syncthreads();
@@ -1633,7 +1634,7 @@ __global__ __launch_bounds__(512) void k_stage1_query(ScoreArgs a, const void* p
   const int lo = query_lo(a.q_lo, t, pos);
   const int n_blocks = (int)(a.rows_per_seq / a.B);
   {
-    const int b_first = lo / a.B, n_bvis = pos < 0 ? 0 : pos / a.B + 1;
+    const int b_first = lo > 0 ? lo / a.B : 0, n_bvis = pos < 0 ? 0 : pos / a.B + 1;
     if (n_bvis - b_first <= a.m && never_neg_inf(a.w + (long)t * a.H, a.H, nullptr, 0, 0)) {   // nothing to score
       for (int p = threadIdx.x; p < a.m; p += NT) block_idx_out[(long)t * a.m + p] = p < n_bvis - b_first ? b_first + p : -1;
       return;

@@ -96,6 +96,32 @@ def test_rows_kept_whole_equal_the_scored_rows(k_dtype, H, d, T):
         _routes_agree(Q, K, short, B, m, k)
 
 
+@pytest.mark.parametrize("T", [200, 300])
+@pytest.mark.parametrize("k_dtype,H,d", [("bf16", 64, 128), ("fp8_e4m3", 32, 128), ("f32", 4, 64)])
+def test_queries_before_position_zero_see_nothing(k_dtype, H, d, T):
+    # as far before it as several blocks, where the first visible block must not come out below 0: every id is
+    # -1, whatever is asked for; the queries after them are as they are without them
+    from paper_2603_28458_amd import hisa
+
+    B, m, k = 32, 8, 130
+    f32 = k_dtype == "f32"
+    wl = W.make_workload(f"before_{k_dtype}_{T}", seq_len=T, T=T, H=H, d=d, B=B, m=m, k=k, q_dtype="f32" if f32 else "bf16",
+                         k_dtype=k_dtype, seed=435)
+    Q, K = hisa.to_device(wl)
+    pd = hisa.HISA_F32 if f32 else hisa.HISA_BF16
+    pooled = hisa.hisa_pool_blocks(K, B, pooled_dtype=pd)
+    Q.q_pos0 = -150
+    for scores in (False, True):
+        blocks = hisa.hisa_block_score_topk(Q, K, pooled, pd, B, m, want_scores=scores)[0]
+        ids = hisa.hisa_token_refine_topk(Q, K, B, m, blocks, k, want_topk_scores=scores)[0]
+        got = [blocks, ids]
+        if not f32:
+            got += list(hisa.hisa_indexer_topk(Q, K, pooled, pd, B, m, k, want_block_idx=True, want_topk_scores=scores))[:2]
+        for x in got:
+            x = x.cpu().numpy()
+            assert (x[:150] == -1).all() and (x[150:, 0] >= 0).all(), (scores, np.nonzero((x[:150] != -1).any(1))[0])
+
+
 @pytest.mark.parametrize("k_dtype,m,k", [("bf16", 128, 1024), ("fp8_e4m3", 128, 2048), ("fp8_e4m3", 200, 700)])
 def test_top_k_bins_in_the_tile_rings(k_dtype, m, k):
     # fused Stage 2 with 32 heads, up to 4096 and 8192 candidates: the one-pass top-k's bins share the rings with
