@@ -52,8 +52,9 @@ struct ScoreArgs {
   int t_begin, t_count;
   int tiles_per_wave;        // score_ranges: 32-key tiles each wave handles
   int groups;                // workgroups per query (score_ranges) or per 8 queries (score_prefill)
-  // A query that sees at most this many rows keeps them all and is not scored (-1: score all), unless a
-  // score of -inf could drop one of them or its block list is not Stage 1's (never_neg_inf, blocks_ascending).
+  // A query that sees at most this many rows keeps them all and is not scored (-1: score all), unless its
+  // score could drop one of them (-inf: never_neg_inf; in the fused kernel the mark of a masked slot: no_nan) or
+  // its block list is not Stage 1's (blocks_ascending).
   int whole_rows;
 };
 
@@ -94,6 +95,18 @@ __device__ __forceinline__ bool never_neg_inf(const float* __restrict__ w, int H
   for (int j = lane; j < H; j += 64) ok = ok && w[j] >= 0.f;
   if (scale)
     for (int r = (lo > 0 ? lo : 0) + lane; r <= pos; r += 64) ok = ok && scale[r] >= 0.f;
+  return __ballot(!ok) == 0ull;
+}
+
+// Wave-uniform: no gate and no key scale of this query is NaN.  A NaN among them can come out of the fused
+// kernel's sums as the all-ones pattern that marks masked slots there, and its row is then dropped.
+__device__ __forceinline__ bool no_nan(const float* __restrict__ w, int H, const float* __restrict__ scale, int lo,
+                                       int pos) {
+  const int lane = threadIdx.x & 63;
+  bool ok = true;
+  for (int j = lane; j < H; j += 64) ok = ok && w[j] == w[j];
+  if (scale)
+    for (int r = (lo > 0 ? lo : 0) + lane; r <= pos; r += 64) ok = ok && scale[r] == scale[r];
   return __ballot(!ok) == 0ull;
 }
 
@@ -1718,8 +1731,9 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_refine_fused(Score
   const int pos = query_pos(a, t, seq);
   const int n_vis = pos + 1;
   const int lo = query_lo(a.q_lo, t, pos);   // first visible token (0 unless sequences are packed)
-  // (the select below takes a score of -inf like any other: only the block list has to be Stage 1's)
-  if (E1 == 0 && n_vis - lo <= a.whole_rows && blocks_ascending(a.block_idx + (long)t * a.m, a.m, a.B, lo, pos)) {
+  // (the select below takes a score of -inf like any other, so gates and scales may be negative here)
+  if (E1 == 0 && n_vis - lo <= a.whole_rows && blocks_ascending(a.block_idx + (long)t * a.m, a.m, a.B, lo, pos) &&
+      no_nan(a.w + (long)t * a.H, a.H, a.k_scale ? a.k_scale + (long)seq * a.rows_per_seq : nullptr, lo, pos)) {
     take_all_visible<NT>(a.block_idx + (long)t * a.m, a.m, a.B, pos, lo, k, topk_idx + (long)t * k);
     return;
   }

@@ -94,6 +94,15 @@ def test_rows_kept_whole_equal_the_scored_rows(k_dtype, H, d, T):
         Q.w.clamp_(max=2.0)
         K.k_scale[:, ::7] = -np.inf
         _routes_agree(Q, K, short, B, m, k)
+    # memory filled with ones: the pattern that marks a masked slot in the fused kernel
+    Q.w.abs_()
+    ones = torch.full((1,), -1, dtype=torch.int32, device="cuda").view(torch.float32)
+    Q.w[::4, 2] = ones
+    _routes_agree(Q, K, short, B, m, k)
+    if k_dtype == "fp8_e4m3":
+        Q.w[:] = 1.0
+        K.k_scale[:, 5::9] = ones
+        _routes_agree(Q, K, short, B, m, k)
 
 
 @pytest.mark.parametrize("T", [200, 300])
