@@ -107,14 +107,14 @@ ScoreArgs base_args(const hisa_queries* q, const hisa_keys* k) {
 }
 
 // ---- scoring launches -------------------------------------------------------------------
-template <int KDT>
+template <int KDT, bool GATHER>
 void launch_ranges_mfma(ScoreArgs a, int n_tiles_max, hipStream_t st) {
   a.groups = (n_tiles_max + 4 * a.tiles_per_wave - 1) / (4 * a.tiles_per_wave);
   dim3 grid((unsigned)((long)a.groups * a.t_count));
   if (a.H == 64)
-    hipLaunchKernelGGL((k_score_ranges<2, KDT>), grid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL((k_score_ranges<2, KDT, GATHER>), grid, dim3(256), 0, st, a);
   else
-    hipLaunchKernelGGL((k_score_ranges<1, KDT>), grid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL((k_score_ranges<1, KDT, GATHER>), grid, dim3(256), 0, st, a);
 }
 
 constexpr int kCUs = 256;
@@ -227,8 +227,10 @@ void launch_score(int path, int key_dt, ScoreArgs a, long n_rows_max, bool conse
   int tpw = a.t_count >= 1024 ? 8 : (a.t_count >= 128 ? 4 : 2);
   if (gather) tpw = gather_tiles_per_wave(a.t_count, n_tiles, a.H == 32 && key_dt != HISA_BF16 ? 4 : 2);
   a.tiles_per_wave = tpw;
-  if (key_dt == HISA_BF16) launch_ranges_mfma<DT_BF16>(a, n_tiles, st);
-  else launch_ranges_mfma<DT_FP8>(a, n_tiles, st);
+  if (key_dt == HISA_BF16)
+    gather ? launch_ranges_mfma<DT_BF16, true>(a, n_tiles, st) : launch_ranges_mfma<DT_BF16, false>(a, n_tiles, st);
+  else
+    gather ? launch_ranges_mfma<DT_FP8, true>(a, n_tiles, st) : launch_ranges_mfma<DT_FP8, false>(a, n_tiles, st);
 }
 
 // ---- selection launches -----------------------------------------------------------------
@@ -659,6 +661,8 @@ static int token_refine_impl(const hisa_queries* queries, const hisa_keys* keys,
   a.ld = n_slots;
   // a query that sees at most k tokens selects them all: scored only if the scores are asked for
   a.whole_rows = (topk_scores || cand_scores) ? -1 : k;
+  a.k = k;
+  a.topk_idx = topk_idx;
 
   const bool fused = path == PATH_MFMA && !cand_scores && T >= 256 && n_slots <= 16384;
   if (fused) {
@@ -699,11 +703,7 @@ static int token_refine_impl(const hisa_queries* queries, const hisa_keys* keys,
   sa.block_idx = block_idx;
   sa.m = m;
   sa.B = B;
-  sa.n_blocks = keys->s_max / B;
   sa.whole_rows = a.whole_rows;
-  sa.w = a.w;
-  sa.H = a.H;
-  sa.k_scale = a.k_scale;
   sa.t_begin = 0;
   sa.k = k;
   sa.out_idx = topk_idx;

@@ -56,7 +56,13 @@ struct ScoreArgs {
   // score could drop one of them (-inf: never_neg_inf; in the fused kernel the mark of a masked slot: no_nan) or
   // its block list is not Stage 1's (blocks_ascending).
   int whole_rows;
+  int k;                     // gather with whole_rows: such a query's ids are written here, [T, k], and its score
+  int32_t* topk_idx;         //   row starts with kRowDoneBits
 };
+
+// First entry of a score row whose query needs no select (ScoreArgs::whole_rows): a signalling NaN, which no
+// arithmetic produces, so a score never looks like it.
+constexpr uint32_t kRowDoneBits = 0x7f800001u;
 
 // Position and sequence of query t, clamped so that no key row past the sequence is visible.
 __device__ __forceinline__ int query_pos(const ScoreArgs& a, int t, int& seq) {
@@ -119,6 +125,41 @@ __device__ __forceinline__ bool blocks_ascending(const int32_t* __restrict__ blk
     ok = ok && (b < 0 || (b >= b_lo && b <= b_hi && (i == 0 || (prev >= 0 && prev < b))));
   }
   return __ballot(!ok) == 0ull;
+}
+
+// Section 4.1, boundary behaviour: a query that sees at most k tokens selects all of them, and no score
+// decides anything.  Writes the visible tokens (lo .. pos) of the kept blocks, ascending, then -1.  The ids
+// are ascending and visible (blocks_ascending), so only the first and the last kept block can be cut.
+template <int THREADS>
+__device__ __forceinline__ void take_all_visible(const int32_t* __restrict__ blk_ids, int m, int B, int pos, int lo, int k, int32_t* __restrict__ out) {
+  int n_used = 0;
+  for (int i = threadIdx.x & 63; i < m; i += 64) {
+    if (blk_ids[i] >= 0) n_used = i + 1;
+  }
+  n_used = (int)wave_max((uint32_t)n_used);
+  auto first_of = [&](int slot) { const int r = blk_ids[slot] * B; return r > lo ? r : lo; };
+  auto end_of = [&](int slot) { const int r = (blk_ids[slot] + 1) * B; return r < pos + 1 ? r : pos + 1; };
+  const int head = n_used > 0 ? first_of(0) : 0;
+  const int c0 = n_used > 0 ? end_of(0) - head : 0;
+  const int total = n_used > 1 ? c0 + (n_used - 2) * B + (end_of(n_used - 1) - first_of(n_used - 1)) : c0;
+  for (int p = threadIdx.x; p < k; p += THREADS) {
+    int tok = -1;
+    if (p < c0) {
+      tok = head + p;
+    } else if (p < total) {
+      const int slot = (p - c0) / B;
+      tok = blk_ids[slot + 1] * B + (p - c0 - slot * B);
+    }
+    out[p] = tok;
+  }
+}
+
+// A gathering scoring kernel's answer for a query kept whole, by the one workgroup of the query that has its
+// first tiles: the ids, and the mark that tells the select to leave the row alone.
+template <int THREADS>
+__device__ __forceinline__ void finish_whole_row(const ScoreArgs& a, int t, int row, int pos, int lo) {
+  take_all_visible<THREADS>(a.block_idx + (long)t * a.m, a.m, a.B, pos, lo, a.k, a.topk_idx + (long)t * a.k);
+  if (threadIdx.x == 0) reinterpret_cast<uint32_t*>(a.out)[row * a.ld] = kRowDoneBits;
 }
 
 // Grids whose second dimension would be the query (row) index are launched one-dimensional, as
@@ -443,8 +484,10 @@ __global__ __launch_bounds__(256) void k_score_ranges_f32(ScoreArgs a, int keys_
   const int lo = query_lo(a.q_lo, t, pos);
   const int lo_row = lo / a.pos_div;   // first visible row when the rows are blocks or tokens in order
   if (visible_rows(a, pos) - lo_row <= a.whole_rows && never_neg_inf(a.w + (long)t * H, H, nullptr, lo, pos) &&
-      (!gather || blocks_ascending(a.block_idx + (long)t * a.m, a.m, a.B, lo, pos)))
+      (!gather || blocks_ascending(a.block_idx + (long)t * a.m, a.m, a.B, lo, pos))) {
+    if (gather && rg.x == 0) finish_whole_row<256>(a, t, rg.row, pos, lo);
     return;
+  }
   const float* q = (const float*)a.q + (long)t * H * d;
   for (int i = tid; i < H * d; i += 256) qs[i] = q[i];
   for (int i = tid; i < H; i += 256) qs[H * d + i] = a.w[(long)t * H + i];
@@ -688,7 +731,7 @@ struct LaneTable {
 // tiles, query); each wave runs the scoring pipeline over its own tiles (nothing is shared between
 // queries here: this is the decode / two-kernel path).  Writes scores, and -inf for masked slots
 // in gather mode.  tiles_per_wave <= 64.
-template <int HG, int KDT>
+template <int HG, int KDT, bool GATHER>
 __global__ __launch_bounds__(256, 2) void k_score_ranges(ScoreArgs a) {
   constexpr int NB = 2;
   __shared__ __align__(16) unsigned char ring[4 * NB * TileGeom<KDT>::kBufBytes];
@@ -697,20 +740,21 @@ __global__ __launch_bounds__(256, 2) void k_score_ranges(ScoreArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   int seq;
   const int pos = query_pos(a, t, seq);
-  const bool gather = a.block_idx != nullptr;
-  const int n_vis = gather ? pos + 1 : visible_rows(a, pos);
-  const int n_tiles = gather ? a.m * (a.B >> 5) : (n_vis + 31) >> 5;
+  const int n_vis = GATHER ? pos + 1 : visible_rows(a, pos);
+  const int n_tiles = GATHER ? a.m * (a.B >> 5) : (n_vis + 31) >> 5;
   // first visible row: a token when gathering, else a row of the array in order (token or block)
-  const int lo_row = gather ? query_lo(a.q_lo, t, pos) : query_lo(a.q_lo, t, pos) / a.pos_div;
+  const int lo_row = GATHER ? query_lo(a.q_lo, t, pos) : query_lo(a.q_lo, t, pos) / a.pos_div;
   const int v0 = rg.x * 4 * a.tiles_per_wave;
   if (v0 >= n_tiles) return;
   if (n_vis - lo_row <= a.whole_rows &&
       never_neg_inf(a.w + (long)t * a.H, a.H, a.k_scale ? a.k_scale + (long)seq * a.rows_per_seq : nullptr, lo_row, pos) &&
-      (!gather || blocks_ascending(a.block_idx + (long)t * a.m, a.m, a.B, lo_row, pos)))
+      (!GATHER || blocks_ascending(a.block_idx + (long)t * a.m, a.m, a.B, lo_row, pos))) {
+    if (GATHER && rg.x == 0) finish_whole_row<256>(a, t, rg.row, pos, lo_row);
     return;
+  }
   // in-order rows below the first visible one are neither scored nor written: the select starts
   // at the first visible row (rounded down to four)
-  if (!gather && (v0 + 4 * a.tiles_per_wave) * 32 <= lo_row) return;
+  if (!GATHER && (v0 + 4 * a.tiles_per_wave) * 32 <= lo_row) return;
   float* out = a.out + (long)rg.row * a.ld;
   const int n_blocks = (int)(a.rows_per_seq / a.B);
 
@@ -731,12 +775,12 @@ __global__ __launch_bounds__(256, 2) void k_score_ranges(ScoreArgs a) {
   {
     const int v = v0 + wave + 4 * lane;
     if (lane < a.tiles_per_wave && v < n_tiles) {
-      const TileLoc Lc = tile_loc(a, t, v, gather);
+      const TileLoc Lc = tile_loc(a, t, v, GATHER);
       my_out = (int)Lc.out0;
       const bool ok = Lc.row0 >= 0 && Lc.row0 < n_vis && Lc.row0 + 32 > lo_row &&
-                      (!gather || Lc.row0 / a.B < n_blocks);
+                      (!GATHER || Lc.row0 / a.B < n_blocks);
       if (ok) my_row = (int)Lc.row0;
-      else if (gather)
+      else if (GATHER)
         for (int x = 0; x < 32; ++x) out[my_out + x] = neg_inf();
     }
   }
@@ -764,7 +808,7 @@ __global__ __launch_bounds__(256, 2) void k_score_ranges(ScoreArgs a) {
   auto finish = [&](int j, float s) {
     const int row = rows.at(j) + (lane & 31);
     if (row >= n_vis || row < lo_row) s = neg_inf();
-    if (lane < 32 && (gather || row < n_vis)) out[outs.at(j) + lane] = s;
+    if (lane < 32 && (GATHER || row < n_vis)) out[outs.at(j) + lane] = s;
   };
   wave_pipeline<HG, KDT, NB>(fo, krsrc, srsrc, ring_addr, nj, row_at, finish);
 }
@@ -995,33 +1039,6 @@ __global__ __launch_bounds__(512) void k_score_resident(ScoreArgs a) {
   }
 }
 
-// Section 4.1, boundary behaviour: a query that sees at most k tokens selects all of them, and no score
-// decides anything.  Writes the visible tokens (lo .. pos) of the kept blocks, ascending, then -1.  The ids
-// are ascending and visible (blocks_ascending), so only the first and the last kept block can be cut.
-template <int THREADS>
-__device__ __forceinline__ void take_all_visible(const int32_t* __restrict__ blk_ids, int m, int B, int pos, int lo, int k, int32_t* __restrict__ out) {
-  int n_used = 0;
-  for (int i = threadIdx.x & 63; i < m; i += 64) {
-    if (blk_ids[i] >= 0) n_used = i + 1;
-  }
-  n_used = (int)wave_max((uint32_t)n_used);
-  auto first_of = [&](int slot) { const int r = blk_ids[slot] * B; return r > lo ? r : lo; };
-  auto end_of = [&](int slot) { const int r = (blk_ids[slot] + 1) * B; return r < pos + 1 ? r : pos + 1; };
-  const int head = n_used > 0 ? first_of(0) : 0;
-  const int c0 = n_used > 0 ? end_of(0) - head : 0;
-  const int total = n_used > 1 ? c0 + (n_used - 2) * B + (end_of(n_used - 1) - first_of(n_used - 1)) : c0;
-  for (int p = threadIdx.x; p < k; p += THREADS) {
-    int tok = -1;
-    if (p < c0) {
-      tok = head + p;
-    } else if (p < total) {
-      const int slot = (p - c0) / B;
-      tok = blk_ids[slot + 1] * B + (p - c0 - slot * B);
-    }
-    out[p] = tok;
-  }
-}
-
 // Row-wise exact top-k over scores in global memory (Eqs. 2, 6, 9).
 enum : int { MAP_FLAT = 0, MAP_BLOCKS = 1, MAP_CAND = 2, MAP_PAIRS = 3 };
 
@@ -1037,13 +1054,12 @@ struct SelectArgs {
   int t_begin;               // global query index of row 0
   int n_fixed;               // CAND / PAIRS: elements per row
   const int32_t* block_idx;  // MAP_CAND: [T, m] (global query indexing)
-  int m, B, n_blocks;
-  // as ScoreArgs::whole_rows: such a row was not scored, all it sees is selected (BLOCKS / CAND); the rest
-  // is what never_neg_inf asks for
+  int m, B;
+  // as ScoreArgs::whole_rows: such a row was not scored.  BLOCKS: all it sees is selected here (w, H: what
+  // never_neg_inf asks for); CAND: the scoring kernel has written the ids and marked the row
   int whole_rows;
   const float* w;            // [T, H]
   int H;
-  const float* k_scale;      // [n_seq, n_blocks * B] (CAND with fp8 keys) or null
   int seg_len, n_seg;        // FLAT: the row is cut into n_seg segments of seg_len (grid.x)
   int k;
   int32_t* out_idx;          // [rows * n_seg, k]
@@ -1065,43 +1081,30 @@ __global__ __launch_bounds__(THREADS) void k_select(SelectArgs a) {
   int n = a.n_fixed;
   int base = 0;
   int first_vis = 0;   // MAP_BLOCKS: entry of the first visible block (0 unless sequences are packed)
-  if (MAP != MAP_PAIRS) {
+  if (MAP == MAP_FLAT || MAP == MAP_BLOCKS) {
     int s = a.q_seq ? a.q_seq[t] : 0;
     s = s < 0 ? 0 : (s >= a.n_seq ? a.n_seq - 1 : s);
     int pos = a.q_pos ? a.q_pos[t] : a.q_pos0 + t;
     const int sl = a.seq_len[s];
     pos = pos < sl ? pos : sl - 1;
-    if constexpr (MAP == MAP_CAND) {
-      const int cap = a.n_blocks * a.B;
-      pos = pos < cap ? pos : cap - 1;          // (whatever seq_len says)
-      const int lo = query_lo(a.q_lo, t, pos);
-      const int32_t* blk_ids = a.block_idx + (long)t * a.m;
-      if (pos + 1 - lo <= a.whole_rows &&
-          never_neg_inf(a.w + (long)t * a.H, a.H, a.k_scale ? a.k_scale + (long)s * cap : nullptr, lo, pos) &&
-          blocks_ascending(blk_ids, a.m, a.B, lo, pos)) {
-        take_all_visible<THREADS>(blk_ids, a.m, a.B, pos, lo, a.k, a.out_idx + (long)row * a.k);
-        return;
-      }
-    } else {
-      int n_vis = pos < 0 ? 0 : pos / a.pos_div + 1;
-      n_vis = n_vis < a.ld ? n_vis : (int)a.ld;   // never past the score row, whatever seq_len says
-      // this segment's rows, cut at the first visible one rounded down to four (16-byte loads; the
-      // up to three rows in between were written as -inf by the scoring kernel)
-      const int lo_row = query_lo(a.q_lo, t, pos) / a.pos_div;
-      const int first = lo_row > 0 ? lo_row : 0;    // (below 0 for a query before position 0, which sees nothing)
-      if (MAP == MAP_BLOCKS && n_vis - first <= a.whole_rows &&
-          never_neg_inf(a.w + (long)t * a.H, a.H, nullptr, 0, 0)) {
-        for (int p = threadIdx.x; p < a.k; p += THREADS)
-          a.out_idx[(long)row * a.k + p] = p < n_vis - first ? first + p : -1;
-        return;
-      }
-      const int seg_end = (seg + 1) * a.seg_len < n_vis ? (seg + 1) * a.seg_len : n_vis;
-      base = seg * a.seg_len;
-      base = base > (lo_row & ~3) ? base : (lo_row & ~3);
-      n = seg_end - base;
-      n = (n < 0 || lo_row >= n_vis) ? 0 : n;     // (first visible row past the last: the query sees nothing)
-      first_vis = lo_row - base;                  // < 0 in later segments: no forced entry there
+    int n_vis = pos < 0 ? 0 : pos / a.pos_div + 1;
+    n_vis = n_vis < a.ld ? n_vis : (int)a.ld;   // never past the score row, whatever seq_len says
+    // this segment's rows, cut at the first visible one rounded down to four (16-byte loads; the
+    // up to three rows in between were written as -inf by the scoring kernel)
+    const int lo_row = query_lo(a.q_lo, t, pos) / a.pos_div;
+    const int first = lo_row > 0 ? lo_row : 0;    // (below 0 for a query before position 0, which sees nothing)
+    if (MAP == MAP_BLOCKS && n_vis - first <= a.whole_rows &&
+        never_neg_inf(a.w + (long)t * a.H, a.H, nullptr, 0, 0)) {
+      for (int p = threadIdx.x; p < a.k; p += THREADS)
+        a.out_idx[(long)row * a.k + p] = p < n_vis - first ? first + p : -1;
+      return;
     }
+    const int seg_end = (seg + 1) * a.seg_len < n_vis ? (seg + 1) * a.seg_len : n_vis;
+    base = seg * a.seg_len;
+    base = base > (lo_row & ~3) ? base : (lo_row & ~3);
+    n = seg_end - base;
+    n = (n < 0 || lo_row >= n_vis) ? 0 : n;     // (first visible row past the last: the query sees nothing)
+    first_vis = lo_row - base;                  // < 0 in later segments: no forced entry there
   }
   const long orow = (long)row * a.n_seg + seg;
   int32_t* oi = a.out_idx + orow * a.k;
@@ -1110,13 +1113,29 @@ __global__ __launch_bounds__(THREADS) void k_select(SelectArgs a) {
   const float* rowp = sc + base;
   // the row through a buffer descriptor of exactly n floats: no branch at the ragged end
   const __amdgpu_buffer_rsrc_t rrow = key_buffer(rowp, (long)n * 4);
+  // CAND: has the scoring kernel done this row?  Its first entry is asked for here and looked at once the row's
+  // own loads are on their way too, so that the question has no latency of its own.  (Looking the query's
+  // position up in front of those loads instead: refinement of 255 queries, B 32, m 8, bf16 11.6 -> 12.6 us,
+  // 16 queries, B 128, m 64 15.9 -> 16.9 us.)
+  const uint32_t mark = MAP == MAP_CAND && a.whole_rows >= 0 ? __builtin_amdgcn_raw_buffer_load_b32(rrow, 0, 0, 0) : 0u;
+  auto row_done = [&] { return MAP == MAP_CAND && __builtin_amdgcn_readfirstlane((int)mark) == (int)kRowDoneBits; };
+  constexpr bool kFine = (MAP == MAP_CAND || MAP == MAP_BLOCKS) && THREADS >= 256;
+  constexpr bool kEarly = MAP == MAP_CAND && !kFine;   // the row itself, asked for right behind
+  u32x4v early[kEarly ? E / 4 : 1];
+  if constexpr (kEarly) {
+#pragma unroll
+    for (int g = 0; g < E / 4; ++g)
+      early[g] = __builtin_amdgcn_raw_buffer_load_b128(rrow, ((int)threadIdx.x * E + 4 * g) * 4, 0, 0);
+    asm volatile("" ::: "memory");   // (they stay in front of the branch on the mark)
+    if (row_done()) return;
+  }
   auto key_of = [&](int i, float v) -> uint32_t {
     if (MAP == MAP_BLOCKS && (i == first_vis || i == n_last)) return 0xffffffffu;   // forced blocks
     return ordered_key(v);
   };
   auto load4 = [&](int q) -> uint4 {
     const int i = 4 * q;
-    const u32x4v r = __builtin_amdgcn_raw_buffer_load_b128(rrow, i * 4, 0, 0);
+    const u32x4v r = kEarly ? early[kEarly ? q - (int)threadIdx.x * (E / 4) : 0] : __builtin_amdgcn_raw_buffer_load_b128(rrow, i * 4, 0, 0);
     uint32_t kk[4];
 #pragma unroll
     for (int x = 0; x < 4; ++x) kk[x] = (i + x < n) ? key_of(i + x, __uint_as_float(r[x])) : 0u;
@@ -1149,7 +1168,7 @@ __global__ __launch_bounds__(THREADS) void k_select(SelectArgs a) {
     if (os) os[p] = key_to_score(key);
   };
   int n_out = -1;
-  if constexpr ((MAP == MAP_CAND || MAP == MAP_BLOCKS) && THREADS >= 256) {
+  if constexpr (kFine) {
     // Candidate rows (Stage 2 behind the separate scoring kernel) and block-score rows (Stage 1)
     // first try the one-pass top-k of the fused kernel: a handful of barriers instead of about
     // sixteen, which is most of this kernel's time when a decode batch gives it a few rows.  It
@@ -1185,6 +1204,7 @@ __global__ __launch_bounds__(THREADS) void k_select(SelectArgs a) {
         mine[g] = make_float4(x[0], x[1], x[2], x[3]);
       }
       fine_select_range<THREADS, E>(fs, x_max, x_min, (int)threadIdx.x >> 6);
+      if (row_done()) return;
       __syncthreads();
       auto vals = [&](int q) -> float4 { return mine[q - (i0 >> 2)]; };
       auto emit_f = [&](uint32_t p, const auto& v, float tau, int32_t*) {
@@ -1206,6 +1226,8 @@ __global__ __launch_bounds__(THREADS) void k_select(SelectArgs a) {
       } else {
         __syncthreads();
       }
+    } else if (row_done()) {
+      return;
     }
   }
   if (n_out < 0) n_out = select_topk<THREADS, E, true, MAP == MAP_BLOCKS>(sm, n, a.k, load4, load1, emit);

@@ -39,13 +39,26 @@ def test_queries_that_keep_everything(k_dtype, H, d, packed):
         _run(W.pack(wl) if packed else wl, n=10000)
 
 
-def _routes_agree(Q, K, blocks, B, m, k):
-    """The ids must not depend on whether the scores are asked for (which scores and selects every row)."""
+def _workspaces(op, Q, K, B, m, k):
+    """Workspaces a call may be handed: full of large scores, of NaN, of the mark that an earlier call leaves
+    in a row it did not score."""
+    import torch
     from paper_2603_28458_amd import hisa
 
-    short = hisa.hisa_token_refine_topk(Q, K, B, m, blocks, k)[0].cpu().numpy()
+    n = max(256, hisa.hisa_workspace_bytes(op, Q, K, B, m, k))
+    for word in (0x7f7fffff, -1, 0x7f800001):
+        yield torch.full((n // 4,), word, dtype=torch.int32, device="cuda").view(torch.uint8)
+
+
+def _routes_agree(Q, K, blocks, B, m, k):
+    """The ids must not depend on whether the scores are asked for (which scores and selects every row), nor
+    on what the workspace holds."""
+    from paper_2603_28458_amd import hisa
+
     general = hisa.hisa_token_refine_topk(Q, K, B, m, blocks, k, want_topk_scores=True)[0].cpu().numpy()
-    assert np.array_equal(short, general), np.nonzero((short != general).any(1))[0]
+    for ws in _workspaces(hisa.OP_TOKEN_REFINE_TOPK, Q, K, B, m, k):
+        short = hisa.hisa_token_refine_topk(Q, K, B, m, blocks, k, ws=ws)[0].cpu().numpy()
+        assert np.array_equal(short, general), np.nonzero((short != general).any(1))[0]
 
 
 @pytest.mark.parametrize("T", [200, 300])        # two-kernel and fused Stage 2 (fp32: two-kernel)
