@@ -1,0 +1,35 @@
+// How a launch's work is cut into workgroups, from its sizes alone: plain arithmetic, so that a host compiler
+// can take the same lines.
+#pragma once
+
+namespace hisa {
+
+constexpr int kCUs = 256;
+
+// Tiles per wave of a gathering k_score_ranges launch (Stage 2 of a decode batch).  A workgroup's four waves
+// walk tpw tiles each behind a set-up (query, position, block list) worth about six tiles.  Two workgroups on
+// a CU take twice as long as their share of it, one alone three quarters of that (nothing covers its waits):
+// a full round of 2 * kCUs workgroups counts 4, a last round 4 or, with at most one per CU, 3.
+// One wave per tile keeps a single query's latency short, a wide batch wants full rounds of long workgroups.
+// Refinement calls, us at the value picked here (in brackets at 4, which every batch below 1024 queries used to
+// get): bf16 keys, 64 heads, B 128: 1 query, m 64 1: 11.6 (13.1); 32, m 64 4: 23.4; 130, m 64 10: 52.8 (60.1);
+// 200, m 32 16: 39.4 (49.6); 200, m 64 13: 72.7 (81.3); 255, m 128 16: 171.7 (179.0); fp8 keys: 32, m 64 4: 17.7;
+// 200, m 64 13: 45.6 (58.6).  Over 432 such calls (1 to 255 queries, 8 to 512 tiles, both key types, 32 and 64
+// heads) the rule is 0.6 % from the best of 1 .. 16 on average and 8 % at most; against 4 tiles it is 3 %
+// slower at most.
+inline int gather_tiles_per_wave(long T, long n_tiles) {
+  int best = 1;
+  long best_cost = 0;
+  for (int tpw = 1; tpw <= 16; ++tpw) {
+    const long wgs = T * ((n_tiles + 4 * tpw - 1) / (4 * tpw));
+    const long rest = wgs % (2 * kCUs);
+    const long cost = (4 * (wgs / (2 * kCUs)) + (rest > kCUs ? 4 : rest > 0 ? 3 : 0)) * (tpw + 6);
+    if (tpw == 1 || cost < best_cost) {
+      best_cost = cost;
+      best = tpw;
+    }
+  }
+  return best;
+}
+
+}  // namespace hisa

@@ -6,6 +6,7 @@
 
 #include <atomic>
 
+#include "dispatch_rules.h"
 #include "hisa_kernels.h"
 
 using namespace hisa;
@@ -117,8 +118,6 @@ void launch_ranges_mfma(ScoreArgs a, int n_tiles_max, hipStream_t st) {
     hipLaunchKernelGGL((k_score_ranges<1, KDT, GATHER>), grid, dim3(256), 0, st, a);
 }
 
-constexpr int kCUs = 256;
-
 // Workgroups per 8 queries of k_score_prefill.  A CU holds one workgroup, so the time of a launch is
 // about (rounds over the CUs) x (key tiles per workgroup + 2 tiles' worth of set-up); this picks the
 // split with the least of that.  1024 queries at 64K keys: 128 workgroups, 1497 us with the select;
@@ -134,27 +133,6 @@ int prefill_split(long q_groups, long n_tiles) {
     if (cost < best_cost * 0.98) {
       best_cost = cost;
       best = s;
-    }
-  }
-  return best;
-}
-
-// Tiles per wave of a gathering k_score_ranges launch (Stage 2 of a decode batch), by the same pricing: a
-// workgroup's four waves walk tpw tiles each behind a set-up (query, block list) worth about four tiles, and
-// the chip holds wg_per_cu workgroups per CU.  One wave per tile keeps a single query's latency short, a wide
-// batch wants full rounds of long workgroups.  Whole decode step at B 128, m 64, by tiles per wave:
-// 200 fp8 sequences of 20K 4 76.5, 6 72.4, 8 72.1, 16 65.9 us; 130 of 30K 61.2, 56.3, 58.7, 59.2 us (6 fills
-// three rounds, 16 starts a second one); 128 bf16 sequences of 20K 74.7, 71.7, 70.1, 68.0 us; one query 2 25.1,
-// 4 26.2, 16 31.9 us, and 24.6 us with the 1 chosen here.
-int gather_tiles_per_wave(long T, long n_tiles, int wg_per_cu) {
-  int best = 1;
-  double best_cost = 1e30;
-  for (int tpw = 1; tpw <= 16; ++tpw) {
-    const long wgs = T * ((n_tiles + 4 * tpw - 1) / (4 * tpw));
-    const double cost = (double)((wgs + kCUs * wg_per_cu - 1) / (kCUs * wg_per_cu)) * (tpw + 4.0);
-    if (cost < best_cost) {
-      best_cost = cost;
-      best = tpw;
     }
   }
   return best;
@@ -225,7 +203,7 @@ void launch_score(int path, int key_dt, ScoreArgs a, long n_rows_max, bool conse
   // few queries: spread one query's tiles over many workgroups; many queries: amortise the
   // query-fragment load over more tiles
   int tpw = a.t_count >= 1024 ? 8 : (a.t_count >= 128 ? 4 : 2);
-  if (gather) tpw = gather_tiles_per_wave(a.t_count, n_tiles, a.H == 32 && key_dt != HISA_BF16 ? 4 : 2);
+  if (gather) tpw = gather_tiles_per_wave(a.t_count, n_tiles);
   a.tiles_per_wave = tpw;
   if (key_dt == HISA_BF16)
     gather ? launch_ranges_mfma<DT_BF16, true>(a, n_tiles, st) : launch_ranges_mfma<DT_BF16, false>(a, n_tiles, st);

@@ -1,0 +1,34 @@
+"""The library's dispatch rules (csrc/dispatch_rules.h), compiled for the host: a test that sits where a rule
+changes its answer asks the rule itself."""
+import ctypes
+import functools
+import os
+import subprocess
+import tempfile
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2603_28458_amd", "csrc")
+
+_SHIM = """
+#include "dispatch_rules.h"
+extern "C" int tiles_per_wave(long T, long n_tiles) { return hisa::gather_tiles_per_wave(T, n_tiles); }
+"""
+
+
+@functools.lru_cache(maxsize=None)
+def _lib():
+    with tempfile.TemporaryDirectory() as d:
+        src, so = os.path.join(d, "shim.cpp"), os.path.join(d, "shim.so")
+        with open(src, "w") as f:
+            f.write(_SHIM)
+        subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", f"-I{CSRC}", src, "-o", so], check=True)
+        return ctypes.CDLL(so)
+
+
+def _call(name, *args):
+    fn = getattr(_lib(), name)
+    fn.argtypes, fn.restype = [ctypes.c_long] * len(args), ctypes.c_int
+    return fn(*args)
+
+
+def tiles_per_wave(T, n_tiles):
+    return _call("tiles_per_wave", T, n_tiles)

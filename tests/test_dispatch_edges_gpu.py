@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 from paper_2603_28458_amd import workloads as W
+from tests.host_rules import tiles_per_wave
 from tests.parity import run_and_check, sample_queries
 
 pytestmark = pytest.mark.gpu
@@ -167,14 +168,19 @@ def test_top_k_bins_in_the_tile_rings(k_dtype, m, k):
     assert torch.equal(got[::3], first)
 
 
-@pytest.mark.parametrize("n_seq,m,k_dtype,H", [(1, 20, "bf16", 64), (3, 250, "fp8_e4m3", 32), (65, 33, "fp8_e4m3", 64),
-                                               (130, 66, "bf16", 32), (255, 12, "fp8_e4m3", 64)])
-def test_tiles_per_wave_of_a_decode_batch(n_seq, m, k_dtype, H):
-    # Stage 2 below 256 queries: the number of tiles a wave walks follows from the queries and the candidates
-    # (1 to 16 here, the last workgroup of a query with some of them, or with idle waves)
-    wl = W.make_workload(f"tpw{n_seq}", n_seq=n_seq, seq_len=[2500 - 7 * i for i in range(n_seq)], T=n_seq, H=H,
-                         d=128, B=32, m=m, k=min(300, 32 * m), q_dtype="bf16", k_dtype=k_dtype, mode="decode", seed=450)
-    _run(wl, n=12)
+@pytest.mark.parametrize("n_seq,B,m,k_dtype,H,tpw", [
+    (1, 32, 20, "bf16", 64, 1), (65, 32, 33, "fp8_e4m3", 64, 3), (3, 32, 250, "fp8_e4m3", 32, 1), (64, 64, 32, "bf16", 64, 4),
+    (130, 32, 66, "bf16", 32, 6), (32, 128, 125, "bf16", 64, 8), (130, 128, 64, "fp8_e4m3", 64, 10),
+    (130, 32, 128, "bf16", 64, 11), (255, 32, 191, "fp8_e4m3", 32, 12), (200, 128, 64, "bf16", 32, 13),
+    (200, 32, 128, "fp8_e4m3", 64, 16), (255, 64, 128, "bf16", 64, 16)])
+def test_tiles_per_wave_of_a_decode_batch(n_seq, B, m, k_dtype, H, tpw):
+    # Stage 2 below 256 queries: the number of tiles a wave walks follows from the queries and the candidates;
+    # lengths of which some leave fewer blocks than m, so that the last workgroups of a query have idle waves
+    assert tiles_per_wave(n_seq, m * B // 32) == tpw
+    L = m * B + 300
+    wl = W.make_workload(f"tpw{n_seq}", n_seq=n_seq, seq_len=[L - (37 * i) % (L // 2) for i in range(n_seq)], T=n_seq, H=H,
+                         d=128, B=B, m=m, k=min(300, B * m), q_dtype="bf16", k_dtype=k_dtype, mode="decode", seed=450)
+    _run(wl, n=8)
 
 
 @pytest.mark.parametrize("T,H", [(2051, 64), (3073, 32), (6145, 64), (12290, 32)])
