@@ -681,7 +681,6 @@ static int token_refine_impl(const hisa_queries* queries, const hisa_keys* keys,
   sa.block_idx = block_idx;
   sa.m = m;
   sa.B = B;
-  sa.whole_rows = a.whole_rows;
   sa.t_begin = 0;
   sa.k = k;
   sa.out_idx = topk_idx;

@@ -746,12 +746,14 @@ __global__ __launch_bounds__(256, 2) void k_score_ranges(ScoreArgs a) {
   const int lo_row = GATHER ? query_lo(a.q_lo, t, pos) : query_lo(a.q_lo, t, pos) / a.pos_div;
   const int v0 = rg.x * 4 * a.tiles_per_wave;
   if (v0 >= n_tiles) return;
-  if (n_vis - lo_row <= a.whole_rows &&
-      never_neg_inf(a.w + (long)t * a.H, a.H, a.k_scale ? a.k_scale + (long)seq * a.rows_per_seq : nullptr, lo_row, pos) &&
-      (!GATHER || blocks_ascending(a.block_idx + (long)t * a.m, a.m, a.B, lo_row, pos))) {
-    if (GATHER && rg.x == 0) finish_whole_row<256>(a, t, rg.row, pos, lo_row);
-    return;
-  }
+  const uint16_t* q_t = (const uint16_t*)a.q + (long)t * a.H * kD;
+  const float* w_t = a.w + (long)t * a.H;
+  auto whole_row = [&] {
+    return n_vis - lo_row <= a.whole_rows &&
+           never_neg_inf(w_t, a.H, a.k_scale ? a.k_scale + (long)seq * a.rows_per_seq : nullptr, lo_row, pos) &&
+           (!GATHER || blocks_ascending(a.block_idx + (long)t * a.m, a.m, a.B, lo_row, pos));
+  };
+  if (!GATHER && whole_row()) return;
   // in-order rows below the first visible one are neither scored nor written: the select starts
   // at the first visible row (rounded down to four)
   if (!GATHER && (v0 + 4 * a.tiles_per_wave) * 32 <= lo_row) return;
@@ -762,12 +764,19 @@ __global__ __launch_bounds__(256, 2) void k_score_ranges(ScoreArgs a) {
   // the LDS of the tile rings, which are not in use yet
   static_assert(sizeof(ring) >= 32 * HG * 260, "the shared query fragment is staged in the rings");
   typename Operands<HG, KDT>::Frag fo;
-  if constexpr (KDT == DT_FP8) {
-    split_query_shared<HG, 4>((const uint16_t*)a.q + (long)t * a.H * kD, a.w + (long)t * a.H, ring, wave, fo);
-  } else {
-    load_qfrag_shared<HG, 4>(fo, (const uint16_t*)a.q + (long)t * a.H * kD, a.w + (long)t * a.H,
-                             (long)a.H * kD * 2, lds_address(ring), wave);
+  SplitShare<HG, 4> q_share;
+  if constexpr (KDT == DT_FP8) split_query_request<HG, 4>(q_share, q_t, w_t, wave);
+  else qfrag_shared_request<HG, 4>(fo, q_t, w_t, (long)a.H * kD * 2, lds_address(ring), wave);
+  if constexpr (GATHER) {   // (asked while the query is on its way: a decode batch never is a whole row)
+    asm volatile("" ::: "memory");
+    if (whole_row()) {
+      if (rg.x == 0) finish_whole_row<256>(a, t, rg.row, pos, lo_row);
+      wait_vmem_le<0>();    // (nothing may still be on its way into this workgroup's LDS)
+      return;
+    }
   }
+  if constexpr (KDT == DT_FP8) split_query_complete<HG, 4>(q_share, ring, wave, fo);
+  else qfrag_shared_complete<HG>(fo, lds_address(ring));
 
   // this wave's tiles: v = v0 + wave + 4 i; lane i looks its tile up; tiles without a visible key
   // are filled with -inf here (gather mode) and left out of the pipeline
@@ -1055,8 +1064,8 @@ struct SelectArgs {
   int n_fixed;               // CAND / PAIRS: elements per row
   const int32_t* block_idx;  // MAP_CAND: [T, m] (global query indexing)
   int m, B;
-  // as ScoreArgs::whole_rows: such a row was not scored.  BLOCKS: all it sees is selected here (w, H: what
-  // never_neg_inf asks for); CAND: the scoring kernel has written the ids and marked the row
+  // BLOCKS: as ScoreArgs::whole_rows: such a row was not scored, and all it sees is selected here (w, H: what
+  // never_neg_inf asks for).  (CAND: the scoring kernel has written the ids and marked the row.)
   int whole_rows;
   const float* w;            // [T, H]
   int H;
@@ -1117,7 +1126,7 @@ __global__ __launch_bounds__(THREADS) void k_select(SelectArgs a) {
   // own loads are on their way too, so that the question has no latency of its own.  (Looking the query's
   // position up in front of those loads instead: refinement of 255 queries, B 32, m 8, bf16 11.6 -> 12.6 us,
   // 16 queries, B 128, m 64 15.9 -> 16.9 us.)
-  const uint32_t mark = MAP == MAP_CAND && a.whole_rows >= 0 ? __builtin_amdgcn_raw_buffer_load_b32(rrow, 0, 0, 0) : 0u;
+  const uint32_t mark = MAP == MAP_CAND ? __builtin_amdgcn_raw_buffer_load_b32(rrow, 0, 0, 0) : 0u;
   auto row_done = [&] { return MAP == MAP_CAND && __builtin_amdgcn_readfirstlane((int)mark) == (int)kRowDoneBits; };
   constexpr bool kFine = (MAP == MAP_CAND || MAP == MAP_BLOCKS) && THREADS >= 256;
   constexpr bool kEarly = MAP == MAP_CAND && !kFine;   // the row itself, asked for right behind
