@@ -5,6 +5,7 @@
 namespace hisa {
 
 constexpr int kCUs = 256;
+constexpr long kLdsPerCU = 160 * 1024;
 
 // Tiles per wave of a gathering k_score_ranges launch (Stage 2 of a decode batch).  A workgroup's four waves
 // walk tpw tiles each behind a set-up (query, position, block list) worth about six tiles.  Two workgroups on
@@ -30,6 +31,27 @@ inline int gather_tiles_per_wave(long T, long n_tiles) {
     }
   }
   return best;
+}
+
+// Workgroups that a CU holds: by their LDS, and at most max_wgs of them by their registers.
+inline int wgs_per_cu(long lds, int max_wgs) {
+  const long n = kLdsPerCU / lds;
+  return n < 1 ? 1 : n < max_wgs ? (int)n : max_wgs;
+}
+
+// Fused Stage 2 with 32 heads: do the top-k's bins lie in the tile rings, so that `with` instead of `without`
+// workgroups fit on a CU (k_refine_fused, wgs_per_cu)?  One more workgroup hides more of the tiles' latency (16K prefill,
+// m 32, bf16 keys 733 -> 668 us, fp8 keys, m 64 +10 %), except where
+// * it saves no round over the CUs: the same rounds are then only longer (fp8 keys, m 64, 2 -> 3 workgroups:
+//   600 queries 28 % faster, 1000 queries 7 % slower; m 32, 3 -> 4: 1000 queries 24 % faster, 1200 3 % slower);
+// * three workgroups' tiles wash each other out of the 4 MB L2 of their XCD: bf16 keys of 64K tokens of one
+//   sequence, queries that agree on nothing, 1058 -> 1294 us (neighbours that agree: 972 -> 865).  Up to 48K tokens
+//   every measured call gains 4-13 %, at 56K some lose up to 13 %, at 64K 18 %.  The queries of a packed stream see
+//   only a part of it (pieces of 4K to 48K of a 64K or 128K stream gain 8-15 %; one piece of 64K loses 4 %);
+//   fp8 keys are half as wide (64K: +10 to 18 %).
+inline bool hist_in_ring(long T, long s_max, bool packed, bool fp8, int without, int with) {
+  if ((T + kCUs * with - 1) / (kCUs * with) >= (T + kCUs * without - 1) / (kCUs * without)) return false;
+  return fp8 || packed || s_max <= 49152;
 }
 
 }  // namespace hisa

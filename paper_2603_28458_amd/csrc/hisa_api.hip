@@ -250,6 +250,22 @@ SelectArgs select_base(const hisa_queries* q, const hisa_keys* k) {
 
 // Fused Stage 2: kFusedWaves waves per query; EC = candidates per thread of a 256-thread select
 // (16: up to 4096 candidates, 32: up to 8192, 64: up to 16384); with 8 waves the per-thread count halves.
+template <int HG, int KDT, int NW, int E, bool RING>
+size_t fused_lds(const ScoreArgs& a) {
+  return (size_t)NW * kNBuf * TileGeom<KDT>::kBufBytes + (size_t)a.m * a.B * 4 +
+         (RING ? 0 : FineSelSmem<NW * 64, E>::kHistBytes) + sizeof(FineSelSmem<NW * 64, E>);
+}
+
+template <int HG, int KDT, int NW, int E, bool RING>
+int launch_fused_ring(const ScoreArgs& a, int k, int32_t* topk_idx, float* topk_scores, hipStream_t st) {
+  const size_t sh = fused_lds<HG, KDT, NW, E, RING>(a);
+  constexpr auto kern = k_refine_fused<HG, KDT, NW, kNBuf, E, 0, RING>;
+  if (raise_lds_limit<kern>(sh)) return HISA_ERR_LAUNCH;
+  hipLaunchKernelGGL(kern, dim3(a.t_count), dim3(NW * 64), sh, st, a, k, topk_idx, topk_scores,
+                     (const void*)nullptr, (int32_t*)nullptr, 0);
+  return HISA_OK;
+}
+
 template <int HG, int KDT, int EC>
 int launch_fused_hg(const ScoreArgs& a, int k, int32_t* topk_idx, float* topk_scores,
                     hipStream_t st) {
@@ -257,13 +273,14 @@ int launch_fused_hg(const ScoreArgs& a, int k, int32_t* topk_idx, float* topk_sc
   // that one gets 8 waves (two per SIMD; and 32 instead of 64 candidates per thread in the select)
   constexpr int NW = EC > 32 ? 8 : kFusedWaves;
   constexpr int E = ((EC * 4 + NW - 1) / NW + 3) / 4 * 4;
-  const size_t sh = (size_t)NW * kNBuf * TileGeom<KDT>::kBufBytes + (size_t)a.m * a.B * 4 +
-                    (kHistInRing<HG, KDT, NW, E, 0> ? 0 : FineSelSmem<NW * 64, E>::kHistBytes) + sizeof(FineSelSmem<NW * 64, E>);
-  constexpr auto kern = k_refine_fused<HG, KDT, NW, kNBuf, E>;
-  if (raise_lds_limit<kern>(sh)) return HISA_ERR_LAUNCH;
-  hipLaunchKernelGGL(kern, dim3(a.t_count), dim3(NW * 64), sh, st, a, k, topk_idx, topk_scores,
-                     (const void*)nullptr, (int32_t*)nullptr, 0);
-  return HISA_OK;
+  if constexpr (kCanRing<HG, KDT, NW, E>) {
+    constexpr int kByRegisters = KDT == DT_FP8 && E <= 16 ? 4 : 3;
+    if (hist_in_ring(a.t_count, a.rows_per_seq, a.q_lo != nullptr, KDT == DT_FP8,
+                     wgs_per_cu(fused_lds<HG, KDT, NW, E, false>(a), kByRegisters),
+                     wgs_per_cu(fused_lds<HG, KDT, NW, E, true>(a), kByRegisters)))
+      return launch_fused_ring<HG, KDT, NW, E, true>(a, k, topk_idx, topk_scores, st);
+  }
+  return launch_fused_ring<HG, KDT, NW, E, false>(a, k, topk_idx, topk_scores, st);
 }
 
 template <int KDT, int EC>

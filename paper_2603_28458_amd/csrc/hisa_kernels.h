@@ -1723,17 +1723,16 @@ __global__ __launch_bounds__(512) void k_stage1_query(ScoreArgs a, const void* p
 // workgroup 512 or 1024 positions behind it into the XCD's L2: 64K prefill +2 %, 16K -1 %, fp8 keys
 // and the 1M chunk unchanged.  The first read of a query is not what a workgroup waits for.)
 //
-// With 32 heads (HG = 1) a wave needs 124-143 registers, three or four waves per SIMD, and a tile is
+// RING: with 32 heads (HG = 1) a wave needs 124-143 registers, three or four waves per SIMD, and a tile is
 // only 8 MFMAs: such a launch waits for its tiles, and LDS decides how many workgroups hide that.  The
-// top-k's bins then lie in the tile rings, dead when the top-k begins (one more barrier), which makes
+// top-k's bins may then lie in the tile rings, dead when the top-k begins (one more barrier), which makes
 // room for a third workgroup per CU with bf16 keys and 4096 candidates (57 -> 49 KB), a fourth with
-// fp8 keys and 4096 (42 -> 34 KB), a third with fp8 and 8192 (59 -> 51 KB).  Packed 24K bf16 prefill, m 32:
-// 536 -> 474 us; 16K prefills: bf16, m 32 767 -> 728 us; fp8, m 32 538 -> 521 us; fp8, m 64 932 -> 855 us.
+// fp8 keys and 4096 (42 -> 34 KB), a third with fp8 and 8192 (59 -> 51 KB).  hist_in_ring says when.
 // With bf16 keys and 8192 candidates it makes room for nothing (72 KB or 64 KB: two), and is not done.
-template <int HG, int KDT, int NW, int E, int E1>
-constexpr bool kHistInRing = HG == 1 && E1 == 0 && NW == 4 && (KDT == DT_FP8 || E <= 16);
+template <int HG, int KDT, int NW, int E>
+constexpr bool kCanRing = HG == 1 && NW == 4 && (KDT == DT_FP8 || E <= 16);
 
-template <int HG, int KDT, int NW, int NB, int E, int E1 = 0>
+template <int HG, int KDT, int NW, int NB, int E, int E1 = 0, bool RING = false>
 __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_refine_fused(ScoreArgs a, int k,
                                                                            int32_t* topk_idx,
                                                                            float* topk_scores,
@@ -1750,8 +1749,8 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_refine_fused(Score
   SelectSmem<NT, E>& sm = *reinterpret_cast<SelectSmem<NT, E>*>(smem);
   // scratch of the top-k's fast path, behind everything else (shared with nothing: see select_topk_fine)
   using Fine = FineSelSmem<NT, E>;
-  constexpr bool kInRing = kHistInRing<HG, KDT, NW, E, E1>;
-  static_assert(Fine::kHistBytes <= kStageBytes, "the bins must fit the rings");
+  constexpr bool kInRing = RING;
+  static_assert(!RING || (E1 == 0 && Fine::kHistBytes <= kStageBytes), "the bins must fit the rings");
   unsigned char* behind =
       smem + kStageBytes + (E1 > 0 ? (size_t)sc_floats * 4 + (size_t)((a.m + 3) / 4 * 4) * 4 : (size_t)a.m * a.B * 4);
   uint32_t* fs_hist = reinterpret_cast<uint32_t*>(kInRing ? smem : behind);

@@ -10,6 +10,9 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 
 _SHIM = """
 #include "dispatch_rules.h"
+extern "C" int in_ring(long T, long s_max, long packed, long fp8, long without, long with) {
+  return hisa::hist_in_ring(T, s_max, packed, fp8, without, with);
+}
 extern "C" int tiles_per_wave(long T, long n_tiles) { return hisa::gather_tiles_per_wave(T, n_tiles); }
 """
 
@@ -32,3 +35,7 @@ def _call(name, *args):
 
 def tiles_per_wave(T, n_tiles):
     return _call("tiles_per_wave", T, n_tiles)
+
+
+def in_ring(T, s_max, packed, fp8, without, with_):
+    return bool(_call("in_ring", T, s_max, packed, fp8, without, with_))

@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 from paper_2603_28458_amd import workloads as W
-from tests.host_rules import tiles_per_wave
+from tests.host_rules import in_ring, tiles_per_wave
 from tests.parity import run_and_check, sample_queries
 
 pytestmark = pytest.mark.gpu
@@ -145,27 +145,53 @@ def test_queries_before_position_zero_see_nothing(k_dtype, H, d, T):
             assert (x[:150] == -1).all() and (x[150:, 0] >= 0).all(), (scores, np.nonzero((x[:150] != -1).any(1))[0])
 
 
-@pytest.mark.parametrize("k_dtype,m,k", [("bf16", 128, 1024), ("fp8_e4m3", 128, 2048), ("fp8_e4m3", 200, 700)])
-def test_top_k_bins_in_the_tile_rings(k_dtype, m, k):
-    # fused Stage 2 with 32 heads, up to 4096 and 8192 candidates: the one-pass top-k's bins share the rings with
-    # the general select, which takes over for rows of tied scores (all gates zero in every third query)
-    wl = W.make_workload(f"rings_{k_dtype}_{m}", seq_len=7000, T=300, H=32, d=128, B=32, m=m, k=k, q_dtype="bf16",
-                         k_dtype=k_dtype, seed=440)
-    _run(wl, n=40)
+@pytest.mark.parametrize("k_dtype,T,m,k,wgs", [("bf16", 600, 128, 1024, 2), ("fp8_e4m3", 800, 128, 1024, 3),
+                                               ("fp8_e4m3", 600, 256, 2048, 2)])
+@pytest.mark.parametrize("kind", ["tied", "groups", "zero", "random"])
+def test_top_k_bins_in_the_tile_rings(k_dtype, T, m, k, wgs, kind):
+    # fused Stage 2 with 32 heads: the one-pass top-k's bins share the rings with the general select, which takes
+    # over for a row it declines.  tied: 30 % of the scores are equal and the k-th is one of them: declined with
+    # the bins full, for a crowded bin.  groups: about 20 equal scores around every rank, the k-th among them:
+    # declined after the last check.  zero: every score equal: declined before a bin is touched
     import torch
     from paper_2603_28458_amd import hisa
+    from tests.test_fine_select import expected_row, one_head_queries
 
-    Q, K = hisa.to_device(wl)
-    Q.w[::3] = 0.0
-    pooled = hisa.hisa_pool_blocks(K, wl.B)
-    blocks = hisa.hisa_block_score_topk(Q, K, pooled, hisa.HISA_BF16, wl.B, m)[0]
-    got = hisa.hisa_token_refine_topk(Q, K, wl.B, m, blocks, k)[0]
+    B, L = 32, 9000
+    assert in_ring(T, L, False, k_dtype != "bf16", wgs, wgs + 1)      # (the form under test; T = 300 takes the other)
+    wl = W.make_workload(f"rings_{k_dtype}_{m}", seq_len=L, T=T, H=32, d=128, B=B, m=m, k=k, q_dtype="bf16", k_dtype=k_dtype,
+                         seed=440)
+    if kind == "random":
+        _run(wl, n=40)
+        return
+    rng = np.random.default_rng(441)
+    if kind == "tied":
+        level = np.where(rng.random(L) < 0.3, 128, np.where(rng.random(L) < 0.2, rng.integers(129, 256, L), rng.integers(0, 128, L)))
+    else:
+        level = rng.integers(0, 200 * m // 128, L) if kind == "groups" else np.zeros(L, np.int64)
+    Q = hisa.Queries(**one_head_queries(32, T, {0: 1.0, 1: 256.0}), q_pos0=L - T)
+    keys = torch.zeros((1, L, 128))
+    scale = None
+    if k_dtype == "bf16":
+        keys[0, :, 0], keys[0, :, 1] = torch.from_numpy(level % 256).float(), torch.from_numpy(level // 256).float()
+        keys = keys.bfloat16().cuda()
+    else:
+        keys[0, :, 0] = 1.0
+        keys = keys.to(torch.float8_e4m3fn).view(torch.uint8).cuda()
+        scale = torch.from_numpy(level).float()[None].cuda()
+    K = hisa.Keys(k=torch.nn.functional.pad(keys, (0, 0, 0, -L % B)), seq_len=torch.tensor([L], dtype=torch.int32).cuda(),
+                  dtype=hisa.DTYPE_CODE[k_dtype], k_scale=None if scale is None else torch.nn.functional.pad(scale, (0, -L % B)))
+    print(f"\n[rings] {k_dtype} m={m} {kind}", flush=True)
+    lists = np.sort(np.argsort(rng.random((T, (L - T) // B)), 1)[:, :m], 1).astype(np.int32)
+    blocks = torch.from_numpy(lists).cuda()
+    got = hisa.hisa_token_refine_topk(Q, K, B, m, blocks, k)[0]
     # the two-kernel path, which keeps its bins apart
-    want = hisa.hisa_token_refine_topk(Q, K, wl.B, m, blocks, k, want_cand_scores=True)[0]
+    want = hisa.hisa_token_refine_topk(Q, K, B, m, blocks, k, want_cand_scores=True)[0]
     assert torch.equal(got, want)
-    # tied rows: the first k candidates
-    first = (blocks[::3, :, None] * wl.B + torch.arange(wl.B, device="cuda")).flatten(1)[:, :k].int()
-    assert torch.equal(got[::3], first)
+    got = got.cpu().numpy()
+    for t in range(0, T, 7):
+        tok = (lists[t][:, None] * B + np.arange(B)).ravel()
+        assert np.array_equal(got[t], expected_row(level[tok], tok, k)), t
 
 
 @pytest.mark.parametrize("n_seq,B,m,k_dtype,H,tpw", [

@@ -1,5 +1,5 @@
 """The rules that cut a launch into workgroups, over the sizes they are asked for."""
-from tests.host_rules import tiles_per_wave
+from tests.host_rules import in_ring, tiles_per_wave
 
 
 def _cost(T, n_tiles, tpw):
@@ -22,3 +22,17 @@ def test_tiles_per_wave():
 def test_tiles_per_wave_at_the_sizes_its_figures_are_for():
     sizes = {(1, 256): 1, (32, 256): 4, (130, 256): 10, (200, 128): 16, (200, 256): 13, (255, 512): 16}
     assert {s: tiles_per_wave(*s) for s in sizes} == sizes
+
+
+def test_bins_in_the_tile_rings():
+    # two or three workgroups per CU: where a third saves a round (one of 512 queries turns into one of 768)
+    for T, want in ((1, False), (512, False), (513, True), (768, True), (769, False), (1024, False), (1025, True),
+                    (65536, True)):
+        assert in_ring(T, 16384, False, True, 2, 3) == want, T
+    # three or four
+    for T, want in ((768, False), (769, True), (1024, True), (1025, False), (1537, True), (2100, False), (65536, True)):
+        assert in_ring(T, 16384, False, True, 3, 4) == want, T
+    assert not in_ring(65536, 16384, False, True, 3, 3)          # no workgroup more
+    # bf16 keys of one long sequence; fp8 keys and packed streams at any length
+    assert in_ring(16384, 49152, False, False, 2, 3) and not in_ring(16384, 49184, False, False, 2, 3)
+    assert in_ring(16384, 1 << 20, True, False, 2, 3) and in_ring(16384, 1 << 20, False, True, 2, 3)

@@ -76,23 +76,27 @@ def test_every_score_of_a_narrow_row_has_a_bin(addresses):
 
 
 # ---------------------------------------------------------------------------------------------------------
-def _expected(scores, ids, k):
+def expected_row(scores, ids, k):
     """Top k by (score descending, id ascending), ids ascending, -1 padded; scores / ids of one row."""
     pick = np.sort(ids[np.argsort(-scores, kind="stable")[:k]])
     return np.concatenate([pick, np.full(k - pick.size, -1, pick.dtype)])
 
 
-def _rows(dtype, H, T, n_rows, level):
-    """Queries whose only gated head scores row r at exactly 1000 + level[r] units in the last place (2^-14):
-    every partial sum is a float32 number, so any order of summation gives these scores bit for bit."""
+def one_head_queries(H, T, weights):
+    """T equal queries of H heads of which one is gated: it scores a key by `weights`, {dimension: weight}."""
     from paper_2603_28458_amd import hisa
 
-    q = torch.zeros((T, H, 128))
-    w = torch.zeros((T, H))
+    q, w = torch.zeros((T, H, 128)), torch.zeros((T, H))
     w[:, 0] = 1.0
-    q[:, 0, 0] = 1.0
-    q[:, 0, 1], q[:, 0, 2] = 2.0 ** -14, 2.0 ** -6
-    Q = dict(q=q.bfloat16().cuda(), w=w.cuda(), dtype=hisa.HISA_BF16)
+    for dim, x in weights.items():
+        q[:, 0, dim] = x
+    return dict(q=q.bfloat16().cuda(), w=w.cuda(), dtype=hisa.HISA_BF16)
+
+
+def _rows(dtype, H, T, n_rows, level):
+    """Queries that score row r at exactly 1000 + level[r] units in the last place (2^-14): every partial sum
+    is a float32 number, so any order of summation gives these scores bit for bit."""
+    Q = one_head_queries(H, T, {0: 1.0, 1: 2.0 ** -14, 2: 2.0 ** -6})
     keys = torch.zeros((1, n_rows, 128))
     lv = torch.from_numpy(level)
     if dtype == "bf16":
@@ -128,7 +132,7 @@ def test_stage2_on_scores_a_few_ulps_apart(dtype, H, m, T, spread):
         for lists, ids in ((blocks, got), (one_blocks, one)):
             tok = (lists[t][:, None] * B + np.arange(B)).ravel()
             tok = tok[tok <= L - T - 7 + t]
-            assert np.array_equal(ids[t], _expected(level[tok], tok, k)), t
+            assert np.array_equal(ids[t], expected_row(level[tok], tok, k)), t
 
 
 @pytest.mark.gpu
@@ -149,4 +153,4 @@ def test_stage1_on_scores_a_few_ulps_apart(spread):
         ids = np.arange(own + 1)
         score = level[ids].astype(np.float64)
         score[[0, own]] = np.inf                 # forced
-        assert np.array_equal(got[t], _expected(score, ids, m)), t
+        assert np.array_equal(got[t], expected_row(score, ids, m)), t
