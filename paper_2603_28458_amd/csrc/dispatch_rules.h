@@ -7,6 +7,38 @@ namespace hisa {
 constexpr int kCUs = 256;
 constexpr long kLdsPerCU = 160 * 1024;
 
+// Workgroups per 8 queries of k_score_prefill: the key tiles (128 rows) of 8 queries are cut into that many
+// ranges.  rows_first, rows_last: what the first and the last query see; the queries between them grow evenly and
+// the longest start first.  A CU holds one workgroup.  With a workgroup's time as its tiles and three more, the
+// launch takes at least as long as its longest workgroup, as its work spread over the CUs, and as r times its
+// 256 (r - 1) + 1-th longest when there are r rounds (a CU has r of them at least that long); this takes the
+// fewest ranges within 2 % of the least.  1024 queries at 64K keys: 128 workgroups, 1497 us with the select; 256
+// (split by 2) 964 us; 512 queries 1369 -> 494 us (by 4), 100 queries at 128K fp8 keys 2605 -> 340 us (by 16).
+// Over 416 calls (64 to 16000 queries, 300 to 200000 rows, flat and Stage 1), measured with 1 .. 32 ranges, the
+// rule is 0.2 % from the best on average and 6 % at most, and one is 3 % slower than unsplit.  (Priced by the length
+// of the key array and as if every query saw all of it: 3000 queries of a 4000-key prefill 5 % slower than
+// unsplit, 1500 queries at 300 of 4096 blocks 33 -> 44 us.)  From four rounds on the split is left alone: 8 rounds
+// of 16K-key rows measured the same with 1, 2 and 4.
+inline int prefill_split(long q_groups, long rows_first, long rows_last) {
+  if (q_groups >= 4 * kCUs) return 1;
+  const double hi = (double)((rows_last + 127) / 128), lo = rows_first < 128 ? 1.0 : rows_first / 128.0;
+  int best = 1;
+  double best_cost = 0.0;
+  for (int s = 1; s <= 32 && (s == 1 || s <= hi); ++s) {
+    const long wgs = q_groups * s, rounds = (wgs + kCUs - 1) / kCUs;
+    const double longest = hi / s + 3.0;
+    const double work = (wgs * 3.0 + q_groups * (hi + lo) / 2.0) / kCUs;
+    const double last_round = rounds * ((hi - (hi - lo) * (double)(kCUs * (rounds - 1)) / wgs) / s + 3.0);
+    double cost = longest > work ? longest : work;
+    cost = cost > last_round ? cost : last_round;
+    if (s == 1 || cost < best_cost * 0.98) {
+      best_cost = cost;
+      best = s;
+    }
+  }
+  return best;
+}
+
 // Tiles per wave of a gathering k_score_ranges launch (Stage 2 of a decode batch).  A workgroup's four waves
 // walk tpw tiles each behind a set-up (query, position, block list) worth about six tiles.  Two workgroups on
 // a CU take twice as long as their share of it, one alone three quarters of that (nothing covers its waits):

@@ -118,30 +118,13 @@ void launch_ranges_mfma(ScoreArgs a, int n_tiles_max, hipStream_t st) {
     hipLaunchKernelGGL((k_score_ranges<1, KDT, GATHER>), grid, dim3(256), 0, st, a);
 }
 
-// Workgroups per 8 queries of k_score_prefill.  A CU holds one workgroup, so the time of a launch is
-// about (rounds over the CUs) x (key tiles per workgroup + 2 tiles' worth of set-up); this picks the
-// split with the least of that.  1024 queries at 64K keys: 128 workgroups, 1497 us with the select;
-// 256 (split by 2) 964 us; 512 queries 1369 -> 494 us (by 4), 100 queries at 128K fp8 keys 2605 -> 340 us
-// (by 16), 3000 at 32K 1523 -> 1209 us (by 2: three rounds of half the length instead of two).  From
-// four rounds on the split is left alone: 8 rounds of 16K-key rows measured the same with 1, 2 and 4.
-int prefill_split(long q_groups, long n_tiles) {
-  if (q_groups >= 4 * kCUs) return 1;
-  int best = 1;
-  double best_cost = 1e30;
-  for (int s = 1; s <= 32 && s <= n_tiles; ++s) {
-    const double cost = (double)((q_groups * s + kCUs - 1) / kCUs) * ((double)n_tiles / s + 2.0);
-    if (cost < best_cost * 0.98) {
-      best_cost = cost;
-      best = s;
-    }
-  }
-  return best;
-}
-
 template <int KDT>
 void launch_prefill_mfma(ScoreArgs a, long n_rows_max, hipStream_t st) {
   const int qg = (a.t_count + 7) / 8;
-  a.groups = prefill_split(qg, (n_rows_max + 127) / 128);
+  // the rows that the first and the last query see, if their sequence reaches that far (its length is on the GPU)
+  auto rows_of = [&](long pos) { return pos < 0 ? 0 : pos / a.pos_div + 1 < n_rows_max ? pos / a.pos_div + 1 : n_rows_max; };
+  const long first = (long)a.q_pos0 + a.t_begin;
+  a.groups = prefill_split(qg, rows_of(first), rows_of(first + a.t_count - 1));
   dim3 grid((unsigned)(qg * a.groups));
   if (a.H == 64)
     hipLaunchKernelGGL((k_score_prefill<2, KDT>), grid, dim3(512), 0, st, a);

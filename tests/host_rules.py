@@ -13,6 +13,7 @@ _SHIM = """
 extern "C" int in_ring(long T, long s_max, long packed, long fp8, long without, long with) {
   return hisa::hist_in_ring(T, s_max, packed, fp8, without, with);
 }
+extern "C" int key_ranges(long q_groups, long first, long last) { return hisa::prefill_split(q_groups, first, last); }
 extern "C" int tiles_per_wave(long T, long n_tiles) { return hisa::gather_tiles_per_wave(T, n_tiles); }
 """
 
@@ -39,3 +40,7 @@ def tiles_per_wave(T, n_tiles):
 
 def in_ring(T, s_max, packed, fp8, without, with_):
     return bool(_call("in_ring", T, s_max, packed, fp8, without, with_))
+
+
+def key_ranges(T, rows_first, rows_last):
+    return _call("key_ranges", -(-T // 8), rows_first, rows_last)

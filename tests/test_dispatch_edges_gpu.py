@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 from paper_2603_28458_amd import workloads as W
-from tests.host_rules import in_ring, tiles_per_wave
+from tests.host_rules import in_ring, key_ranges, tiles_per_wave
 from tests.parity import run_and_check, sample_queries
 
 pytestmark = pytest.mark.gpu
@@ -16,13 +16,16 @@ def _run(wl, n=24, **kw):
     return run_and_check(wl, queries=sample_queries(wl, n), **kw)
 
 
-@pytest.mark.parametrize("T,L,k_dtype", [(64, 9001, "bf16"), (71, 4097, "fp8_e4m3"), (257, 30000, "bf16"),
-                                         (1000, 6400, "fp8_e4m3"), (2055, 2055, "bf16")])
-def test_key_ranges_of_the_prefill_scoring_kernel(T, L, k_dtype):
+@pytest.mark.parametrize("T,L,s_max,k_dtype,ranges", [
+    (64, 9001, None, "bf16", 32), (71, 4097, None, "fp8_e4m3", 28), (257, 30000, None, "bf16", 7), (1000, 6400, None, "fp8_e4m3", 2),
+    (2055, 2055, None, "bf16", 2), (3000, 4000, None, "bf16", 1), (300, 700, 20000, "fp8_e4m3", 6)])
+def test_key_ranges_of_the_prefill_scoring_kernel(T, L, s_max, k_dtype, ranges):
     # the dense scoring kernel (flat indexer, Stage 1 of a chunk) cuts the keys of 8 queries into ranges of
-    # 128-key tiles: 9, 8, 2 and 1 queries groups over the CUs, uneven ranges, ranges past a short prefix
-    wl = W.make_workload(f"ranges{T}", seq_len=L, T=T, H=64, d=128, B=32, m=20, k=512, q_dtype="bf16",
-                         k_dtype=k_dtype, seed=400 + T)
+    # 128-key tiles: by how many groups of 8 there are and what their queries see, whatever the cache was made
+    # for; uneven ranges, ranges past a short prefix
+    assert key_ranges(T, L - T + 1, L) == ranges
+    wl = W.make_workload(f"ranges{T}", seq_len=L, T=T, H=64, d=128, B=32, m=20, k=min(512, L), q_dtype="bf16",
+                         k_dtype=k_dtype, s_max=s_max, seed=400 + T)
     _run(wl)
 
 

@@ -1,5 +1,5 @@
 """The rules that cut a launch into workgroups, over the sizes they are asked for."""
-from tests.host_rules import in_ring, tiles_per_wave
+from tests.host_rules import in_ring, key_ranges, tiles_per_wave
 
 
 def _cost(T, n_tiles, tpw):
@@ -36,3 +36,17 @@ def test_bins_in_the_tile_rings():
     # bf16 keys of one long sequence; fp8 keys and packed streams at any length
     assert in_ring(16384, 49152, False, False, 2, 3) and not in_ring(16384, 49184, False, False, 2, 3)
     assert in_ring(16384, 1 << 20, True, False, 2, 3) and in_ring(16384, 1 << 20, False, True, 2, 3)
+
+
+def test_key_ranges_of_the_prefill_scoring_kernel():
+    for T in (1, 64, 77, 100, 256, 777, 1024, 2048, 4096, 8184):
+        for last in (0, 1, 127, 128, 129, 5000, 65536, 1 << 20):
+            for first in (0, last // 2, max(0, last - T), last):
+                s = key_ranges(T, first, last)
+                assert 1 <= s <= 32 and (s == 1 or s <= -(-last // 128)), (T, first, last, s)     # no empty range
+    assert key_ranges(8192, 0, 65536) == 1                       # four rounds by themselves
+    # queries at the end of a long context fill the CUs as often as they can be cut evenly
+    assert [key_ranges(T, 64512, 65536) for T in (1024, 512, 256)] == [2, 4, 8]
+    assert key_ranges(3000, 1, 3000) == 1                        # a triangle: the short queries fill the second round
+    # what is seen counts, not the array's length: 300 pooled keys, whatever the cache was made for
+    assert key_ranges(1500, 253, 300) == 1
