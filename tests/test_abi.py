@@ -191,3 +191,17 @@ def test_the_header_is_valid_c_and_the_plain_c_example_links(tmp_path):
     res = subprocess.run(B.example_command(out), capture_output=True, text=True)
     assert res.returncode == 0, res.stderr
     assert os.path.exists(out)
+
+
+def test_current_stream_without_the_raw_handle(monkeypatch):
+    # the raw handle of the current stream is no documented part of torch: without it the Stream object is asked
+    class Stream:
+        cuda_stream = 1234
+
+    monkeypatch.setattr(hisa, "_raw_stream", None)
+    monkeypatch.setattr(hisa.torch.cuda, "current_stream", lambda: Stream())
+    assert hisa._stream(None) == 1234
+    monkeypatch.setattr(hisa, "_raw_stream", lambda device: 5000 + device)
+    monkeypatch.setattr(hisa.torch.cuda, "current_device", lambda: 3)
+    assert hisa._stream(None) == 5003
+    assert hisa._stream(Stream()) == 1234 and hisa._stream(77) == 77
