@@ -122,6 +122,69 @@ def test_rows_kept_whole_equal_the_scored_rows(k_dtype, H, d, T):
         _routes_agree(Q, K, short, B, m, k)
 
 
+@pytest.mark.parametrize("T,positions,packed", [(100, False, False), (600, False, False), (600, True, False), (600, False, True),
+                                                (2100, False, False), (2100, False, True)])
+@pytest.mark.parametrize("H", [64, 32])
+def test_gates_that_refuse_the_direct_write_of_blocks(T, H, positions, packed):
+    # every query sees at most m blocks, so nothing is scored unless a gate could make a score -inf or NaN; on each
+    # route of Stage 1 (k_stage1_query, k_score_prefill, k_score_ranges by given positions and packed,
+    # k_score_resident plain and packed) and in the single-launch call the blocks must be those of the scored
+    # rows, whatever the workspace holds
+    import torch
+    from paper_2603_28458_amd import hisa
+
+    B, m = 32, 80
+    cut = [0, T // 3 + 5, T]
+    lens = [b - a for a, b in zip(cut, cut[1:])] if packed else T
+    wl = W.make_workload(f"gates{T}_{positions}_{packed}", n_seq=2 if packed else 1, seq_len=lens, T=T, H=H, d=128, B=B, m=m, k=64,
+                         q_dtype="bf16", k_dtype="bf16", mode="varlen" if packed else "prefill", seed=470)
+    Q, K = hisa.to_device(W.pack(wl) if packed else wl)
+    if positions:
+        Q.q_pos = torch.arange(T, dtype=torch.int32, device="cuda")
+    print(f"\n[gates] T={T} H={H} positions={positions} packed={packed}", flush=True)
+    pooled = hisa.hisa_pool_blocks(K, B)
+    ones = torch.full((1,), -1, dtype=torch.int32, device="cuda").view(torch.float32)
+    Q.w[::3, 1] = -np.inf
+    Q.w[1::5, 0] *= -1.0
+    Q.w[2::7, 3] = ones
+    general = hisa.hisa_block_score_topk(Q, K, pooled, hisa.HISA_BF16, B, m, want_scores=True)[0].cpu().numpy()
+    for ws in _workspaces(hisa.OP_BLOCK_SCORE_TOPK, Q, K, B, m, 0):
+        short = hisa.hisa_block_score_topk(Q, K, pooled, hisa.HISA_BF16, B, m, ws=ws)[0].cpu().numpy()
+        assert np.array_equal(short, general), np.nonzero((short != general).any(1))[0]
+    one = hisa.hisa_indexer_topk(Q, K, pooled, hisa.HISA_BF16, B, m, 64, want_block_idx=True)[0].cpu().numpy()
+    assert np.array_equal(one, general), np.nonzero((one != general).any(1))[0]
+
+
+@pytest.mark.parametrize("H", [64, 32])
+@pytest.mark.parametrize("T,q_pos0", [(2100, -1700), (4100, -3600)])
+def test_flat_indexer_on_a_short_packed_stream(T, q_pos0, H):
+    # at most 512 bf16 keys and 2048 queries or more at consecutive positions, with first visible positions: the
+    # resident kernel (64, 32 or 8 queries per workgroup), against the same queries with their positions given
+    # one by one, which go through the per-query kernel.  Queries before the stream, inside it, past its end
+    import torch
+    from paper_2603_28458_amd import hisa
+
+    S, k = 480, 70
+    wl = W.make_workload(f"flat_packed{T}", seq_len=S, T=S, H=H, d=128, B=32, m=4, k=k, q_dtype="bf16", k_dtype="bf16", seed=480)
+    _, K = hisa.to_device(wl)
+    g = torch.Generator().manual_seed(481)
+    pos = q_pos0 + torch.arange(T)
+    starts = torch.tensor([0, 7, 150, 151, 333, 1 << 20])
+    lo = starts[torch.searchsorted(starts, pos.clamp(min=0), right=True) - 1].int().cuda()
+    Q = hisa.Queries(q=torch.randn((T, H, 128), generator=g).bfloat16().cuda(), w=torch.rand((T, H), generator=g).cuda(),
+                     dtype=hisa.HISA_BF16, q_pos0=q_pos0, q_lo=lo)
+    print(f"\n[flat packed] T={T} H={H}", flush=True)
+    ids, sc = hisa.dsa_flat_indexer_topk(Q, K, k, want_topk_scores=True)[:2]
+    Q.q_pos = pos.int().cuda()
+    want_ids, want_sc = hisa.dsa_flat_indexer_topk(Q, K, k, want_topk_scores=True)[:2]
+    assert torch.equal(ids, want_ids) and torch.equal(sc, want_sc)
+    ids = ids.cpu().numpy()
+    assert (ids[: -q_pos0] == -1).all() and (ids[-q_pos0 : S - q_pos0, 0] >= 0).all()
+    for t in range(-q_pos0, min(T, S - q_pos0), 11):
+        row = ids[t][ids[t] >= 0]
+        assert row.size == min(k, t + q_pos0 - int(lo[t]) + 1) and row[0] >= int(lo[t]) and row[-1] <= t + q_pos0
+
+
 @pytest.mark.parametrize("T", [200, 300])
 @pytest.mark.parametrize("k_dtype,H,d", [("bf16", 64, 128), ("fp8_e4m3", 32, 128), ("f32", 4, 64)])
 def test_queries_before_position_zero_see_nothing(k_dtype, H, d, T):
