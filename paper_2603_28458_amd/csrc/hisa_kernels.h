@@ -495,15 +495,15 @@ __global__ __launch_bounds__(256) void k_score_ranges_f32(ScoreArgs a, int keys_
   const int n_total = gather ? a.m * a.B : visible_rows(a, pos);
   const int lo = query_lo(a.q_lo, t, pos);
   const int lo_row = lo / a.pos_div;   // first visible row when the rows are blocks or tokens in order
-  BlockList list;
+  const float* q = (const float*)a.q + (long)t * H * d;
+  for (int i = tid; i < H * d; i += 256) qs[i] = q[i];
+  for (int i = tid; i < H; i += 256) qs[H * d + i] = a.w[(long)t * H + i];
+  BlockList list;   // (behind the query's loads: in front of them the position's latency comes on top)
   if (visible_rows(a, pos) - lo_row <= a.whole_rows && never_neg_inf(a.w + (long)t * H, H, nullptr, lo, pos) &&
       (!gather || blocks_ascending(a.block_idx + (long)t * a.m, a.m, a.B, lo, pos, list))) {
     if (gather && rg.x == 0) finish_whole_row<256>(a, list, t, rg.row, pos, lo);
     return;
   }
-  const float* q = (const float*)a.q + (long)t * H * d;
-  for (int i = tid; i < H * d; i += 256) qs[i] = q[i];
-  for (int i = tid; i < H; i += 256) qs[H * d + i] = a.w[(long)t * H + i];
   __syncthreads();
   const int c0 = rg.x * keys_per_wg;
   const int c1 = (c0 + keys_per_wg) < n_total ? (c0 + keys_per_wg) : n_total;
