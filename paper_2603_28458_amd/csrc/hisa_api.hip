@@ -678,7 +678,7 @@ static int token_refine_impl(const hisa_queries* queries, const hisa_keys* keys,
   sa.scores = C;
   sa.ld = n_slots;
   sa.n_fixed = n_slots;
-  sa.block_idx = block_idx;
+  sa.ids = block_idx;
   sa.m = m;
   sa.B = B;
   sa.t_begin = 0;
@@ -804,7 +804,7 @@ int dsa_flat_indexer_topk(const hisa_queries* queries, const hisa_keys* keys, in
       if (st) return st;
       SelectArgs sm = select_base(queries, keys);
       sm.scores = part_sc;
-      sm.idx_in = part_id;
+      sm.ids = part_id;
       sm.ld = (long)p.n_seg * k;
       sm.n_fixed = p.n_seg * k;
       sm.t_begin = (int)t0;

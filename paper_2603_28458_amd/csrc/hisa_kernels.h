@@ -1065,10 +1065,13 @@ __global__ __launch_bounds__(512) void k_score_resident(ScoreArgs a) {
 // Row-wise exact top-k over scores in global memory (Eqs. 2, 6, 9).
 enum : int { MAP_FLAT = 0, MAP_BLOCKS = 1, MAP_CAND = 2, MAP_PAIRS = 3 };
 
+// (128 bytes: two cache lines of kernel arguments.  A third one, first read behind the position's lookups, cost a small
+// fp32 prefill 0.2 of 32 us.)
 struct SelectArgs {
   const float* scores;       // [rows, ld]
   long ld;
-  const int32_t* idx_in;     // MAP_PAIRS: [rows, ld] ids aligned with scores
+  const int32_t* ids;        // MAP_CAND: the kept blocks [T, m] (global query indexing); MAP_PAIRS: [rows, ld] ids
+                             // aligned with scores
   const int32_t* q_seq;      // position info of the queries (FLAT / BLOCKS)
   const int32_t* q_pos;
   const int32_t* q_lo;       // first visible position per query or null (FLAT / BLOCKS)
@@ -1076,18 +1079,18 @@ struct SelectArgs {
   int q_pos0, n_seq, pos_div;
   int t_begin;               // global query index of row 0
   int n_fixed;               // CAND / PAIRS: elements per row
-  const int32_t* block_idx;  // MAP_CAND: [T, m] (global query indexing)
-  int m, B;
+  int m, B;                  // CAND
   // BLOCKS: as ScoreArgs::whole_rows: such a row was not scored, and all it sees is selected here (w, H: what
   // never_neg_inf asks for).  (CAND: the scoring kernel has written the ids and marked the row.)
   int whole_rows;
-  const float* w;            // [T, H]
   int H;
   int seg_len, n_seg;        // FLAT: the row is cut into n_seg segments of seg_len (grid.x)
   int k;
+  const float* w;            // [T, H]
   int32_t* out_idx;          // [rows * n_seg, k]
   float* out_scores;         // same shape, or null
 };
+static_assert(sizeof(SelectArgs) == 128, "two lines");
 
 template <int THREADS, int E, int MAP>
 __global__ __launch_bounds__(THREADS) void k_select(SelectArgs a) {
@@ -1173,7 +1176,7 @@ __global__ __launch_bounds__(THREADS) void k_select(SelectArgs a) {
   int my_base = 0;
   if (one_slot) {
     const int my_slot = (int)(threadIdx.x * E) / a.B;
-    if (my_slot < a.m) my_base = (a.block_idx[(long)t * a.m + my_slot] - my_slot) * a.B;
+    if (my_slot < a.m) my_base = (a.ids[(long)t * a.m + my_slot] - my_slot) * a.B;
   }
   auto emit = [&](int p, int i, uint32_t key) {
     int id;
@@ -1181,9 +1184,9 @@ __global__ __launch_bounds__(THREADS) void k_select(SelectArgs a) {
       id = my_base + i;
     } else if (MAP == MAP_CAND) {
       const int slot = i / a.B;
-      id = a.block_idx[(long)t * a.m + slot] * a.B + (i - slot * a.B);
+      id = a.ids[(long)t * a.m + slot] * a.B + (i - slot * a.B);
     } else if (MAP == MAP_PAIRS) {
-      id = a.idx_in[(long)row * a.ld + i];
+      id = a.ids[(long)row * a.ld + i];
     } else {
       id = base + i;
     }
