@@ -64,11 +64,14 @@ struct ScoreArgs {
 // arithmetic produces, so a score never looks like it.
 constexpr uint32_t kRowDoneBits = 0x7f800001u;
 
-// Position and sequence of query t, clamped so that no key row past the sequence is visible.
-__device__ __forceinline__ int query_pos(const ScoreArgs& a, int t, int& seq) {
-  int s = a.q_seq ? a.q_seq[t] : 0;
-  s = s < 0 ? 0 : (s >= a.n_seq ? a.n_seq - 1 : s);
-  seq = s;
+// Sequence of query t.
+__device__ __forceinline__ int query_seq(const ScoreArgs& a, int t) {
+  const int s = a.q_seq ? a.q_seq[t] : 0;
+  return s < 0 ? 0 : (s >= a.n_seq ? a.n_seq - 1 : s);
+}
+
+// Position of query t of sequence s, clamped so that no key row past the sequence is visible.
+__device__ __forceinline__ int query_pos_in(const ScoreArgs& a, int t, int s) {
   int pos = a.q_pos ? a.q_pos[t] : a.q_pos0 + t;
   // a sequence cannot be longer than the padded row count of its key array (a bad seq_len must
   // not turn into an index past the arrays)
@@ -76,6 +79,12 @@ __device__ __forceinline__ int query_pos(const ScoreArgs& a, int t, int& seq) {
   int sl = a.seq_len[s];
   sl = sl < cap ? sl : (int)cap;
   return pos < sl ? pos : sl - 1;
+}
+
+// Both.
+__device__ __forceinline__ int query_pos(const ScoreArgs& a, int t, int& seq) {
+  seq = query_seq(a, t);
+  return query_pos_in(a, t, seq);
 }
 
 __device__ __forceinline__ int visible_rows(const ScoreArgs& a, int pos) {
@@ -1623,12 +1632,21 @@ __global__ __launch_bounds__(StreamSelect::kThreads, 8) void k_select_stream(Sel
 // by the select).  Ends with a barrier: ids visible, score area and rings free again.
 // primed: every wave has already issued the DMA of its first tile (blocks 32 * wave ..) into its
 // ring slot 0, and that DMA has completed.
-template <int HG, int NW, int NB, int E1, int TILE>
+// fine: scratch of the one-pass top-k, tried first when given (shared with nothing; its bins cleared and a barrier
+// passed by the caller), or null.
+template <int NT, int E1>
+struct Stage1Fine {
+  FineSelSmem<NT, E1>* sm;
+  uint32_t* hist;
+};
+
+template <int HG, int NW, int NB, int E1, int TILE, class Fine = std::nullptr_t>
 __device__ __forceinline__ void stage1_in_workgroup(const QFrag<HG>& f, const ScoreArgs& a, const void* pooled,
                                                     int t, int seq, int pos, int lo, int n_blocks,
                                                     unsigned char* smem, float* sc, int32_t* blk_lds, int wave,
-                                                    bool primed = false) {
+                                                    bool primed = false, Fine fine = nullptr) {
   constexpr int NT = NW * 64;
+  constexpr bool kFine = !std::is_same<Fine, std::nullptr_t>::value;
   const int lane = threadIdx.x & 63;
   const int n_bvis = pos < 0 ? 0 : pos / a.B + 1;
   const int b_first = lo > 0 ? lo / a.B : 0;   // first visible block (0 unless sequences are packed)
@@ -1639,20 +1657,63 @@ __device__ __forceinline__ void stage1_in_workgroup(const QFrag<HG>& f, const Sc
   }
   const int nt1 = (n_bvis + 31) >> 5;
   const int nj1 = nt1 > wave ? (nt1 - wave + NW - 1) / NW : 0;
+  const int n_last = n_bvis - 1;
   const __amdgpu_buffer_rsrc_t prsrc =
       key_buffer((const char*)pooled + (long)seq * n_blocks * kD * 2, (long)n_blocks * kD * 2);
+  float s_max = -__builtin_inff(), s_min = __builtin_inff();   // of the scores between the forced ones (kFine)
+  bool any_nan = false;
   wave_pipeline<HG, DT_BF16, NB>(
       f, prsrc, prsrc, lds_address(smem) + wave * NB * TILE, nj1,
       [&](int j) { return (wave + NW * j) * 32; },
       [&](int j, float s) {
         const int b = (wave + NW * j) * 32 + (lane & 31);
-        if (lane < 32) sc[b] = (b < n_bvis && b >= b_first) ? s : neg_inf();
+        const bool visible = b < n_bvis && b >= b_first;
+        if constexpr (kFine) {
+          const float x = b > b_first && b < n_last ? s : __uint_as_float(0xffffffffu);   // (NaN is passed over)
+          s_max = vmax_f32(s_max, x);
+          s_min = vmin_f32(s_min, x);
+          any_nan |= visible && s != s;
+        }
+        if (lane < 32) sc[b] = visible ? s : neg_inf();
       },
       primed && nj1 > 0);
+  // (an infinite range makes the one-pass top-k decline: the select below takes a NaN score first)
+  if constexpr (kFine) fine_select_range<NT, E1>(*fine.sm, any_nan ? __builtin_inff() : s_max, s_min, wave);
   __syncthreads();   // block scores complete, rings dead
+  const int n = b_first <= n_last ? n_bvis : 0;   // (a first visible block past the query's own: it sees nothing)
+  if constexpr (kFine) {
+    // The one-pass top-k of the other blocks; the two forced ones take the first and the last place.
+    if (n - b_first - 2 > a.m - 2 && a.m > 2) {
+      const float qnan = __uint_as_float(0xffffffffu);
+      auto vals = [&](int q) -> float4 {
+        const float4 v = *reinterpret_cast<const float4*>(sc + 4 * q);
+        float x[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int i = 4 * q + e;
+          x[e] = (i == b_first || i == n_last || x[e] == neg_inf()) ? qnan : x[e];
+        }
+        return make_float4(x[0], x[1], x[2], x[3]);
+      };
+      auto emit = [&](uint32_t p, const auto& v, float tau, int32_t*) {
+        ++p;
+#pragma unroll
+        for (int j = 0; j < E1; ++j) {
+          if (v[j] >= tau) blk_lds[p++] = (int)threadIdx.x * E1 + j;
+        }
+      };
+      if (select_topk_fine<NT, E1>(*fine.sm, fine.hist, n, a.m - 2, vals, emit)) {
+        if (threadIdx.x == 0) {
+          blk_lds[0] = b_first;
+          blk_lds[a.m - 1] = n_last;
+        }
+        __syncthreads();
+        return;
+      }
+    }
+  }
   {
     SelectSmem<NT, E1>& sm1 = *reinterpret_cast<SelectSmem<NT, E1>*>(smem);
-    const int n_last = n_bvis - 1;
     auto key_of = [&](int i, float v) -> uint32_t {
       return (i == b_first || i == n_last) ? 0xffffffffu : ordered_key(v);   // first and own block forced
     };
@@ -1663,8 +1724,7 @@ __device__ __forceinline__ void stage1_in_workgroup(const QFrag<HG>& f, const Sc
     };
     auto load1 = [&](int i) -> uint32_t { return key_of(i, sc[i]); };
     auto emit = [&](int p, int i, uint32_t) { blk_lds[p] = i; };
-    // (a first visible block past the query's own: the query sees nothing, nothing is forced)
-    const int n_kept = select_topk<NT, E1>(sm1, b_first <= n_last ? n_bvis : 0, a.m, load4, load1, emit);
+    const int n_kept = select_topk<NT, E1>(sm1, n, a.m, load4, load1, emit);
     for (int p = n_kept + threadIdx.x; p < a.m; p += NT) blk_lds[p] = -1;
   }
   __syncthreads();
@@ -1676,6 +1736,10 @@ __device__ __forceinline__ void stage1_in_workgroup(const QFrag<HG>& f, const Sc
 // of them there; only the m ids leave the CU.  Against the scoring launch plus the select launch
 // this saves a launch, the round trip of the block scores through HBM and the second query read;
 // with one workgroup per query it only pays while the queries are fewer than the CUs.
+// Latency bound: launch, sequence, query and tiles, then the top-m.  The one-pass top-m (five barriers) instead of
+// the range-bracketing one (about sixteen), and the query and first tiles requested before the sequence's length
+// is known: 32 queries of 1024 blocks 10.05 -> 9.1 us, 200 of 157 8.75 -> 7.4, 77 of 1564 11.9 -> 10.8, 4 of 7812
+// 28.7 -> 28.0.  (A row that it declines, one in thousands by a tie, ends with the other select behind it: 9.5 -> 11 us.)
 // sc_floats >= the block count rounded up to 32; LDS: the tile rings, sc_floats scores, m ids
 // (rounded up to 4), HG * 8192 bytes for the query fragment.
 template <int HG, int E1, int NB>
@@ -1688,21 +1752,16 @@ __global__ __launch_bounds__(512) void k_stage1_query(ScoreArgs a, const void* p
   float* sc = reinterpret_cast<float*>(smem + kStageBytes);
   int32_t* blk_lds = reinterpret_cast<int32_t*>(sc + sc_floats);
   unsigned char* q_lds = reinterpret_cast<unsigned char*>(blk_lds + (a.m + 3) / 4 * 4);   // HG * 8192 bytes
+  // the one-pass top-k's bins take the place of the query once that is in registers
+  __shared__ FineSelSmem<NT, E1> fs;
+  static_assert(FineSelSmem<NT, E1>::kHistBytes <= HG * 8192, "the bins must fit the query's area");
   const int t = a.t_begin + blockIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int seq;
-  const int pos = query_pos(a, t, seq);
-  const int lo = query_lo(a.q_lo, t, pos);
+  const int seq = query_seq(a, t);
   const int n_blocks = (int)(a.rows_per_seq / a.B);
-  {
-    const int b_first = lo > 0 ? lo / a.B : 0, n_bvis = pos < 0 ? 0 : pos / a.B + 1;
-    if (n_bvis - b_first <= a.m && never_neg_inf(a.w + (long)t * a.H, a.H, nullptr, 0, 0)) {   // nothing to score
-      for (int p = threadIdx.x; p < a.m; p += NT) block_idx_out[(long)t * a.m + p] = p < n_bvis - b_first ? b_first + p : -1;
-      return;
-    }
-  }
-  // the query fragment is staged in an area of its own, so that every wave's first tile of pooled
-  // keys can be requested right behind it: one memory latency for both
+  // The query fragment is staged in an area of its own, so that every wave's first tile of pooled keys can be
+  // requested right behind it, and both as soon as the sequence is known: one memory latency for the query, the
+  // tiles and the sequence's length (rows past its end, or of a query that is not scored, are not used).
   QFrag<HG> f;
   qfrag_shared_request<HG, NW>(f, (const uint16_t*)a.q + (long)t * a.H * kD, a.w + (long)t * a.H,
                                (long)a.H * kD * 2, lds_address(q_lds), wave);
@@ -1711,9 +1770,22 @@ __global__ __launch_bounds__(512) void k_stage1_query(ScoreArgs a, const void* p
         key_buffer((const char*)pooled + (long)seq * n_blocks * kD * 2, (long)n_blocks * kD * 2);
     tile_dma<DT_BF16>(prsrc, prsrc, lds_address(smem) + wave * NB * TILE, wave * 32);
   }
+  const int pos = query_pos_in(a, t, seq);
+  const int lo = query_lo(a.q_lo, t, pos);
+  {
+    const int b_first = lo > 0 ? lo / a.B : 0, n_bvis = pos < 0 ? 0 : pos / a.B + 1;
+    if (n_bvis - b_first <= a.m && never_neg_inf(a.w + (long)t * a.H, a.H, nullptr, 0, 0)) {   // nothing to score
+      for (int p = threadIdx.x; p < a.m; p += NT) block_idx_out[(long)t * a.m + p] = p < n_bvis - b_first ? b_first + p : -1;
+      wait_vmem_le<0>();    // (nothing may still be on its way into this workgroup's LDS)
+      return;
+    }
+  }
   qfrag_shared_complete<HG>(f, lds_address(q_lds));
   qfrag_ready<HG>(f);
-  stage1_in_workgroup<HG, NW, NB, E1, TILE>(f, a, pooled, t, seq, pos, lo, n_blocks, smem, sc, blk_lds, wave, true);
+  uint32_t* hist = reinterpret_cast<uint32_t*>(q_lds);
+  fine_select_prepare<NT, E1>(fs, hist);   // (the barrier behind the scores comes before their first use)
+  stage1_in_workgroup<HG, NW, NB, E1, TILE>(f, a, pooled, t, seq, pos, lo, n_blocks, smem, sc, blk_lds, wave, true,
+                                            Stage1Fine<NT, E1>{&fs, hist});
   for (int p = threadIdx.x; p < a.m; p += NT) block_idx_out[(long)t * a.m + p] = blk_lds[p];
 }
 

@@ -154,3 +154,48 @@ def test_stage1_on_scores_a_few_ulps_apart(spread):
         score = level[ids].astype(np.float64)
         score[[0, own]] = np.inf                 # forced
         assert np.array_equal(got[t], expected_row(score, ids, m)), t
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["random", "tied", "negative", "nan"])
+@pytest.mark.parametrize("M,m", [(40, 3), (70, 69), (300, 126), (512, 2), (2048, 64), (2049, 128), (8192, 1000)])
+def test_stage1_of_a_small_batch_against_a_sort(M, m, kind):
+    # the one-launch Stage 1: queries that see from m + 1 blocks to all of them, some from the middle of a stream on.
+    # tied: crowded bins and ties across the threshold, declined.  negative: scores of -inf, which are no candidates.
+    # nan: declined (the general select takes such a block first); NaN in blocks that a query does not see changes nothing
+    from paper_2603_28458_amd import hisa
+
+    if kind == "nan" and M > 512:
+        pytest.skip("the scored route takes NaN differently above 512 blocks")
+    B, T, H = 32, 24, 64 if M % 2 == 0 else 32
+    print(f"\n[small stage 1] M={M} m={m} H={H} {kind}", flush=True)
+    rng = np.random.default_rng(M + m)
+    level = rng.integers(0, 5, M) if kind == "tied" else rng.permutation(M)
+    sign = -1.0 if kind == "negative" else 1.0
+    q = one_head_queries(H, T, {0: 1.0, 1: 256.0, 2: 256.0})
+    q["w"] *= sign
+    pooled = torch.zeros((1, M, 128))
+    pooled[0, :, 0], pooled[0, :, 1] = torch.from_numpy(level % 256).float(), torch.from_numpy(level // 256).float()
+    score = sign * level.astype(np.float64)
+    if kind == "negative":
+        gone = rng.permutation(M)[: M // 5]
+        pooled[0, gone, 2] = 3e38
+        score[gone] = -np.inf
+    if kind == "nan":
+        pooled[0, -M // 4:, 3] = float("nan")
+    pos = np.sort(np.concatenate([[m * B, m * B + 40, M * B - 1], rng.integers(m * B, M * B, T - 3)])).clip(max=M * B - 1)
+    lo = np.where(np.arange(T) % 3 == 0, 0, rng.integers(0, np.maximum(1, pos - m * B)))
+    Q = hisa.Queries(**q, q_pos=torch.from_numpy(pos.astype(np.int32)).cuda(), q_lo=torch.from_numpy(lo.astype(np.int32)).cuda())
+    K = hisa.Keys(k=None, seq_len=torch.tensor([M * B], dtype=torch.int32).cuda(), dtype=hisa.HISA_BF16, n_seq=1, s_max=M * B, d=128)
+    pooled = pooled.bfloat16().cuda()
+    got = hisa.hisa_block_score_topk(Q, K, pooled, hisa.HISA_BF16, B, m)[0].cpu().numpy()
+    if kind == "nan":
+        want = hisa.hisa_block_score_topk(Q, K, pooled, hisa.HISA_BF16, B, m, want_scores=True)[0].cpu().numpy()
+        assert np.array_equal(got, want)
+        return
+    for t in range(T):
+        ids = np.arange(lo[t] // B, pos[t] // B + 1)
+        s = score[ids].copy()
+        s[[0, -1]] = np.inf                      # forced
+        ids, s = ids[s > -np.inf], s[s > -np.inf]
+        assert np.array_equal(got[t], expected_row(s, ids, m)), t
