@@ -65,6 +65,19 @@ inline int gather_tiles_per_wave(long T, long n_tiles) {
   return best;
 }
 
+// Waves per query of k_rows_f32 (fp32 rows of at most 512 candidates, 64 of which a wave scores at a time; a workgroup
+// holds 9 KB of LDS per wave).  Few queries: a wave for every 64 candidates, so that none scores twice in a row.  Many:
+// half as many, since a wave that only waits for the others' scores keeps its LDS.  Refinement, us with 1 / 2 / 4 / 8
+// waves (two launches: the last figure): 300 queries of 512 candidates 28.6 / 21.1 / 17.4 / 13.4 (16.3), 600 of 512
+// 43.7 / 28.7 / 22.2 / 19.7 (23.3), 1024 of 256 20.4 / 15.1 / 12.8 / 18.7 (18.6), 1500 of 96 14.6 / 12.3 / 18.5 (21.0),
+// 3000 of 512 43.4 / 44.6 / 46.9 / 64.6 (53.8); Stage 1: 2000 of 125 blocks 10.3 / 9.3 / 13.6 (15.3), 3000 of 94
+// 19.3 / 21.3 / 29.9 (20.9), 3000 of 47 10.6 / 15.0 / 20.6 (14.7).
+inline int rows_f32_waves(long T, long n_max) {
+  const long per_wave = T > 2048 ? 128 : 64;
+  const int nw = n_max <= per_wave ? 1 : n_max <= 2 * per_wave ? 2 : n_max <= 4 * per_wave ? 4 : 8;
+  return nw == 8 && T > 768 ? 4 : nw;
+}
+
 // Workgroups that a CU holds: by their LDS, and at most max_wgs of them by their registers.
 inline int wgs_per_cu(long lds, int max_wgs) {
   const long n = kLdsPerCU / lds;

@@ -195,6 +195,27 @@ void launch_score(int path, int key_dt, ScoreArgs a, long n_rows_max, bool conse
 }
 
 // ---- selection launches -----------------------------------------------------------------
+// fp32 rows of at most 512 candidates (one wave's select), whose scores nobody asked for: scored and selected in one
+// launch, k ids per query.
+constexpr int kRowsF32Max = 512;
+
+template <bool GATHER, int NW>
+void launch_rows_f32_nw(const ScoreArgs& a, int n_max, int k, int32_t* out_idx, float* out_scores, hipStream_t st) {
+  if (n_max <= 256)
+    hipLaunchKernelGGL((k_rows_f32<GATHER, NW, 4>), dim3(a.t_count), dim3(NW * 64), 0, st, a, k, out_idx, out_scores);
+  else
+    hipLaunchKernelGGL((k_rows_f32<GATHER, NW, 8>), dim3(a.t_count), dim3(NW * 64), 0, st, a, k, out_idx, out_scores);
+}
+
+template <bool GATHER>
+void launch_rows_f32(const ScoreArgs& a, int n_max, int k, int32_t* out_idx, float* out_scores, hipStream_t st) {
+  const int nw = rows_f32_waves(a.t_count, n_max);
+  if (nw == 1) launch_rows_f32_nw<GATHER, 1>(a, n_max, k, out_idx, out_scores, st);
+  else if (nw == 2) launch_rows_f32_nw<GATHER, 2>(a, n_max, k, out_idx, out_scores, st);
+  else if (nw == 4) launch_rows_f32_nw<GATHER, 4>(a, n_max, k, out_idx, out_scores, st);
+  else launch_rows_f32_nw<GATHER, 8>(a, n_max, k, out_idx, out_scores, st);
+}
+
 template <int MAP>
 int launch_select(const SelectArgs& a, int rows, int n_max, hipStream_t st) {
   dim3 grid((unsigned)((long)a.n_seg * rows));
@@ -569,6 +590,10 @@ int hisa_block_score_topk(const hisa_queries* queries, const hisa_keys* keys, co
   a.t_count = T;
   // a query that sees at most m blocks keeps them all: its block scores are only computed if asked for
   a.whole_rows = block_scores ? -1 : m;
+  if (path == PATH_F32 && !block_scores && M <= kRowsF32Max) {
+    launch_rows_f32<false>(a, M, m, block_idx, nullptr, s);
+    return launch_status();
+  }
   if (block_scores) {
     const long n = (long)T * M;
     hipLaunchKernelGGL(k_fill_f32, dim3((unsigned)((n + 255) / 256 > 4096 ? 4096 : (n + 255) / 256)),
@@ -670,6 +695,10 @@ static int token_refine_impl(const hisa_queries* queries, const hisa_keys* keys,
     }
     if (!ws || ws_bytes < (size_t)T * n_slots * 4) return HISA_ERR_WORKSPACE;
     C = (float*)ws;
+  }
+  if (path == PATH_F32 && !cand_scores && n_slots <= kRowsF32Max) {
+    launch_rows_f32<true>(a, n_slots, k, topk_idx, topk_scores, s);
+    return launch_status();
   }
   a.out = C;
   launch_score(path, keys->k_dtype, a, n_slots, false, s);

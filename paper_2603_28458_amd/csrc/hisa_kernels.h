@@ -1273,6 +1273,156 @@ __global__ __launch_bounds__(THREADS) void k_select(SelectArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------
+// Eqs. 5-6 / 7-9 on the plain fp32 ALU in one launch, for rows of at most 64 * E candidates (blocks, or GATHER: the
+// tokens of the kept blocks): one workgroup of NW waves scores a query's row into LDS, then its first wave selects k there (the
+// other three end; what is left of the workgroup's barriers costs one wave nothing).
+// Latency bound, and before that bound by the key rows' addresses: one key per thread read straight from memory
+// touches 64 lines per load.  Here a wave brings its 64 keys in pieces of 128 bytes, 8 lanes to a key, and
+// turns them through LDS (row pitch of 9 16-byte chunks: reads and writes free of conflicts); queries and gates are
+// the same for all lanes and come through the scalar cache.  The sums are k_score_ranges_f32's, in its order.
+// 1024 queries of 16 blocks and 256 candidates (4 heads of 64): Stage 1 11.2 -> 9.1 us, Stage 2 18.5 -> 12.8 us against
+// two launches each; the whole prefill 32.3 -> 24.6 us; 2000 queries of 512 candidates, 16 heads of 128: Stage 2
+// 206 -> 120 us.  (Eight heads to a piece of the rows: more scalar registers than there are, 14.3 and 151 us.)
+template <bool GATHER, int NW, int E>
+__global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 4) void k_rows_f32(ScoreArgs a, int k, int32_t* out_idx, float* out_scores) {
+  constexpr int PITCH = 9, N = 64 * E, HB = 4;
+  __shared__ __align__(16) float4 turn[NW][64 * PITCH];
+  __shared__ __align__(16) float row[N];
+  SelectSmem<64, E>& sm = *reinterpret_cast<SelectSmem<64, E>*>(&turn[0][0]);
+  static_assert(sizeof(SelectSmem<64, E>) <= sizeof(turn), "select scratch must fit the key area");
+  const int t = a.t_begin + (int)blockIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  int seq;
+  const int pos = query_pos(a, t, seq);
+  const int H = a.H, d = a.d, dq = d >> 2;
+  const int n_vis = visible_rows(a, pos);
+  const int lo = query_lo(a.q_lo, t, pos);
+  const int lo_row = lo / a.pos_div;
+  const int first = lo_row > 0 ? lo_row : 0;
+  const float* w = a.w + (long)t * H;
+  const int32_t* ids = GATHER ? a.block_idx + (long)t * a.m : nullptr;
+  int32_t* oi = out_idx + (long)t * k;
+  float* os = out_scores ? out_scores + (long)t * k : nullptr;
+  BlockList list;
+  if (n_vis - lo_row <= a.whole_rows && never_neg_inf(w, H, nullptr, lo, pos) &&
+      (!GATHER || blocks_ascending(ids, a.m, a.B, lo, pos, list))) {
+    if constexpr (GATHER)
+      take_all_visible<NW * 64>(ids, list, a.B, pos, lo, k, oi);
+    else
+      for (int p = threadIdx.x; p < k; p += NW * 64) oi[p] = p < n_vis - first ? first + p : -1;
+    return;
+  }
+  const int n_total = GATHER ? a.m * a.B : n_vis;   // <= N
+  // (the constant address space: uniform reads of memory that the launch does not write, through the scalar cache)
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  typedef const __attribute__((address_space(4))) f32x4* uniform4;
+  const uniform4 q = (uniform4)reinterpret_cast<uintptr_t>((const float*)a.q + (long)t * H * d);
+  const uint32_t row_bytes = (uint32_t)d * 4u;
+  const __amdgpu_buffer_rsrc_t keys =
+      key_buffer((const float*)a.keys + (long)seq * a.rows_per_seq * d, a.rows_per_seq * (long)row_bytes);
+  float4* mine = turn[wave];
+  for (int c0 = wave * 64; c0 < n_total; c0 += NW * 64) {
+    const int c = c0 + lane;
+    int r = -1;   // this lane's key row
+    if (c < n_total) {
+      if constexpr (GATHER) {
+        const int slot = c / a.B, off = c - slot * a.B;
+        const int blk = ids[slot];
+        const long x = (long)blk * a.B + off;
+        if (blk >= 0 && x <= pos && x >= lo) r = (int)x;
+      } else if (c >= lo_row) {
+        r = c;
+      }
+    }
+    float s = neg_inf();
+    if (__ballot(r >= 0) != 0ull) {
+      int src[8];   // the rows whose pieces this lane brings: 8 u + lane / 8
+#pragma unroll
+      for (int u = 0; u < 8; ++u) src[u] = __shfl(r, 8 * u + (lane >> 3));
+      u32x4v piece[8];
+      auto request = [&](int i0) {   // 16-byte chunks i0 .. i0 + 7 of the 64 rows (zeros for no row, and past a row's end)
+        const int i = i0 + (lane & 7);
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          piece[u] = __builtin_amdgcn_raw_buffer_load_b128(
+              keys, (src[u] < 0 || i >= dq) ? -16 : (int)((uint32_t)src[u] * row_bytes + 16u * (uint32_t)i), 0, 0);
+      };
+      s = 0.f;
+      for (int j = 0; j < H; j += HB) {
+        const int nh = H - j < HB ? H - j : HB;
+        float p[HB][4];
+#pragma unroll
+        for (int h = 0; h < HB; ++h)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) p[h][e] = 0.f;
+        request(0);
+        for (int i0 = 0; i0 < dq; i0 += 8) {
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            *reinterpret_cast<u32x4v*>(&mine[(8 * u + (lane >> 3)) * PITCH + (lane & 7)]) = piece[u];
+          if (i0 + 8 < dq) request(i0 + 8);
+          // (a wave reads what it wrote itself: in order, no barrier)
+          auto chunk = [&](int x) {
+            const float4 kv = mine[lane * PITCH + x];
+#pragma unroll
+            for (int h = 0; h < HB; ++h) {
+              if (h < nh) {
+                const f32x4 qv = q[(j + h) * dq + i0 + x];
+                p[h][0] = __builtin_fmaf(qv.x, kv.x, p[h][0]);
+                p[h][1] = __builtin_fmaf(qv.y, kv.y, p[h][1]);
+                p[h][2] = __builtin_fmaf(qv.z, kv.z, p[h][2]);
+                p[h][3] = __builtin_fmaf(qv.w, kv.w, p[h][3]);
+              }
+            }
+          };
+          if (i0 + 8 <= dq && nh == HB) {
+#pragma unroll
+            for (int x = 0; x < 8; ++x) chunk(x);
+          } else {
+            for (int x = 0; x < dq - i0 && x < 8; ++x) chunk(x);
+          }
+        }
+#pragma unroll
+        for (int h = 0; h < HB; ++h) {
+          if (h < nh) {
+            const float dot = (p[h][0] + p[h][1]) + (p[h][2] + p[h][3]);
+            s = __builtin_fmaf(w[j + h], __builtin_fmaxf(dot, 0.f), s);
+          }
+        }
+      }
+    }
+    if (c < n_total) row[c] = r >= 0 ? s : neg_inf();
+  }
+  __syncthreads();   // the row is complete, the key area dead
+  if (wave != 0) return;
+  const int n = GATHER ? n_total : (lo_row >= n_vis ? 0 : n_vis);
+  const int n_last = n - 1;
+  auto key_of = [&](int i, float v) -> uint32_t {
+    if (!GATHER && (i == first || i == n_last)) return 0xffffffffu;   // forced blocks
+    return ordered_key(v);
+  };
+  auto load4 = [&](int x) -> uint4 {
+    const float4 v = *reinterpret_cast<const float4*>(row + 4 * x);
+    return make_uint4(key_of(4 * x, v.x), key_of(4 * x + 1, v.y), key_of(4 * x + 2, v.z), key_of(4 * x + 3, v.w));
+  };
+  auto load1 = [&](int i) -> uint32_t { return key_of(i, row[i]); };
+  auto emit = [&](int p, int i, uint32_t key) {
+    int id = i;
+    if constexpr (GATHER) {
+      const int slot = i / a.B;
+      id = ids[slot] * a.B + (i - slot * a.B);
+    }
+    oi[p] = id;
+    if (os) os[p] = key_to_score(key);
+  };
+  const int n_out = select_topk<64, E, false, !GATHER>(sm, n, k, load4, load1, emit);
+  for (int p = n_out + lane; p < k; p += 64) {
+    oi[p] = -1;
+    if (os) os[p] = neg_inf();
+  }
+}
+
+// ------------------------------------------------------------------------------------------
 // Streaming exact top-k of one long score row (flat indexer, Eq. 2; k <= 2048).  The row stays in
 // global memory and is read a few times instead of being held in registers:
 //   1. a sample of the row gives a key range [rlo, rhi];

@@ -285,3 +285,24 @@ def test_queries_per_wave_of_the_resident_scoring_kernel(T, H, packed):
     wl = W.make_workload(f"resident{T}_{packed}", n_seq=4 if packed else 1, seq_len=lens, T=T, H=H, d=128, B=32, m=9,
                          k=256, q_dtype="bf16", k_dtype="bf16", mode="varlen" if packed else "prefill", seed=460)
     _run(W.pack(wl) if packed else wl, n=48)
+
+
+@pytest.mark.parametrize("T,H,d,B,m,k", [
+    (65, 4, 64, 16, 4, 50), (900, 9, 36, 8, 9, 65), (129, 3, 4, 16, 8, 128), (700, 1, 132, 43, 6, 200), (780, 8, 32, 64, 8, 300),
+    (2049, 2, 64, 16, 8, 100), (2100, 5, 32, 17, 9, 130), (1030, 4, 64, 2, 256, 400), (530, 4, 64, 1, 512, 512), (514, 4, 64, 1, 513, 500)])
+def test_fp32_rows_in_one_launch(T, H, d, B, m, k):
+    # rows around 64, 128, 256 and 512 candidates or blocks (above 512: two launches), heads that are no multiple of
+    # four, row pieces that are no 128 bytes; bit for bit against the route that writes its scores, in two launches
+    import torch
+    from paper_2603_28458_amd import hisa
+
+    wl = W.make_workload(f"rows_f32_{T}", seq_len=T, T=T, H=H, d=d, B=B, m=m, k=k, q_dtype="f32", k_dtype="f32", seed=490)
+    print(f"\n[fp32 rows] {wl.name} H={H} d={d} B={B} m={m} k={k}", flush=True)
+    Q, K = hisa.to_device(wl)
+    Q.w[::7] *= -1.0
+    pooled = hisa.hisa_pool_blocks(K, B, pooled_dtype=hisa.HISA_F32)
+    blocks = hisa.hisa_block_score_topk(Q, K, pooled, hisa.HISA_F32, B, m)[0]
+    assert torch.equal(blocks, hisa.hisa_block_score_topk(Q, K, pooled, hisa.HISA_F32, B, m, want_scores=True)[0])
+    ids, sc = hisa.hisa_token_refine_topk(Q, K, B, m, blocks, k, want_topk_scores=True)[:2]
+    want, want_sc = hisa.hisa_token_refine_topk(Q, K, B, m, blocks, k, want_topk_scores=True, want_cand_scores=True)[:2]
+    assert torch.equal(ids, want) and torch.equal(sc, want_sc)
