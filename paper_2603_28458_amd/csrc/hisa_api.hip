@@ -108,14 +108,33 @@ ScoreArgs base_args(const hisa_queries* q, const hisa_keys* k) {
 }
 
 // ---- scoring launches -------------------------------------------------------------------
-template <int KDT, bool GATHER>
+template <int KDT>
 void launch_ranges_mfma(ScoreArgs a, int n_tiles_max, hipStream_t st) {
+  // few queries: spread one query's tiles over many workgroups; many queries: amortise the
+  // query-fragment load over more tiles
+  a.tiles_per_wave = a.t_count >= 1024 ? 8 : (a.t_count >= 128 ? 4 : 2);
   a.groups = (n_tiles_max + 4 * a.tiles_per_wave - 1) / (4 * a.tiles_per_wave);
   dim3 grid((unsigned)((long)a.groups * a.t_count));
   if (a.H == 64)
-    hipLaunchKernelGGL((k_score_ranges<2, KDT, GATHER>), grid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL((k_score_ranges<2, KDT>), grid, dim3(256), 0, st, a);
   else
-    hipLaunchKernelGGL((k_score_ranges<1, KDT, GATHER>), grid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL((k_score_ranges<1, KDT>), grid, dim3(256), 0, st, a);
+}
+
+template <int HG, int KDT>
+void launch_gather_hg(ScoreArgs a, int n_tiles, hipStream_t st) {
+  a.tiles_per_wave = gather_tiles_per_wave(a.t_count, n_tiles);
+  a.groups = (n_tiles + 4 * a.tiles_per_wave - 1) / (4 * a.tiles_per_wave);
+  constexpr int sh = kGatherLds<HG, KDT>;
+  // (a refusal to raise the LDS limit makes the launch fail, which the entry point reports)
+  if constexpr (sh > 65536) (void)raise_lds_limit<k_score_gather<HG, KDT>>(sh);
+  hipLaunchKernelGGL((k_score_gather<HG, KDT>), dim3((unsigned)((long)a.groups * a.t_count)), dim3(256), sh, st, a);
+}
+
+template <int KDT>
+void launch_gather_mfma(const ScoreArgs& a, int n_tiles, hipStream_t st) {
+  if (a.H == 64) launch_gather_hg<2, KDT>(a, n_tiles, st);
+  else launch_gather_hg<1, KDT>(a, n_tiles, st);
 }
 
 template <int KDT>
@@ -183,15 +202,10 @@ void launch_score(int path, int key_dt, ScoreArgs a, long n_rows_max, bool conse
     return;
   }
   const int n_tiles = (int)((n_rows_max + 31) / 32);
-  // few queries: spread one query's tiles over many workgroups; many queries: amortise the
-  // query-fragment load over more tiles
-  int tpw = a.t_count >= 1024 ? 8 : (a.t_count >= 128 ? 4 : 2);
-  if (gather) tpw = gather_tiles_per_wave(a.t_count, n_tiles);
-  a.tiles_per_wave = tpw;
-  if (key_dt == HISA_BF16)
-    gather ? launch_ranges_mfma<DT_BF16, true>(a, n_tiles, st) : launch_ranges_mfma<DT_BF16, false>(a, n_tiles, st);
+  if (gather)
+    key_dt == HISA_BF16 ? launch_gather_mfma<DT_BF16>(a, n_tiles, st) : launch_gather_mfma<DT_FP8>(a, n_tiles, st);
   else
-    gather ? launch_ranges_mfma<DT_FP8, true>(a, n_tiles, st) : launch_ranges_mfma<DT_FP8, false>(a, n_tiles, st);
+    key_dt == HISA_BF16 ? launch_ranges_mfma<DT_BF16>(a, n_tiles, st) : launch_ranges_mfma<DT_FP8>(a, n_tiles, st);
 }
 
 // ---- selection launches -----------------------------------------------------------------

@@ -579,29 +579,6 @@ __global__ __launch_bounds__(256) void k_score_ranges_f32(ScoreArgs a, int keys_
   }
 }
 
-// Where virtual tile v of a query lives: key rows [row0, row0+32), output slots [out0, out0+32).
-// Flat / Stage 1: tile v covers rows 32v ..; gather (Stage 2): tile v is sub-tile v % (B/32) of
-// the kept block in slot v / (B/32).  row0 < 0: the slot is empty (-1 padding).
-struct TileLoc {
-  long row0;
-  long out0;
-};
-
-__device__ __forceinline__ TileLoc tile_loc(const ScoreArgs& a, int t, int v, bool gather) {
-  TileLoc L;
-  if (gather) {
-    const int tpb = a.B >> 5;
-    const int slot = v / tpb, sub = v - slot * tpb;
-    const int blk = a.block_idx[(long)t * a.m + slot];
-    L.out0 = (long)slot * a.B + sub * 32;
-    L.row0 = blk < 0 ? -1 : (long)blk * a.B + sub * 32;
-  } else {
-    L.row0 = (long)v * 32;
-    L.out0 = L.row0;
-  }
-  return L;
-}
-
 // ------------------------------------------------------------------------------------------
 // The per-wave scoring pipeline shared by Stage 2 and the per-query scoring kernels.
 //
@@ -647,13 +624,13 @@ __device__ __forceinline__ void tile_dma(__amdgpu_buffer_rsrc_t krsrc, __amdgpu_
     tile_dma_fp8(krsrc, srsrc, lds_addr, row);
 }
 
-// primed: the caller has already issued the DMA of tile 0 into ring slot 0 (tile_dma above), to
-// overlap it with other loads of its own.
+// primed: the caller has already issued the DMA of the first `primed` tiles into their ring slots (tile_dma above), to
+// overlap them with other loads of its own.
 template <int HG, int KDT, int NB, class RowAt, class Finish>
 __device__ __forceinline__ void wave_pipeline(const typename Operands<HG, KDT>::Frag& f,
                                               __amdgpu_buffer_rsrc_t krsrc,
                                               __amdgpu_buffer_rsrc_t srsrc, uint32_t ring_addr, int nj,
-                                              RowAt row_at, Finish finish, bool primed = false) {
+                                              RowAt row_at, Finish finish, int primed = 0) {
   static_assert(NB >= 1 && NB <= 3, "ring of one to three tiles");
   constexpr int L = TileGeom<KDT>::kLoads;
   constexpr int BB = TileGeom<KDT>::kBufBytes;
@@ -687,7 +664,7 @@ __device__ __forceinline__ void wave_pipeline(const typename Operands<HG, KDT>::
   if (nj <= 0) return;
 #pragma unroll
   for (int b = 0; b < NB; ++b)
-    if (b < nj && !(primed && b == 0)) dma(b, b);
+    if (b < nj && b >= primed) dma(b, b);
   int buf = 0;                       // ring slot of the tile the next step consumes
   float sc_a = 1.f, sc_b = 1.f;      // fp8: per-key scales of the tiles held in acc_a / acc_b
   // one step: tile jn -> acc_out (matrix cores) while tile jn-1 = acc_in is finished (vector ALU)
@@ -749,11 +726,9 @@ struct LaneTable {
   }
 };
 
-// Eq. 1 / Eq. 5 / Eq. 8 on MFMA for arbitrary queries: one workgroup of 4 waves per (group of
-// tiles, query); each wave runs the scoring pipeline over its own tiles (nothing is shared between
-// queries here: this is the decode / two-kernel path).  Writes scores, and -inf for masked slots
-// in gather mode.  tiles_per_wave <= 64.
-template <int HG, int KDT, bool GATHER>
+// Eq. 1 / Eq. 5 on MFMA for arbitrary queries: one workgroup of 4 waves per (group of 128-row tiles, query); each wave
+// runs the scoring pipeline over its own tiles (nothing is shared between queries here).  tiles_per_wave <= 64.
+template <int HG, int KDT>
 __global__ __launch_bounds__(256, 2) void k_score_ranges(ScoreArgs a) {
   constexpr int NB = 2;
   __shared__ __align__(16) unsigned char ring[4 * NB * TileGeom<KDT>::kBufBytes];
@@ -762,87 +737,124 @@ __global__ __launch_bounds__(256, 2) void k_score_ranges(ScoreArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   int seq;
   const int pos = query_pos(a, t, seq);
-  const int n_vis = GATHER ? pos + 1 : visible_rows(a, pos);
-  const int n_tiles = GATHER ? a.m * (a.B >> 5) : (n_vis + 31) >> 5;
-  // first visible row: a token when gathering, else a row of the array in order (token or block)
-  const int lo_row = GATHER ? query_lo(a.q_lo, t, pos) : query_lo(a.q_lo, t, pos) / a.pos_div;
+  const int n_vis = visible_rows(a, pos);
+  const int n_tiles = (n_vis + 31) >> 5;
+  const int lo_row = query_lo(a.q_lo, t, pos) / a.pos_div;   // first visible row (token or block)
   const int v0 = rg.x * 4 * a.tiles_per_wave;
   if (v0 >= n_tiles) return;
   const uint16_t* q_t = (const uint16_t*)a.q + (long)t * a.H * kD;
   const float* w_t = a.w + (long)t * a.H;
-  BlockList list;
-  auto whole_row = [&] {
-    return n_vis - lo_row <= a.whole_rows &&
-           never_neg_inf(w_t, a.H, a.k_scale ? a.k_scale + (long)seq * a.rows_per_seq : nullptr, lo_row, pos) &&
-           (!GATHER || blocks_ascending(a.block_idx + (long)t * a.m, a.m, a.B, lo_row, pos, list));
-  };
-  if (!GATHER && whole_row()) return;
-  // in-order rows below the first visible one are neither scored nor written: the select starts
+  if (n_vis - lo_row <= a.whole_rows &&
+      never_neg_inf(w_t, a.H, a.k_scale ? a.k_scale + (long)seq * a.rows_per_seq : nullptr, lo_row, pos))
+    return;
+  // rows below the first visible one are neither scored nor written: the select starts
   // at the first visible row (rounded down to four)
-  if (!GATHER && (v0 + 4 * a.tiles_per_wave) * 32 <= lo_row) return;
+  if ((v0 + 4 * a.tiles_per_wave) * 32 <= lo_row) return;
   float* out = a.out + (long)rg.row * a.ld;
-  const int n_blocks = (int)(a.rows_per_seq / a.B);
 
   // the four waves share one query: its fragment is loaded (fp8 keys: converted) once, through
   // the LDS of the tile rings, which are not in use yet
   static_assert(sizeof(ring) >= 32 * HG * 260, "the shared query fragment is staged in the rings");
   typename Operands<HG, KDT>::Frag fo;
+  if constexpr (KDT == DT_FP8) split_query_shared<HG, 4>(q_t, w_t, ring, wave, fo);
+  else load_qfrag_shared<HG, 4>(fo, q_t, w_t, (long)a.H * kD * 2, lds_address(ring), wave);
+
+  // this wave's tiles: v = v0 + wave + 4 j, from the first with a visible row on
+  const int v_end = v0 + 4 * a.tiles_per_wave < n_tiles ? v0 + 4 * a.tiles_per_wave : n_tiles;
+  int v_first = v0 + wave;
+  const int v_lo = lo_row >> 5;
+  if (v_first < v_lo) v_first += (v_lo - v_first + 3) >> 2 << 2;
+  const int nj = v_end > v_first ? (v_end - v_first + 3) >> 2 : 0;
+  __amdgpu_buffer_rsrc_t krsrc, srsrc;
+  key_buffers<KDT>(a, seq, krsrc, srsrc);
+  const uint32_t ring_addr = lds_address(ring) + wave * NB * TileGeom<KDT>::kBufBytes;
+  auto row_at = [&](int j) { return (v_first + 4 * j) * 32; };
+  auto finish = [&](int j, float s) {
+    const int row = row_at(j) + (lane & 31);
+    if (row < lo_row) s = neg_inf();
+    if (lane < 32 && row < n_vis) out[row] = s;
+  };
+  wave_pipeline<HG, KDT, NB>(fo, krsrc, srsrc, ring_addr, nj, row_at, finish);
+}
+
+// Eqs. 7-8 on MFMA into global memory (Stage 2 of fewer than 256 queries, or with the candidate scores asked for): one
+// workgroup of 4 waves per (group of tiles, query), a wave walking tiles_per_wave (at most 64) tiles of 32 candidates,
+// which lie at out[32 v] for tile v (-inf for slots that are masked).
+// Bound by latency with few queries and by HBM with many (every key is read once).  Nothing waits for what it does not
+// need: the query, the block ids of the wave's tiles and the query's sequence are requested together, the first tiles as
+// soon as ids and sequence are there, and the query's position is looked up behind them: three memory latencies where
+// sequence, length, query, ids and tiles one after the other are five.  That takes LDS for the query beside the rings:
+// 80 KB with 64 heads and bf16 keys, two workgroups per CU as before.
+// Refinement call against the five: 1 query (bf16, m 64) 11.8 -> 11.2 us, 32 22.9 -> 22.1, 200 (fp8) 49.1 -> 45.7, 77 (fp8)
+// 23.7 -> 22.1, 100 of 30K (fp8) 30.4 -> 28.3; 1.0-1.5 us of a kernel alone.
+template <int HG, int KDT>
+constexpr int kGatherLds = 4 * 2 * TileGeom<KDT>::kBufBytes + (KDT == DT_FP8 ? 32 * HG * 260 : HG * 8192);
+
+template <int HG, int KDT>
+__global__ __launch_bounds__(256, 2) void k_score_gather(ScoreArgs a) {
+  constexpr int NB = 2, BB = TileGeom<KDT>::kBufBytes;
+  extern __shared__ __align__(16) unsigned char smem[];   // [wave][NB] tile rings, then the query: kGatherLds
+  unsigned char* q_lds = smem + 4 * NB * BB;
+  const RowGroup rg = row_group(a.groups);
+  const int t = a.t_begin + rg.row;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int seq = query_seq(a, t);
+  const uint16_t* q_t = (const uint16_t*)a.q + (long)t * a.H * kD;
+  const float* w_t = a.w + (long)t * a.H;
+  typename Operands<HG, KDT>::Frag fo;
   SplitShare<HG, 4> q_share;
   if constexpr (KDT == DT_FP8) split_query_request<HG, 4>(q_share, q_t, w_t, wave);
-  else qfrag_shared_request<HG, 4>(fo, q_t, w_t, (long)a.H * kD * 2, lds_address(ring), wave);
-  if constexpr (GATHER) {   // (asked while the query is on its way: a decode batch never is a whole row)
-    asm volatile("" ::: "memory");
-    if (whole_row()) {
-      if (rg.x == 0) finish_whole_row<256>(a, list, t, rg.row, pos, lo_row);
+  else qfrag_shared_request<HG, 4>(fo, q_t, w_t, (long)a.H * kD * 2, lds_address(q_lds), wave);
+
+  // lane j: the first key row of this wave's j-th tile, v = v0 + wave + 4 j, or -1 (an empty slot, a block out of range)
+  const int tpb = a.B >> 5, n_tiles = a.m * tpb, n_blocks = (int)(a.rows_per_seq / a.B);
+  const int v0 = rg.x * 4 * a.tiles_per_wave;
+  const int32_t* ids = a.block_idx + (long)t * a.m;
+  const int my_v = v0 + wave + 4 * lane;
+  const bool mine = lane < a.tiles_per_wave && my_v < n_tiles;
+  int my_row = -1;
+  if (mine) {
+    const int slot = my_v / tpb;
+    const int blk = ids[slot];
+    if (blk >= 0 && blk < n_blocks) my_row = blk * a.B + (my_v - slot * tpb) * 32;
+  }
+  const uint64_t used = __ballot(my_row >= 0);
+  const int nj = used ? 64 - __builtin_clzll(used) : 0;   // the tiles behind the last used one hold nothing
+  auto row_at = [&](int j) {
+    const int r = __builtin_amdgcn_readlane(my_row, j);
+    return r < 0 ? 0 : r;   // a tile without a block flows through and is masked below
+  };
+  __amdgpu_buffer_rsrc_t krsrc, srsrc;
+  key_buffers<KDT>(a, seq, krsrc, srsrc);
+  const uint32_t ring_addr = lds_address(smem) + wave * NB * BB;
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+    if (b < nj) tile_dma<KDT>(krsrc, srsrc, ring_addr + b * BB, row_at(b));
+
+  const int pos = query_pos_in(a, t, seq);
+  const int n_vis = pos + 1;
+  const int lo = query_lo(a.q_lo, t, pos);
+  if (n_vis - lo <= a.whole_rows) {
+    BlockList list;
+    if (never_neg_inf(w_t, a.H, a.k_scale ? a.k_scale + (long)seq * a.rows_per_seq : nullptr, lo, pos) &&
+        blocks_ascending(ids, a.m, a.B, lo, pos, list)) {
+      if (rg.x == 0) finish_whole_row<256>(a, list, t, rg.row, pos, lo);
       wait_vmem_le<0>();    // (nothing may still be on its way into this workgroup's LDS)
       return;
     }
   }
-  if constexpr (KDT == DT_FP8) split_query_complete<HG, 4>(q_share, ring, wave, fo);
-  else qfrag_shared_complete<HG>(fo, lds_address(ring));
-
-  // this wave's tiles: v = v0 + wave + 4 i; lane i looks its tile up; tiles without a visible key
-  // are filled with -inf here (gather mode) and left out of the pipeline
-  int my_row = -1, my_out = 0;
-  {
-    const int v = v0 + wave + 4 * lane;
-    if (lane < a.tiles_per_wave && v < n_tiles) {
-      const TileLoc Lc = tile_loc(a, t, v, GATHER);
-      my_out = (int)Lc.out0;
-      const bool ok = Lc.row0 >= 0 && Lc.row0 < n_vis && Lc.row0 + 32 > lo_row &&
-                      (!GATHER || Lc.row0 / a.B < n_blocks);
-      if (ok) my_row = (int)Lc.row0;
-      else if (GATHER)
-        for (int x = 0; x < 32; ++x) out[my_out + x] = neg_inf();
-    }
-  }
-  // compact the valid tiles to the low lanes (order does not matter)
-  const uint64_t okmask = __ballot(my_row >= 0);
-  const int nj = __popcll(okmask);
-  LaneTable rows{-1, -1}, outs{0, 0};
-  {
-    // lane j fetches the j-th valid entry: the source lane is the j-th set bit of okmask
-    int src = 0;
-    uint64_t mrem = okmask;
-    for (int q = 0; q < 64; ++q) {           // wave-uniform loop over set bits
-      if (!mrem) break;
-      const int bit = __builtin_ctzll(mrem);
-      mrem &= mrem - 1;
-      if (lane == q) src = bit;
-    }
-    rows.lo = __shfl(my_row, src);
-    outs.lo = __shfl(my_out, src);
-  }
-  __amdgpu_buffer_rsrc_t krsrc, srsrc;
-  key_buffers<KDT>(a, seq, krsrc, srsrc);
-  const uint32_t ring_addr = lds_address(ring) + wave * NB * TileGeom<KDT>::kBufBytes;
-  auto row_at = [&](int j) { return rows.at(j); };
+  float* out = a.out + (long)rg.row * a.ld;
+  if (mine && lane >= nj)
+    for (int x = 0; x < 32; ++x) out[my_v * 32 + x] = neg_inf();
+  if constexpr (KDT == DT_FP8) split_query_complete<HG, 4>(q_share, q_lds, wave, fo);
+  else qfrag_shared_complete<HG>(fo, lds_address(q_lds));
   auto finish = [&](int j, float s) {
-    const int row = rows.at(j) + (lane & 31);
-    if (row >= n_vis || row < lo_row) s = neg_inf();
-    if (lane < 32 && (GATHER || row < n_vis)) out[outs.at(j) + lane] = s;
+    const int r = __builtin_amdgcn_readlane(my_row, j);
+    const int row = r + (lane & 31);
+    if (r < 0 || row >= n_vis || row < lo) s = neg_inf();
+    if (lane < 32) out[(v0 + wave + 4 * j) * 32 + lane] = s;
   };
-  wave_pipeline<HG, KDT, NB>(fo, krsrc, srsrc, ring_addr, nj, row_at, finish);
+  wave_pipeline<HG, KDT, NB>(fo, krsrc, srsrc, ring_addr, nj, row_at, finish, NB);
 }
 
 // Eq. 1 / Eq. 5 on MFMA for a causal prefill of ONE sequence with consecutive positions: one
@@ -1826,7 +1838,7 @@ __device__ __forceinline__ void stage1_in_workgroup(const QFrag<HG>& f, const Sc
         }
         if (lane < 32) sc[b] = visible ? s : neg_inf();
       },
-      primed && nj1 > 0);
+      primed && nj1 > 0 ? 1 : 0);
   // (an infinite range makes the one-pass top-k decline: the select below takes a NaN score first)
   if constexpr (kFine) fine_select_range<NT, E1>(*fine.sm, any_nan ? __builtin_inff() : s_max, s_min, wave);
   __syncthreads();   // block scores complete, rings dead
@@ -2109,7 +2121,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_refine_fused(Score
     s_max = vmax_f32(s_max, s);
     s_min = vmin_f32(s_min, s);
   };
-  wave_pipeline<HG, KDT, NB>(fo, krsrc, srsrc, ring_addr, nj, row_at, finish, primed);
+  wave_pipeline<HG, KDT, NB>(fo, krsrc, srsrc, ring_addr, nj, row_at, finish, primed ? 1 : 0);
   fine_select_range<NT, E>(fs, s_max, s_min, wave);
   __syncthreads();   // scores complete, rings dead: the select scratch may overwrite them
   const int n_cand_slots = n_active * 32;   // score slots actually written
