@@ -323,13 +323,7 @@ __device__ __forceinline__ accvec<HG> mfma_tile(const QFrag<HG>& f, const u32x32
   return out;
 }
 
-// Sum of both 32-lane halves in every lane (one swap of the halves, one add).
-__device__ __forceinline__ float add_halves(float s) {
-  const uint32_t b = __float_as_uint(s);
-  const auto sw = __builtin_amdgcn_permlane32_swap(b, b, false, false);
-  return __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-}
-
+// ReLU, gate and head sum of one tile: a lane's share, the other half of its key's heads being 32 lanes away.
 template <int HG, class Frag>
 __device__ __forceinline__ float tile_epilogue(const Frag& f, const accvec<HG>& acc) {
   float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
@@ -343,7 +337,15 @@ __device__ __forceinline__ float tile_epilogue(const Frag& f, const accvec<HG>& 
       s3 = __builtin_fmaf(relu(acc[g * 16 + i + 3]), f.w[g][i + 3], s3);
     }
   }
-  return add_halves((s0 + s1) + (s2 + s3));
+  float s = (s0 + s1) + (s2 + s3);
+  asm volatile("" : "+v"(s));   // (summed HERE, over the MFMAs it stands beside, and not where it is first needed)
+  return s;
+}
+
+// The shares of two tiles put together: lanes 0-31 get the scores of the first, lanes 32-63 those of the second.
+__device__ __forceinline__ float join_tiles(float a, float b) {
+  const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -592,7 +592,12 @@ __global__ __launch_bounds__(256) void k_score_ranges_f32(ScoreArgs a, int keys_
 // a wave waits on an LDS read: Stage 2 of the 64K prefill 3-4 % slower with bf16 and with fp8 keys,
 // wherever in the step the next DMA was issued.  The step is not waiting on LDS latency.)
 // row_at(j): first key row of tile j (wave-uniform, a row inside the sequence's key array);
-// finish(j, s): lane l < 32 receives the score of key row_at(j) + l (fp8: already scaled).
+// finish(j, both, s): tiles are finished two at a time (one exchange of halves, one mask, one store for 64 keys):
+// lane l < 32 receives the score of key row_at(j) + l, lane 32 + l that of row_at(j + 1) + l if `both`, else nothing
+// (fp8: already scaled).  One at a time, half of the lanes had nothing to mask, compare and store: 78 vector instructions a
+// tile instead of 71 (64 are the heads' ReLU and gate), and 6 branches; Stage 2 at 64K 8774 -> 8347 us (bf16), 6947 -> 6747
+// (fp8), at 16K 1031 -> 989, 1024 queries at 64K 161 -> 154, the flat indexer there 1011 -> 976, Stage 1 of the 1M chunk
+// 2073 -> 1990 (one card, which runs all of them at its power limit).
 template <int KDT>
 struct TileGeom {
   static constexpr int kLoads = KDT == DT_BF16 ? 8 : 5;                 // DMA instructions per tile
@@ -667,8 +672,8 @@ __device__ __forceinline__ void wave_pipeline(const typename Operands<HG, KDT>::
     if (b < nj && b >= primed) dma(b, b);
   int buf = 0;                       // ring slot of the tile the next step consumes
   float sc_a = 1.f, sc_b = 1.f;      // fp8: per-key scales of the tiles held in acc_a / acc_b
-  // one step: tile jn -> acc_out (matrix cores) while tile jn-1 = acc_in is finished (vector ALU)
-  auto step = [&](int jn, const accvec<HG>& acc_in, float sc_in, accvec<HG>& acc_out, float& sc_out) {
+  // one step: tile jn -> acc_out (matrix cores) while the vector ALU sums the heads of tile jn-1 = acc_in
+  auto step = [&](int jn, const accvec<HG>& acc_in, accvec<HG>& acc_out, float& sc_out) -> float {
     wait_tile(jn);
     if constexpr (KDT == DT_BF16) {
       // bf16 tile: the MFMAs of the first two 16-element chunks start as soon as those chunks are
@@ -681,14 +686,18 @@ __device__ __forceinline__ void wave_pipeline(const typename Operands<HG, KDT>::
       acc_out = mfma_tile_progressive<HG>(f, tr, [&] {
         if (jn + NB < nj) dma(jn + NB, slot);
       });
-      finish(jn - 1, tile_epilogue<HG>(f, acc_in) * sc_in);
-      return;
+      return tile_epilogue<HG>(f, acc_in);
     }
     const Tile kv = read_tile(buf, sc_out);
     if (jn + NB < nj) dma(jn + NB, buf);
     buf = (buf + 1 == NB) ? 0 : buf + 1;
     acc_out = mfma_tile(f, kv);
-    finish(jn - 1, tile_epilogue<HG>(f, acc_in) * sc_in);
+    return tile_epilogue<HG>(f, acc_in);
+  };
+  auto finish2 = [&](int j, bool both, float first, float second, float sc_first, float sc_second) {
+    float s = join_tiles(first, second);
+    if constexpr (KDT == DT_FP8) s *= lane < 32 ? sc_first : sc_second;
+    finish(j, both, s);
   };
   wait_tile(0);
   const Tile kv0 = read_tile(0, sc_a);
@@ -697,14 +706,18 @@ __device__ __forceinline__ void wave_pipeline(const typename Operands<HG, KDT>::
   accvec<HG> acc_a = mfma_tile(f, kv0), acc_b;
   int j = 0;                         // acc_a holds tile j
   for (; j + 2 < nj; j += 2) {
-    step(j + 1, acc_a, sc_a, acc_b, sc_b);
-    step(j + 2, acc_b, sc_b, acc_a, sc_a);
+    float sc_next = 1.f;
+    const float first = step(j + 1, acc_a, acc_b, sc_b);
+    const float second = step(j + 2, acc_b, acc_a, sc_next);
+    finish2(j, true, first, second, sc_a, sc_b);
+    sc_a = sc_next;
   }
   if (j + 1 < nj) {
-    step(j + 1, acc_a, sc_a, acc_b, sc_b);
-    finish(j + 1, tile_epilogue<HG>(f, acc_b) * sc_b);
+    const float first = step(j + 1, acc_a, acc_b, sc_b);
+    finish2(j, true, first, tile_epilogue<HG>(f, acc_b), sc_a, sc_b);
   } else {
-    finish(j, tile_epilogue<HG>(f, acc_a) * sc_a);
+    const float first = tile_epilogue<HG>(f, acc_a);
+    finish2(j, false, first, first, sc_a, sc_a);
   }
 }
 
@@ -718,11 +731,12 @@ __device__ __forceinline__ void key_buffers(const ScoreArgs& a, int seq, __amdgp
                      a.k_scale ? a.rows_per_seq * 4 : 0);
 }
 
-// Lane j of the returned pair holds rows[j] / rows[64 + j]; at(j) broadcasts entry j.
+// Lane j holds rows[j] and, WIDE, rows[64 + j]; at(j) broadcasts entry j.
+template <bool WIDE>
 struct LaneTable {
   int lo, hi;
   __device__ __forceinline__ int at(int j) const {
-    return j < 64 ? __builtin_amdgcn_readlane(lo, j) : __builtin_amdgcn_readlane(hi, j - 64);
+    return !WIDE || j < 64 ? __builtin_amdgcn_readlane(lo, j) : __builtin_amdgcn_readlane(hi, j - 64);
   }
 };
 
@@ -769,10 +783,10 @@ __global__ __launch_bounds__(256, 2) void k_score_ranges(ScoreArgs a) {
   key_buffers<KDT>(a, seq, krsrc, srsrc);
   const uint32_t ring_addr = lds_address(ring) + wave * NB * TileGeom<KDT>::kBufBytes;
   auto row_at = [&](int j) { return (v_first + 4 * j) * 32; };
-  auto finish = [&](int j, float s) {
-    const int row = row_at(j) + (lane & 31);
+  auto finish = [&](int j, bool both, float s) {
+    const int row = row_at(j) + (lane < 32 ? lane : 96 + lane);   // (a wave's next tile is 128 rows on)
     if (row < lo_row) s = neg_inf();
-    if (lane < 32 && row < n_vis) out[row] = s;
+    if ((both || lane < 32) && row < n_vis) out[row] = s;
   };
   wave_pipeline<HG, KDT, NB>(fo, krsrc, srsrc, ring_addr, nj, row_at, finish);
 }
@@ -848,11 +862,12 @@ __global__ __launch_bounds__(256, 2) void k_score_gather(ScoreArgs a) {
     for (int x = 0; x < 32; ++x) out[my_v * 32 + x] = neg_inf();
   if constexpr (KDT == DT_FP8) split_query_complete<HG, 4>(q_share, q_lds, wave, fo);
   else qfrag_shared_complete<HG>(fo, lds_address(q_lds));
-  auto finish = [&](int j, float s) {
-    const int r = __builtin_amdgcn_readlane(my_row, j);
+  auto finish = [&](int j, bool both, float s) {
+    const int r0 = __builtin_amdgcn_readlane(my_row, j), r1 = __builtin_amdgcn_readlane(my_row, both ? j + 1 : j);
+    const int r = lane < 32 ? r0 : r1;
     const int row = r + (lane & 31);
     if (r < 0 || row >= n_vis || row < lo) s = neg_inf();
-    if (lane < 32) out[(v0 + wave + 4 * j) * 32 + lane] = s;
+    if (both || lane < 32) out[(v0 + wave + 4 * j) * 32 + (lane < 32 ? lane : 96 + lane)] = s;
   };
   wave_pipeline<HG, KDT, NB>(fo, krsrc, srsrc, ring_addr, nj, row_at, finish, NB);
 }
@@ -949,10 +964,12 @@ __global__ __launch_bounds__(512) void k_score_prefill(ScoreArgs a) {
       return lds_read_tile_fp8_raw(addr);
     }
   };
-  // sub-tile u of this workgroup covers the 32 rows from it0 * TK + 32u
-  auto finish = [&](int u, float s) {
-    const int row = it0 * TK + u * 32 + (lane & 31);
-    if (lane < 32 && row < n_vis) out[row] = s;
+  // sub-tile u of this workgroup covers the 32 rows from it0 * TK + 32u; u is even here and u + 1 is finished with it
+  auto finish = [&](int u, float first, float second, float sc_first, float sc_second) {
+    float s = join_tiles(first, second);
+    if constexpr (KDT == DT_FP8) s *= lane < 32 ? sc_first : sc_second;
+    const int row = it0 * TK + u * 32 + lane;
+    if (row < n_vis) out[row] = s;
   };
 
   if (n_iter > 0) dma_tile(0, 0);
@@ -974,25 +991,24 @@ __global__ __launch_bounds__(512) void k_score_prefill(ScoreArgs a) {
   wait_vmem_le<0>();
   __syncthreads();
   accvec<HG> acc_a, acc_b;
-  float sc_a = 1.f, sc_b = 1.f;
+  float sc_a = 1.f, sc_b = 1.f, sum_a = 0.f;   // sum_a: the head sums of an even sub-tile, until the next one's are there
   for (int it = 0; it < n_iter; ++it) {
     const int buf = it & 1;
     if (it + 1 < n_iter) dma_tile(it + 1, buf ^ 1);
 #pragma unroll
     for (int h = 0; h < SUBS / 2; ++h) {
-      {
-        acc_b = score_sub(buf, 2 * h, sc_b);                                       // sub-tile SUBS*it + 2h
-        if (it > 0 || h > 0) finish(SUBS * it + 2 * h - 1, tile_epilogue<HG>(f, acc_a) * sc_a);   // the one before
-      }
-      {
-        acc_a = score_sub(buf, 2 * h + 1, sc_a);                                   // sub-tile SUBS*it + 2h + 1
-        finish(SUBS * it + 2 * h, tile_epilogue<HG>(f, acc_b) * sc_b);
-      }
+      float sc_next = 1.f;
+      acc_a = score_sub(buf, 2 * h, sc_next);                                      // sub-tile SUBS*it + 2h
+      if (it > 0 || h > 0)                                                         // the two before
+        finish(SUBS * it + 2 * h - 2, sum_a, tile_epilogue<HG>(f, acc_b), sc_a, sc_b);
+      sc_a = sc_next;
+      acc_b = score_sub(buf, 2 * h + 1, sc_b);                                     // sub-tile SUBS*it + 2h + 1
+      sum_a = tile_epilogue<HG>(f, acc_a);
     }
     wait_vmem_le<0>();   // the next tile (and this wave's score stores) have landed
     __syncthreads();
   }
-  if (n_iter > 0) finish(SUBS * n_iter - 1, tile_epilogue<HG>(f, acc_a) * sc_a);
+  if (n_iter > 0) finish(SUBS * n_iter - 2, sum_a, tile_epilogue<HG>(f, acc_b), sc_a, sc_b);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1059,9 +1075,11 @@ __global__ __launch_bounds__(512) void k_score_resident(ScoreArgs a) {
     QFrag<HG> f;
     load_qfrag<HG>(f, (const uint16_t*)a.q + (long)t * a.H * kD, a.w + (long)t * a.H);
     qfrag_ready<HG>(f);
-    auto store = [&](int u, float s) {
-      const int row = u * 32 + (lane & 31);
-      if (lane < 32 && row < n_vis) out[row] = row < lo_row ? neg_inf() : s;
+    // sub-tiles u and, if `both`, u + 1
+    auto store = [&](int u, bool both, float first, float second) {
+      const float s = join_tiles(first, second);
+      const int row = u * 32 + lane;
+      if ((both || lane < 32) && row < n_vis) out[row] = row < lo_row ? neg_inf() : s;
     };
     // MFMAs of sub-tile u over the epilogue of sub-tile u-1 (two accumulator sets, unrolled by two)
     int u = lo_row >> 5;                 // acc_a holds sub-tile u
@@ -1069,16 +1087,17 @@ __global__ __launch_bounds__(512) void k_score_resident(ScoreArgs a) {
     accvec<HG> acc_a = mfma_tile<HG>(f, lds_read_tile_raw(tiles_addr + u * 8192)), acc_b;
     for (; u + 2 < nu; u += 2) {
       acc_b = mfma_tile<HG>(f, lds_read_tile_raw(tiles_addr + (u + 1) * 8192));
-      store(u, tile_epilogue<HG>(f, acc_a));
+      const float first = tile_epilogue<HG>(f, acc_a);
       acc_a = mfma_tile<HG>(f, lds_read_tile_raw(tiles_addr + (u + 2) * 8192));
-      store(u + 1, tile_epilogue<HG>(f, acc_b));
+      store(u, true, first, tile_epilogue<HG>(f, acc_b));
     }
     if (u + 1 < nu) {
       acc_b = mfma_tile<HG>(f, lds_read_tile_raw(tiles_addr + (u + 1) * 8192));
-      store(u, tile_epilogue<HG>(f, acc_a));
-      store(u + 1, tile_epilogue<HG>(f, acc_b));
+      const float first = tile_epilogue<HG>(f, acc_a);
+      store(u, true, first, tile_epilogue<HG>(f, acc_b));
     } else {
-      store(u, tile_epilogue<HG>(f, acc_a));
+      const float first = tile_epilogue<HG>(f, acc_a);
+      store(u, false, first, first);
     }
   }
 }
@@ -1827,16 +1846,16 @@ __device__ __forceinline__ void stage1_in_workgroup(const QFrag<HG>& f, const Sc
   wave_pipeline<HG, DT_BF16, NB>(
       f, prsrc, prsrc, lds_address(smem) + wave * NB * TILE, nj1,
       [&](int j) { return (wave + NW * j) * 32; },
-      [&](int j, float s) {
-        const int b = (wave + NW * j) * 32 + (lane & 31);
-        const bool visible = b < n_bvis && b >= b_first;
+      [&](int j, bool both, float s) {
+        const int b = (wave + NW * j) * 32 + (lane < 32 ? lane : NW * 32 + lane - 32);
+        const bool visible = (both || lane < 32) && b < n_bvis && b >= b_first;
         if constexpr (kFine) {
-          const float x = b > b_first && b < n_last ? s : __uint_as_float(0xffffffffu);   // (NaN is passed over)
+          const float x = (both || lane < 32) && b > b_first && b < n_last ? s : __uint_as_float(0xffffffffu);   // (NaN is passed over)
           s_max = vmax_f32(s_max, x);
           s_min = vmin_f32(s_min, x);
           any_nan |= visible && s != s;
         }
-        if (lane < 32) sc[b] = visible ? s : neg_inf();
+        if (both || lane < 32) sc[b] = visible ? s : neg_inf();
       },
       primed && nj1 > 0 ? 1 : 0);
   // (an infinite range makes the one-pass top-k decline: the select below takes a NaN score first)
@@ -2076,10 +2095,10 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_refine_fused(Score
     return (blk < 0 || blk >= n_blocks || row0 >= n_vis) ? -1 : row0;
   };
   const int nj = n_active > wave ? (n_active - wave + NW - 1) / NW : 0;   // tiles of this wave
-  // lane j holds the first key row of this wave's j-th tile (wave + NW * j)
-  LaneTable rows;
+  // lane j holds the first key row of this wave's j-th tile (wave + NW * j), of which there are at most 2 * E
+  LaneTable<(E > 32)> rows;
   rows.lo = row_of(wave + NW * (lane < nj ? lane : 0));
-  rows.hi = (nj > 64) ? row_of(wave + NW * (lane + 64 < nj ? lane + 64 : 0)) : -1;
+  rows.hi = (E > 32 && nj > 64) ? row_of(wave + NW * (lane + 64 < nj ? lane + 64 : 0)) : -1;
   __amdgpu_buffer_rsrc_t krsrc, srsrc;
   key_buffers<KDT>(a, seq, krsrc, srsrc);
   auto row_at = [&](int j) {
@@ -2100,24 +2119,25 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_refine_fused(Score
     Operands<HG, KDT>::make(f, fo);
   }
   float s_max = -__builtin_inff(), s_min = __builtin_inff();   // this lane's largest / smallest score so far
-  // score_slot of candidate tile * 32 + lane is tile * 32 + a lane pattern that depends on tile % 8
-  // only, and this wave's tiles (wave + NW * j) alternate between two values of it
-  static_assert((2 * NW) % 8 == 0, "a wave's tiles take two values modulo 8");
+  // Score_slot of candidate tile * 32 + lane is tile * 32 + a lane pattern that depends on tile % 8 only.  Two tiles,
+  // wave + NW * j and the next, are finished together, the second by lanes 32-63; j is even, so a lane's address
+  // advances by 2 * NW tiles and its pattern stays.
+  static_assert((2 * NW) % 8 == 0, "a lane's tiles must agree modulo 8");
   const int l31 = lane & 31;
-  const uint32_t pat0 = (uint32_t)(((((l31 >> 2) ^ wave) & 7) << 2) | (l31 & 3)) * 4u;
-  const uint32_t pat1 = (uint32_t)(((((l31 >> 2) ^ (wave + NW)) & 7) << 2) | (l31 & 3)) * 4u;
-  const uint32_t sc_addr = lds_address(sc);
+  const int my_tile = wave + NW * (lane >> 5);
+  const uint32_t sc_lane = lds_address(sc) + (uint32_t)my_tile * 128u + (uint32_t)(((((l31 >> 2) ^ my_tile) & 7) << 2) | (l31 & 3)) * 4u;
   const int lane_lo = l31 - lo;
-  auto finish = [&](int j, float s) {
-    const int r = rows.at(j);
+  const uint32_t span = n_vis - lo > 0 ? (uint32_t)(n_vis - lo) : 0u;
+  auto finish = [&](int j, bool both, float s) {
+    const int r0 = rows.at(j), r1 = both ? rows.at(j + 1) : -1;
+    const int r = lane < 32 ? r0 : r1;
     // a masked slot holds the all-ones pattern, a NaN (ordered_key_plain sends it to "not a
     // candidate", the maximum / minimum below ignore it); a finished score is a sum that starts
     // from +0, so it is never -0.  Visible: lo <= row < n_vis, i.e. unsigned(row - lo) < n_vis - lo
     // (nothing, for a tile without a kept block).
-    const int span = r < 0 ? 0 : (n_vis - lo > 0 ? n_vis - lo : 0);
-    if ((uint32_t)((r < 0 ? 0 : r) + lane_lo) >= (uint32_t)span) s = __uint_as_float(kNoCandidateBits);
-    const uint32_t addr = sc_addr + (uint32_t)(wave + NW * j) * 128u + ((j & 1) ? pat1 : pat0);
-    if (lane < 32) asm volatile("ds_write_b32 %0, %1" : : "v"(addr), "v"(s) : "memory");
+    if (r < 0 || (uint32_t)(r + lane_lo) >= span) s = __uint_as_float(kNoCandidateBits);
+    const uint32_t addr = sc_lane + (uint32_t)(NW * 128) * (uint32_t)j;
+    if (both || lane < 32) asm volatile("ds_write_b32 %0, %1" : : "v"(addr), "v"(s) : "memory");
     s_max = vmax_f32(s_max, s);
     s_min = vmin_f32(s_min, s);
   };
