@@ -84,6 +84,15 @@ inline int wgs_per_cu(long lds, int max_wgs) {
   return n < 1 ? 1 : n < max_wgs ? (int)n : max_wgs;
 }
 
+// Fused Stage 2: ticks (10 ns) that a wave takes for two tiles of 32 keys, by which the walks of all workgroups are laid
+// over each other (k_refine_fused); 0 where the keys of a sequence fit an XCD's L2 anyway.  Measured per tile, us:
+// 0.8-1.1 with bf16 keys, 0.65-1.1 with fp8.  Too long costs little, too short a lot (20000 bf16 queries at 128K with
+// 0.65 / 0.8 / 0.95 / 1.1 / 1.3: 3921 / 2749 / 2778 / 2854 / 2964 us, 4166 without; 16000 at 256K: 3825 / 3462 / 2591 / 2662 /
+// 2828, 3834; 16000 fp8 at 500K: 1858 / 1874 / 1892 / 1902 / 1906, 1917), so bf16 has the long end of its range.
+inline unsigned walk_ticks(long key_bytes, bool fp8) {
+  return key_bytes <= 4l << 20 ? 0u : fp8 ? 160u : 200u;
+}
+
 // Fused Stage 2 with 32 heads: do the top-k's bins lie in the tile rings, so that `with` instead of `without`
 // workgroups fit on a CU (k_refine_fused, wgs_per_cu)?  One more workgroup hides more of the tiles' latency (16K prefill,
 // m 32, bf16 keys 733 -> 668 us, fp8 keys, m 64 +10 %), except where

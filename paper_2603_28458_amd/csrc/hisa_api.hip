@@ -279,7 +279,9 @@ int launch_fused_ring(const ScoreArgs& a, int k, int32_t* topk_idx, float* topk_
   const size_t sh = fused_lds<HG, KDT, NW, E, RING>(a);
   constexpr auto kern = k_refine_fused<HG, KDT, NW, kNBuf, E, 0, RING>;
   if (raise_lds_limit<kern>(sh)) return HISA_ERR_LAUNCH;
-  hipLaunchKernelGGL(kern, dim3(a.t_count), dim3(NW * 64), sh, st, a, k, topk_idx, topk_scores,
+  ScoreArgs aw = a;
+  aw.walk = walk_ticks(a.rows_per_seq * kD * (KDT == DT_FP8 ? 1 : 2), KDT == DT_FP8);
+  hipLaunchKernelGGL(kern, dim3(a.t_count), dim3(NW * 64), sh, st, aw, k, topk_idx, topk_scores,
                      (const void*)nullptr, (int32_t*)nullptr, 0);
   return HISA_OK;
 }

@@ -58,6 +58,8 @@ struct ScoreArgs {
   int whole_rows;
   int k;                     // gather with whole_rows: such a query's ids are written here, [T, k], and its score
   int32_t* topk_idx;         //   row starts with kRowDoneBits
+  uint32_t walk;             // fused Stage 2: ticks of the real-time counter per two tiles of a walk, 0: walks start at
+                             //   their first tile (walk_ticks)
 };
 
 // First entry of a score row whose query needs no select (ScoreArgs::whole_rows): a signalling NaN, which no
@@ -2097,8 +2099,21 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_refine_fused(Score
   const int nj = n_active > wave ? (n_active - wave + NW - 1) / NW : 0;   // tiles of this wave
   // lane j holds the first key row of this wave's j-th tile (wave + NW * j), of which there are at most 2 * E
   LaneTable<(E > 32)> rows;
-  rows.lo = row_of(wave + NW * (lane < nj ? lane : 0));
-  rows.hi = (E > 32 && nj > 64) ? row_of(wave + NW * (lane + 64 < nj ? lane + 64 : 0)) : -1;
+  // The walk over them starts where the others are by now.  Workgroups start as CUs come free, so after a few rounds the
+  // walks of an XCD are spread over the whole key array, and its 4 MB L2 sees all of it at once.  The blocks are in key
+  // order, so a walk that begins at (time / duration of a walk) of its tiles and wraps round meets the walks of its
+  // neighbours on the same keys, whenever each of them began; a duration that is 20 % off lets them drift apart by 20 % of
+  // the array within a walk.  Where a walk starts changes nothing in its results (a tile's scores have their own place).
+  // Stage 2, us: bf16 keys, 64 heads, prefill of 64K 8067 -> 7761, 20000 queries at 128K 4166 -> 2749, 16000 at 256K
+  // 3834 -> 2591, 8000 at 500K 1857 -> 1689; 32 heads, prefill of 60K 6132 -> 5446; fp8 keys, 64K 6443 -> 6343, 12000 at 128K (32 heads) 961 -> 854, 16384 at 1M
+  // 4233 -> 4085; 1024 queries at 64K and 16K prefill +-0.5 %.  (By the launch order instead of the clock: 128K 3040, but
+  // 1024 queries at 64K, which all start at once, 151 -> 198.)
+  int j0 = 0;
+  if (E1 == 0 && a.walk != 0u && nj > 0 && (nj & 1) == 0)   // (pairs of tiles are finished together: an odd walk starts at 0)
+    j0 = (int)(((uint32_t)__builtin_amdgcn_s_memrealtime() / a.walk) % ((uint32_t)nj >> 1)) * 2;
+  auto walked = [&](int j) { return j + j0 < nj ? j + j0 : j + j0 - nj; };
+  rows.lo = row_of(wave + NW * (lane < nj ? walked(lane) : 0));
+  rows.hi = (E > 32 && nj > 64) ? row_of(wave + NW * (lane + 64 < nj ? walked(lane + 64) : 0)) : -1;
   __amdgpu_buffer_rsrc_t krsrc, srsrc;
   key_buffers<KDT>(a, seq, krsrc, srsrc);
   auto row_at = [&](int j) {
@@ -2136,7 +2151,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_refine_fused(Score
     // from +0, so it is never -0.  Visible: lo <= row < n_vis, i.e. unsigned(row - lo) < n_vis - lo
     // (nothing, for a tile without a kept block).
     if (r < 0 || (uint32_t)(r + lane_lo) >= span) s = __uint_as_float(kNoCandidateBits);
-    const uint32_t addr = sc_lane + (uint32_t)(NW * 128) * (uint32_t)j;
+    const uint32_t addr = sc_lane + (uint32_t)(NW * 128) * (uint32_t)walked(j);
     if (both || lane < 32) asm volatile("ds_write_b32 %0, %1" : : "v"(addr), "v"(s) : "memory");
     s_max = vmax_f32(s_max, s);
     s_min = vmin_f32(s_min, s);

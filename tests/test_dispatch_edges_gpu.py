@@ -306,3 +306,32 @@ def test_fp32_rows_in_one_launch(T, H, d, B, m, k):
     ids, sc = hisa.hisa_token_refine_topk(Q, K, B, m, blocks, k, want_topk_scores=True)[:2]
     want, want_sc = hisa.hisa_token_refine_topk(Q, K, B, m, blocks, k, want_topk_scores=True, want_cand_scores=True)[:2]
     assert torch.equal(ids, want) and torch.equal(sc, want_sc)
+
+
+@pytest.mark.parametrize("k_dtype,H,L,B,m,k", [
+    ("bf16", 64, 16500, 32, 200, 700), ("bf16", 64, 17000, 32, 133, 500), ("bf16", 32, 16400, 32, 128, 512), ("bf16", 32, 20000, 64, 120, 900),
+    ("fp8_e4m3", 64, 33000, 32, 256, 1000), ("fp8_e4m3", 32, 33000, 32, 100, 400), ("fp8_e4m3", 64, 34000, 128, 128, 2000),
+    ("bf16", 32, 16500, 32, 400, 1000)])
+def test_walks_that_start_anywhere(k_dtype, H, L, B, m, k):
+    # fused Stage 2 over keys that fill more than 4 MB: where a query's walk over its tiles begins follows the clock, and
+    # the ids must not: the same bits as the two-kernel route in every call; 4 and 8 waves per query, odd walks,
+    # lists with fewer blocks than m (walks of another length), waves with unequal walks
+    import time
+    import torch
+    from paper_2603_28458_amd import hisa
+
+    T = 300
+    wl = W.make_workload(f"walk_{k_dtype}_{m}", seq_len=L, T=T, H=H, d=128, B=B, m=m, k=k, q_dtype="bf16", k_dtype=k_dtype, seed=500)
+    assert wl.keys.nbytes > 4 << 20
+    print(f"\n[walk] {wl.name} H={H} L={L} B={B} k={k}", flush=True)
+    Q, K = hisa.to_device(wl)
+    rng = np.random.default_rng(501)
+    lists = np.sort(np.argsort(rng.random((T, (L - T) // B)), 1)[:, :m], 1).astype(np.int32)
+    for t in range(0, T, 3):
+        lists[t, int(rng.integers(1, m + 1)):] = -1
+    blocks = torch.from_numpy(lists).cuda()
+    want = hisa.hisa_token_refine_topk(Q, K, B, m, blocks, k, want_cand_scores=True)[0]
+    for i in range(12):
+        got = hisa.hisa_token_refine_topk(Q, K, B, m, blocks, k)[0]
+        assert torch.equal(got, want), i
+        time.sleep(0.0007)
