@@ -339,28 +339,28 @@ int launch_indexer(const ScoreArgs& a, const void* pooled, int k, int32_t* block
              : launch_indexer_hg<1, KDT, NW, 32>(a, pooled, k, block_idx_out, topk_idx, topk_scores, st);
 }
 
-// Stage 1 of a small batch in one launch (k_stage1_query): M blocks per sequence, E1 per thread.
-template <int HG, int E1>
+// Stage 1 of a small batch in one launch (k_stage1_query): M blocks per sequence (NW * 64 * E1 at most), E1 per thread.
+template <int HG, int E1, int NW>
 int launch_stage1_query_e(const ScoreArgs& a, const void* pooled, int M, int32_t* block_idx, hipStream_t st) {
   const int sc_floats = (int)round_up(M, 32);
-  // up to 2048 blocks a ring of two tiles per wave fits beside the scores, above that a ring of one
-  constexpr int NB = E1 <= 4 ? 2 : 1;
-  const size_t sh = (size_t)8 * NB * 8192 + (size_t)sc_floats * 4 + (size_t)round_up(a.m, 4) * 4 + (size_t)HG * 8192;
-  constexpr auto kern = k_stage1_query<HG, E1, NB>;
+  // 8 waves: up to 2048 blocks a ring of two tiles per wave fits beside the scores, above that a ring of one
+  constexpr int NB = NW == 8 && E1 <= 4 ? 2 : 1;
+  const size_t sh = (size_t)NW * NB * 8192 + (size_t)sc_floats * 4 + (size_t)round_up(a.m, 4) * 4 + (size_t)HG * 8192;
+  constexpr auto kern = k_stage1_query<HG, E1, NB, NW>;
   if (raise_lds_limit<kern>(sh)) return HISA_ERR_LAUNCH;
-  hipLaunchKernelGGL(kern, dim3(a.t_count), dim3(512), sh, st, a, pooled, block_idx, sc_floats);
+  hipLaunchKernelGGL(kern, dim3(a.t_count), dim3(NW * 64), sh, st, a, pooled, block_idx, sc_floats);
   return HISA_OK;
 }
 
-constexpr int kStage1QueryMaxT = 256;    // one workgroup per query: while the queries are fewer than the CUs
-constexpr int kStage1QueryMaxM = 8192;   // 512 threads x 16 blocks
-
 int launch_stage1_query(const ScoreArgs& a, const void* pooled, int M, int32_t* block_idx, hipStream_t st) {
+  if (a.t_count > kCUs)
+    return a.H == 64 ? launch_stage1_query_e<2, 4, 4>(a, pooled, M, block_idx, st)
+                     : launch_stage1_query_e<1, 4, 4>(a, pooled, M, block_idx, st);
   if (M <= 2048)
-    return a.H == 64 ? launch_stage1_query_e<2, 4>(a, pooled, M, block_idx, st)
-                     : launch_stage1_query_e<1, 4>(a, pooled, M, block_idx, st);
-  return a.H == 64 ? launch_stage1_query_e<2, 16>(a, pooled, M, block_idx, st)
-                   : launch_stage1_query_e<1, 16>(a, pooled, M, block_idx, st);
+    return a.H == 64 ? launch_stage1_query_e<2, 4, 8>(a, pooled, M, block_idx, st)
+                     : launch_stage1_query_e<1, 4, 8>(a, pooled, M, block_idx, st);
+  return a.H == 64 ? launch_stage1_query_e<2, 16, 8>(a, pooled, M, block_idx, st)
+                   : launch_stage1_query_e<1, 16, 8>(a, pooled, M, block_idx, st);
 }
 
 // Flat indexer: rows of queries scored per chunk, and the size of the segment-merge area.
@@ -585,9 +585,8 @@ int hisa_block_score_topk(const hisa_queries* queries, const hisa_keys* keys, co
     if (!ws || ws_bytes < (size_t)T * M * 4) return HISA_ERR_WORKSPACE;
     J = (float*)ws;
   }
-  if (path == PATH_MFMA && pooled_dtype == HISA_BF16 && !block_scores && T <= kStage1QueryMaxT &&
-      M <= kStage1QueryMaxM) {
-    // a decode batch: scoring and selection of a query in one workgroup, nothing through the workspace
+  if (path == PATH_MFMA && pooled_dtype == HISA_BF16 && !block_scores && stage1_one_launch(T, M, a.H)) {
+    // a small batch: scoring and selection of a query in one workgroup, nothing through the workspace
     a.B = B;
     a.m = m;
     a.t_begin = 0;

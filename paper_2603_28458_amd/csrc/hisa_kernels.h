@@ -1914,22 +1914,24 @@ __device__ __forceinline__ void stage1_in_workgroup(const QFrag<HG>& f, const Sc
 }
 
 // ------------------------------------------------------------------------------------------
-// Stage 1 (Eqs. 5-6) of a FEW queries (a decode batch), one launch: one workgroup of 8 waves per
-// query loads the query fragment, scores the pooled keys of the visible blocks into LDS and keeps m
+// Stage 1 (Eqs. 5-6) of a FEW queries (a decode batch, the tokens of a short chunk), one launch: one workgroup of NW
+// waves per query loads the query fragment, scores the pooled keys of the visible blocks into LDS and keeps m
 // of them there; only the m ids leave the CU.  Against the scoring launch plus the select launch
 // this saves a launch, the round trip of the block scores through HBM and the second query read;
-// with one workgroup per query it only pays while the queries are fewer than the CUs.
+// with one workgroup per query it pays while the queries are few (stage1_one_launch).  8 waves make a single query's
+// latency short; 4, with a ring of one tile, put two or three workgroups on a CU, whose waits cover each other, where there
+// are more queries than CUs: 512 queries of 512 blocks 12.4 (consecutive: 16.4) -> 8.9 us, 1024 of them 17.5 (19.4) -> 16.0.
 // Latency bound: launch, sequence, query and tiles, then the top-m.  The one-pass top-m (five barriers) instead of
 // the range-bracketing one (about sixteen), and the query and first tiles requested before the sequence's length
 // is known: 32 queries of 1024 blocks 10.05 -> 9.1 us, 200 of 157 8.75 -> 7.4, 77 of 1564 11.9 -> 10.8, 4 of 7812
 // 28.7 -> 28.0.  (A row that it declines, one in thousands by a tie, ends with the other select behind it: 9.5 -> 11 us.)
 // sc_floats >= the block count rounded up to 32; LDS: the tile rings, sc_floats scores, m ids
 // (rounded up to 4), HG * 8192 bytes for the query fragment.
-template <int HG, int E1, int NB>
-__global__ __launch_bounds__(512) void k_stage1_query(ScoreArgs a, const void* pooled, int32_t* block_idx_out,
-                                                      int sc_floats) {
+template <int HG, int E1, int NB, int NW>
+__global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_stage1_query(ScoreArgs a, const void* pooled,
+                                                                           int32_t* block_idx_out, int sc_floats) {
   extern __shared__ __align__(16) unsigned char smem[];
-  constexpr int NW = 8, NT = NW * 64, TILE = 8192;
+  constexpr int NT = NW * 64, TILE = 8192;
   constexpr size_t kStageBytes = (size_t)NW * NB * TILE;
   static_assert(sizeof(SelectSmem<NT, E1>) <= kStageBytes, "select scratch must fit the rings");
   float* sc = reinterpret_cast<float*>(smem + kStageBytes);

@@ -199,3 +199,43 @@ def test_stage1_of_a_small_batch_against_a_sort(M, m, kind):
         s[[0, -1]] = np.inf                      # forced
         ids, s = ids[s > -np.inf], s[s > -np.inf]
         assert np.array_equal(got[t], expected_row(s, ids, m)), t
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("T,H,M,m", [(257, 64, 512, 64), (1024, 64, 511, 500), (1025, 64, 512, 64), (300, 64, 33, 2), (700, 64, 130, 32),
+                                     (1536, 32, 512, 128), (1537, 32, 512, 64), (769, 32, 64, 63), (258, 32, 3, 2), (600, 32, 513, 64)])
+def test_stage1_in_one_launch_beyond_a_query_per_cu(T, H, M, m):
+    # edges of the rule and of the tiles, bit for bit against the route that writes its scores (two kernels): ragged
+    # sequences, queries that see nothing, all they can or a later part of a stream, ties, scores of -inf and +inf, NaN
+    from paper_2603_28458_amd import hisa
+
+    B, n = 32, 3
+    print(f"\n[stage 1, one launch] T={T} H={H} M={M} m={m}", flush=True)
+    rng = np.random.default_rng(T + M)
+    g = torch.Generator().manual_seed(T)
+    q = torch.randn((T, H, 128), generator=g).bfloat16()
+    w = torch.rand((T, H), generator=g)
+    w[::11] *= -1.0
+    pooled = torch.randn((n, M, 128), generator=g)
+    pooled[0, M // 3: M // 2] = pooled[0, M // 3].clone()           # ties
+    q[5::50, :, 0] = 3e38                                           # infinite scores
+    q[7::50, :, 1] = float("nan")
+    if M <= 512:
+        pooled[2, M // 2] = float("nan")
+    seq = rng.integers(0, n, T)
+    lens = np.array([M * B, max(1, (M * B * 3) // 4 - 5), M * B - 1])
+    pos = rng.integers(0, lens[seq])
+    pos[::13] = lens[seq[::13]] - 1
+    pos[::97] = -1
+    lo = np.where(np.arange(T) % 4 == 0, rng.integers(0, np.maximum(1, pos + 1)), 0)
+    ints = lambda x: torch.from_numpy(x.astype(np.int32)).cuda()
+    K = hisa.Keys(k=None, seq_len=ints(lens), dtype=hisa.HISA_BF16, n_seq=n, s_max=M * B, d=128)
+    P = pooled.bfloat16().cuda()
+    Q = hisa.Queries(q=q.cuda(), w=w.cuda(), dtype=hisa.HISA_BF16, q_seq=ints(seq), q_pos=ints(pos), q_lo=ints(lo))
+    K1 = hisa.Keys(k=None, seq_len=ints(lens[:1]), dtype=hisa.HISA_BF16, n_seq=1, s_max=M * B, d=128)
+    C = hisa.Queries(q=q.cuda(), w=w.cuda(), dtype=hisa.HISA_BF16, q_pos0=max(0, M * B - T))   # consecutive
+    for queries, keys, pk in ((Q, K, P), (C, K1, P[:1].contiguous())):
+        got = hisa.hisa_block_score_topk(queries, keys, pk, hisa.HISA_BF16, B, m)[0]
+        want = hisa.hisa_block_score_topk(queries, keys, pk, hisa.HISA_BF16, B, m, want_scores=True)[0]
+        bad = (got != want).any(1).nonzero().flatten()
+        assert bad.numel() == 0, (bad[:8].tolist(), got[bad[0]].tolist(), want[bad[0]].tolist())
