@@ -79,7 +79,7 @@ inline int rows_f32_waves(long T, long n_max) {
 }
 
 // Stage 1 in one launch (k_stage1_query), or scoring and select in two?  T queries of M blocks, H heads.
-// Up to a query per CU, workgroups of 8 waves, any row that their select holds.  Beyond, workgroups of 4 waves, of which a
+// Up to a query per CU, any row that the select holds.  Beyond, workgroups of 4 waves, of which a
 // CU holds two (64 heads, by registers) or three (32, by LDS); each round of them takes 6-9 us, and the two launches,
 // which are better at many queries, 9-16 us at first.  us in one launch (in two: queries with positions of their
 // own / consecutive), 512 blocks, 64 heads: 257 queries 8.4 (11.7 / 14.6), 512 8.9 (12.4 / 16.4), 640 13.5 (15.9 / 17.6), 1024

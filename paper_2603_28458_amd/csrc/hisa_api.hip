@@ -343,7 +343,7 @@ int launch_indexer(const ScoreArgs& a, const void* pooled, int k, int32_t* block
 template <int HG, int E1, int NW>
 int launch_stage1_query_e(const ScoreArgs& a, const void* pooled, int M, int32_t* block_idx, hipStream_t st) {
   const int sc_floats = (int)round_up(M, 32);
-  // 8 waves: up to 2048 blocks a ring of two tiles per wave fits beside the scores, above that a ring of one
+  // 4 waves: a ring of one; 8: up to 2048 blocks a ring of two tiles per wave fits beside the scores, above that a ring of one
   constexpr int NB = NW == 8 && E1 <= 4 ? 2 : 1;
   const size_t sh = (size_t)NW * NB * 8192 + (size_t)sc_floats * 4 + (size_t)round_up(a.m, 4) * 4 + (size_t)HG * 8192;
   constexpr auto kern = k_stage1_query<HG, E1, NB, NW>;
@@ -353,7 +353,7 @@ int launch_stage1_query_e(const ScoreArgs& a, const void* pooled, int M, int32_t
 }
 
 int launch_stage1_query(const ScoreArgs& a, const void* pooled, int M, int32_t* block_idx, hipStream_t st) {
-  if (a.t_count > kCUs)
+  if (a.t_count > kCUs || M <= 1024)   // (4 waves: k_stage1_query)
     return a.H == 64 ? launch_stage1_query_e<2, 4, 4>(a, pooled, M, block_idx, st)
                      : launch_stage1_query_e<1, 4, 4>(a, pooled, M, block_idx, st);
   if (M <= 2048)

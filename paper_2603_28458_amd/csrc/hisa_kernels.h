@@ -1918,9 +1918,11 @@ __device__ __forceinline__ void stage1_in_workgroup(const QFrag<HG>& f, const Sc
 // waves per query loads the query fragment, scores the pooled keys of the visible blocks into LDS and keeps m
 // of them there; only the m ids leave the CU.  Against the scoring launch plus the select launch
 // this saves a launch, the round trip of the block scores through HBM and the second query read;
-// with one workgroup per query it pays while the queries are few (stage1_one_launch).  8 waves make a single query's
-// latency short; 4, with a ring of one tile, put two or three workgroups on a CU, whose waits cover each other, where there
-// are more queries than CUs: 512 queries of 512 blocks 12.4 (consecutive: 16.4) -> 8.9 us, 1024 of them 17.5 (19.4) -> 16.0.
+// with one workgroup per query it pays while the queries are few (stage1_one_launch).  4 waves with a ring of one tile up
+// to 1024 blocks: their barriers, shares of the query and figures of the top-m cost less than 8 waves' ever do, and where
+// there are more queries than CUs two or three workgroups share a CU and cover each other's waits.  Against 8 waves with a
+// ring of two, 64 heads: 1 query of 512 blocks 6.9 -> 6.65 us, 32 of 1024 8.75 -> 8.3, 200 of 157 6.65 -> 6.35, 256 of 1024 9.8 -> 9.4;
+// 32 heads 0-3 %; against two launches: 512 queries of 512 blocks 12.4 (consecutive: 16.4) -> 8.9, 1024 17.5 (19.4) -> 16.0.
 // Latency bound: launch, sequence, query and tiles, then the top-m.  The one-pass top-m (five barriers) instead of
 // the range-bracketing one (about sixteen), and the query and first tiles requested before the sequence's length
 // is known: 32 queries of 1024 blocks 10.05 -> 9.1 us, 200 of 157 8.75 -> 7.4, 77 of 1564 11.9 -> 10.8, 4 of 7812

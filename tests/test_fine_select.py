@@ -158,7 +158,7 @@ def test_stage1_on_scores_a_few_ulps_apart(spread):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("kind", ["random", "tied", "negative", "nan"])
-@pytest.mark.parametrize("M,m", [(40, 3), (70, 69), (300, 126), (512, 2), (2048, 64), (2049, 128), (8192, 1000)])
+@pytest.mark.parametrize("M,m", [(40, 3), (70, 69), (300, 126), (512, 2), (1024, 100), (1025, 7), (2048, 64), (2049, 128), (8192, 1000)])
 def test_stage1_of_a_small_batch_against_a_sort(M, m, kind):
     # the one-launch Stage 1: queries that see from m + 1 blocks to all of them, some from the middle of a stream on.
     # tied: crowded bins and ties across the threshold, declined.  negative: scores of -inf, which are no candidates.
