@@ -355,12 +355,12 @@ def bench_config(name, steps, warmup, flat_steps, torch, hisa, W, with_flat=True
     if wl.q_dtype == "f32":
         # the small fp32 configuration runs on the plain vector ALU; at this size it is bound by launch latency
         roof = {"bound": "alu", "achieved": p2 * flop_pair / (ms_s2 * 1e-3) / 1e12, "peak": PEAK_FP32_ALU_TFLOPS,
-                "unit": "TFLOP/s", "kernel": "k_score_ranges_f32 + k_select",
+                "unit": "TFLOP/s", "kernel": "k_rows_f32",
                 "note": "launch-latency bound at this size: three launches of a few microseconds each"}
     elif decode:
         # every candidate key is read once: the whole step (both stages, three launches) against the HBM peak
         roof = {"bound": "hbm", "achieved": hbm_bytes / (ms_step * 1e-3) / 1e9, "peak": PEAK_HBM_GBS, "unit": "GB/s",
-                "kernel": "whole step: k_stage1_query (Stage 1), k_score_ranges + k_select (Stage 2)",
+                "kernel": "whole step: k_stage1_query (Stage 1), k_score_gather + k_select (Stage 2)",
                 "stage2_scoring_and_select_GBs": (p2 * kbytes + T * (qbytes + wl.m * 4 + wl.k * 4) + 2 * p2 * 4)
                 / (ms_s2 * 1e-3) / 1e9}
     else:
@@ -368,7 +368,7 @@ def bench_config(name, steps, warmup, flat_steps, torch, hisa, W, with_flat=True
         # the sum of two e4m3 numbers): `achieved` stays the algorithmic rate, `peak` is that pipe's
         roof = {"bound": "mfma", "achieved": p2 * flop_pair / (ms_s2 * 1e-3) / 1e12,
                 "peak": PEAK_FP8_TFLOPS if fp8 else PEAK_BF16_TFLOPS,
-                "unit": "TFLOP/s", "kernel": "k_refine_fused" if fused else "k_score_ranges + k_select",
+                "unit": "TFLOP/s", "kernel": "k_refine_fused" if fused else "k_score_gather + k_select",
                 "mfma": "fp8 e4m3 x e4m3, 2 executed flop per algorithmic flop" if fp8 else "bf16"}
     roof["frac"] = roof["achieved"] / roof["peak"]
     roof["ms_per_launch"] = ms_step if decode else ms_s2
