@@ -5,6 +5,7 @@
 #include <type_traits>
 
 #include "hisa_device.h"
+#include "tile_walk.h"
 
 
 namespace hisa {
@@ -2115,9 +2116,8 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_refine_fused(Score
   int j0 = 0;
   if (E1 == 0 && a.walk != 0u && nj > 0 && (nj & 1) == 0)   // (pairs of tiles are finished together: an odd walk starts at 0)
     j0 = (int)(((uint32_t)__builtin_amdgcn_s_memrealtime() / a.walk) % ((uint32_t)nj >> 1)) * 2;
-  auto walked = [&](int j) { return j + j0 < nj ? j + j0 : j + j0 - nj; };
-  rows.lo = row_of(wave + NW * (lane < nj ? walked(lane) : 0));
-  rows.hi = (E > 32 && nj > 64) ? row_of(wave + NW * (lane + 64 < nj ? walked(lane + 64) : 0)) : -1;
+  rows.lo = row_of(walk_tile(lane, nj, j0, wave, NW));
+  rows.hi = (E > 32 && nj > 64) ? row_of(walk_tile(lane + 64, nj, j0, wave, NW)) : -1;
   __amdgpu_buffer_rsrc_t krsrc, srsrc;
   key_buffers<KDT>(a, seq, krsrc, srsrc);
   auto row_at = [&](int j) {
@@ -2155,7 +2155,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_refine_fused(Score
     // from +0, so it is never -0.  Visible: lo <= row < n_vis, i.e. unsigned(row - lo) < n_vis - lo
     // (nothing, for a tile without a kept block).
     if (r < 0 || (uint32_t)(r + lane_lo) >= span) s = __uint_as_float(kNoCandidateBits);
-    const uint32_t addr = sc_lane + (uint32_t)(NW * 128) * (uint32_t)walked(j);
+    const uint32_t addr = sc_lane + (uint32_t)(NW * 128) * (uint32_t)walk_place(j, nj, j0);
     if (both || lane < 32) asm volatile("ds_write_b32 %0, %1" : : "v"(addr), "v"(s) : "memory");
     s_max = vmax_f32(s_max, s);
     s_min = vmin_f32(s_min, s);

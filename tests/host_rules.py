@@ -1,5 +1,5 @@
-"""The library's dispatch rules (csrc/dispatch_rules.h), compiled for the host: a test that sits where a rule
-changes its answer asks the rule itself."""
+"""The library's dispatch rules (csrc/dispatch_rules.h) and the walk of a wave over its tiles (csrc/tile_walk.h), compiled
+for the host: a test that sits where a rule changes its answer asks the rule itself."""
 import ctypes
 import functools
 import os
@@ -10,10 +10,14 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 
 _SHIM = """
 #include "dispatch_rules.h"
+#include "tile_walk.h"
 extern "C" int in_ring(long T, long s_max, long packed, long fp8, long without, long with) {
   return hisa::hist_in_ring(T, s_max, packed, fp8, without, with);
 }
 extern "C" int key_ranges(long q_groups, long first, long last) { return hisa::prefill_split(q_groups, first, last); }
+extern "C" int tile_of_walk(long j, long nj, long j0, long wave, long n_waves) {
+  return hisa::walk_tile(j, nj, j0, wave, n_waves);
+}
 extern "C" int tiles_per_wave(long T, long n_tiles) { return hisa::gather_tiles_per_wave(T, n_tiles); }
 """
 
@@ -44,3 +48,7 @@ def in_ring(T, s_max, packed, fp8, without, with_):
 
 def key_ranges(T, rows_first, rows_last):
     return _call("key_ranges", -(-T // 8), rows_first, rows_last)
+
+
+def tile_of_walk(j, nj, j0, wave, n_waves):
+    return _call("tile_of_walk", j, nj, j0, wave, n_waves)

@@ -1,5 +1,5 @@
 """The rules that cut a launch into workgroups, over the sizes they are asked for."""
-from tests.host_rules import in_ring, key_ranges, tiles_per_wave
+from tests.host_rules import in_ring, key_ranges, tile_of_walk, tiles_per_wave
 
 
 def _cost(T, n_tiles, tpw):
@@ -50,3 +50,16 @@ def test_key_ranges_of_the_prefill_scoring_kernel():
     assert key_ranges(3000, 1, 3000) == 1                        # a triangle: the short queries fill the second round
     # what is seen counts, not the array's length: 300 pooled keys, whatever the cache was made for
     assert key_ranges(1500, 253, 300) == 1
+
+
+def test_walks_cover_a_waves_tiles_and_stay_in_the_block_list():
+    # the fused Stage 2: every lane of every wave looks a tile up in the query's m block ids, also lanes and waves without one
+    for n_waves, m, per_block in ((4, 2, 1), (4, 3, 1), (4, 2, 2), (4, 5, 1), (4, 7, 4), (8, 2, 1), (8, 3, 2), (8, 257, 1), (4, 64, 4)):
+        for used in sorted({0, 1, m - 1, m}):
+            tiles = used * per_block
+            for wave in range(n_waves):
+                nj = max(0, -(-(tiles - wave) // n_waves))
+                for j0 in sorted({0, nj // 2 // 2 * 2, max(0, nj - 2)} if nj % 2 == 0 else {0}):
+                    at = [tile_of_walk(j, nj, j0, wave, n_waves) for j in range(max(64, nj))]
+                    assert all(0 <= v < m * per_block for v in at), (n_waves, m, per_block, used, wave, at)
+                    assert sorted(at[:nj]) == list(range(wave, tiles, n_waves)), (n_waves, m, used, wave)
