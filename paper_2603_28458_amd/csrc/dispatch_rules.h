@@ -78,6 +78,33 @@ inline int rows_f32_waves(long T, long n_max) {
   return nw == 8 && T > 768 ? 4 : nw;
 }
 
+// fp32 rows of at most 512 candidates: scored and selected in one launch (k_rows_f32), or in two (k_score_ranges_f32 and
+// the select)?  T queries, n_max candidates, H heads of d elements.  In one launch a launch is saved and the key rows come
+// in whole pieces of 128 bytes, 4 heads at a time; but a wave takes such a step (4 heads, 8 chunks of 16 bytes) in 1 us
+// however few of the 8 chunks a row has, 64 candidates have one wave, and a workgroup keeps 9 KB of LDS per wave until its
+// first wave has selected.  In two, a row is cut over all CUs and costs d / 4 shorter steps, heads beyond a multiple of four
+// one at a time.  Both are priced, in us: launches, the longest chain of one workgroup (a second round of workgroups
+// follows two thirds of a first one later) and what all of them take from a CU.  The prices hold to a few percent for a few heads
+// of whole pieces and to 10-20 % elsewhere, where one launch has to be 10 % better.  us in one launch (in two): 1024 queries of 256, 4
+// heads of 64: 13.4 (17.3); 700 of 512, 4 of 64: 18.3 (21.4); 3000 of 512, 4 of 4: 28 (17.4); 6000 of 32, 128 of 16: 485 (64);
+// 1024 of 64, 64 of 128: 122 (77); 2048 of 512, 16 of 128: 135 (237), 3 of 512: 182 (1488); 100 of 512, 128 of 32: 45 (66).
+// Over 45768 calls (1 to 16000 queries, 20 to 512 candidates, 1 to 128 heads of 4 to 512, both stages) the rule is 1.8 %
+// from the better one on average; what it takes in one launch is at most 5 % slower there in 95 of 100 calls and 16 % in 99
+// (everything in one launch: up to 7.6 times slower).
+inline bool rows_f32_one_launch(long T, long n_max, int H, int d) {
+  const int pieces = d / 4, whole = pieces / 8, rest = pieces % 8;
+  const double four_heads = whole + (rest ? 0.6 + 0.1 * rest : 0.0);
+  const double fewer_heads = 0.6 * ((pieces + 7) / 8) + 0.1 * pieces;
+  const double step = H / 4 * four_heads + (H % 4 ? fewer_heads : 0.0);
+  const long waves = rows_f32_waves(T, n_max), tasks = (n_max + 63) / 64, passes = (tasks + waves - 1) / waves;
+  const long rounds = (T * waves + 16 * kCUs - 1) / (16 * kCUs);   // 16 waves' LDS on a CU
+  const double one = (passes * step + 7.5) * (1.0 + 0.67 * (rounds - 1)) + T * tasks * step / 3000.0;
+  const double row = pieces * (H / 4 * 0.065 + H % 4 * 0.095);
+  const double two = 9.0 + row * ((n_max + 255) / 256 + T * tasks / 1400.0) + 0.0012 * T +
+                     7e-7 * T * n_max * ((H + 3) / 4) * pieces;
+  return one < (rest == 0 && H * d <= 1024 ? 1.05 : 0.9) * two;
+}
+
 // Stage 1 in one launch (k_stage1_query), or scoring and select in two?  T queries of M blocks, H heads.
 // Up to a query per CU, any row that the select holds.  Beyond, workgroups of 4 waves, of which a
 // CU holds two (64 heads, by registers) or three (32, by LDS); each round of them takes 6-9 us, and the two launches,

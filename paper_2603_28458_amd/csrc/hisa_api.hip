@@ -605,7 +605,7 @@ int hisa_block_score_topk(const hisa_queries* queries, const hisa_keys* keys, co
   a.t_count = T;
   // a query that sees at most m blocks keeps them all: its block scores are only computed if asked for
   a.whole_rows = block_scores ? -1 : m;
-  if (path == PATH_F32 && !block_scores && M <= kRowsF32Max) {
+  if (path == PATH_F32 && !block_scores && M <= kRowsF32Max && rows_f32_one_launch(T, M, a.H, a.d)) {
     launch_rows_f32<false>(a, M, m, block_idx, nullptr, s);
     return launch_status();
   }
@@ -711,7 +711,7 @@ static int token_refine_impl(const hisa_queries* queries, const hisa_keys* keys,
     if (!ws || ws_bytes < (size_t)T * n_slots * 4) return HISA_ERR_WORKSPACE;
     C = (float*)ws;
   }
-  if (path == PATH_F32 && !cand_scores && n_slots <= kRowsF32Max) {
+  if (path == PATH_F32 && !cand_scores && n_slots <= kRowsF32Max && rows_f32_one_launch(T, n_slots, a.H, a.d)) {
     launch_rows_f32<true>(a, n_slots, k, topk_idx, topk_scores, s);
     return launch_status();
   }

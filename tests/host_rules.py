@@ -18,6 +18,8 @@ extern "C" int key_ranges(long q_groups, long first, long last) { return hisa::p
 extern "C" int tile_of_walk(long j, long nj, long j0, long wave, long n_waves) {
   return hisa::walk_tile(j, nj, j0, wave, n_waves);
 }
+extern "C" int f32_one_launch(long T, long n, long H, long d) { return hisa::rows_f32_one_launch(T, n, H, d); }
+extern "C" int f32_waves(long T, long n) { return hisa::rows_f32_waves(T, n); }
 extern "C" int tiles_per_wave(long T, long n_tiles) { return hisa::gather_tiles_per_wave(T, n_tiles); }
 """
 
@@ -52,3 +54,11 @@ def key_ranges(T, rows_first, rows_last):
 
 def tile_of_walk(j, nj, j0, wave, n_waves):
     return _call("tile_of_walk", j, nj, j0, wave, n_waves)
+
+
+def f32_one_launch(T, n, H, d):
+    return bool(_call("f32_one_launch", T, n, H, d))
+
+
+def f32_waves(T, n):
+    return _call("f32_waves", T, n)

@@ -1,5 +1,5 @@
 """The rules that cut a launch into workgroups, over the sizes they are asked for."""
-from tests.host_rules import in_ring, key_ranges, tile_of_walk, tiles_per_wave
+from tests.host_rules import f32_one_launch, f32_waves, in_ring, key_ranges, tile_of_walk, tiles_per_wave
 
 
 def _cost(T, n_tiles, tpw):
@@ -63,3 +63,27 @@ def test_walks_cover_a_waves_tiles_and_stay_in_the_block_list():
                     at = [tile_of_walk(j, nj, j0, wave, n_waves) for j in range(max(64, nj))]
                     assert all(0 <= v < m * per_block for v in at), (n_waves, m, per_block, used, wave, at)
                     assert sorted(at[:nj]) == list(range(wave, tiles, n_waves)), (n_waves, m, used, wave)
+
+
+def test_fp32_rows_in_one_launch_only_where_it_is_the_faster():
+    # (queries, candidates, heads, d), us in two launches, us in one
+    measured = [
+        ((1024, 256, 4, 64), 17.3, 13.4), ((1024, 512, 4, 64), 25.9, 18.6), ((700, 512, 4, 64), 21.4, 18.3), ((256, 32, 4, 64), 10.9, 9.9),
+        ((4096, 48, 8, 4), 16.3, 11.4), ((4096, 65, 2, 16), 18.0, 12.9), ((16000, 64, 3, 20), 41.3, 29.4), ((256, 257, 64, 32), 37.2, 26.0),
+        ((700, 256, 3, 64), 28.0, 14.0), ((16000, 64, 6, 64), 108.7, 60.0), ((2048, 65, 3, 96), 32.6, 16.4), ((6000, 256, 3, 96), 356.2, 63.0),
+        ((1024, 512, 16, 96), 99.4, 60.6), ((4096, 48, 8, 128), 36.6, 24.8), ((512, 320, 8, 128), 29.9, 20.7),
+        ((2048, 512, 16, 128), 237.3, 134.5), ((4096, 400, 12, 128), 285.3, 191.9), ((300, 400, 8, 256), 56.8, 35.9), ((3000, 512, 4, 512), 353.9, 201.6),
+        ((400, 320, 9, 512), 125.5, 72.7), ((2048, 512, 3, 512), 1488.0, 182.4), ((100, 512, 128, 32), 66.0, 45.4),
+        ((2048, 48, 128, 4), 22.0, 37.8), ((3000, 512, 4, 4), 17.4, 27.8), ((768, 512, 32, 8), 17.9, 31.3), ((16000, 192, 5, 12), 51.2, 83.5),
+        ((16000, 512, 24, 12), 147.7, 374.1), ((2048, 192, 8, 16), 14.6, 20.8), ((6000, 512, 8, 16), 39.2, 78.1), ((1, 64, 64, 16), 13.3, 28.5),
+        ((100, 20, 128, 16), 25.0, 52.8), ((6000, 32, 128, 16), 63.7, 485.0), ((512, 129, 32, 20), 14.4, 21.3), ((400, 64, 24, 24), 12.8, 18.4),
+        ((600, 128, 24, 28), 15.7, 21.9), ((300, 129, 128, 36), 37.9, 66.6), ((4096, 65, 32, 48), 53.2, 101.2), ((3000, 128, 128, 48), 174.5, 522.7),
+        ((600, 20, 128, 64), 52.3, 82.9), ((100, 192, 128, 96), 80.5, 120.1), ((1024, 64, 64, 128), 77.2, 121.7), ((700, 64, 24, 256), 44.7, 61.0),
+        ((2048, 32, 9, 512), 67.2, 100.6), ((700, 96, 24, 512), 125.7, 185.2)]
+    for call, two, one in measured:
+        assert f32_one_launch(*call) == (one < two), call
+    assert not f32_one_launch(1, 64, 128, 4) and f32_one_launch(1 << 22, 512, 4, 64)     # the ends of what a call may hold
+    for T in (1, 63, 768, 769, 2048, 2049, 1 << 22):
+        for n in (1, 63, 64, 65, 128, 129, 256, 257, 512):
+            waves = f32_waves(T, n)
+            assert waves in (1, 2, 4, 8) and (waves == 1 or 64 * waves // 2 < n), (T, n, waves)   # no wave without a candidate of its own
