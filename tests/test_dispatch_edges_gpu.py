@@ -308,6 +308,48 @@ def test_fp32_rows_in_one_launch(T, H, d, B, m, k):
     assert torch.equal(ids, want) and torch.equal(sc, want_sc)
 
 
+@pytest.mark.parametrize("T,H,d,M,m,B", [
+    (300, 4, 64, 255, 15, 17), (700, 3, 64, 256, 16, 16), (300, 4, 96, 257, 257, 1), (900, 8, 64, 512, 8, 64), (520, 4, 128, 511, 7, 73),
+    (300, 1, 64, 64, 8, 8), (2100, 2, 32, 65, 13, 5), (700, 4, 64, 129, 3, 43), (300, 2, 36, 200, 10, 20), (300, 7, 96, 400, 10, 40),
+    (700, 3, 132, 100, 5, 20)])
+def test_fp32_rows_in_one_launch_with_scores_that_are_no_numbers(T, H, d, M, m, B):
+    # rows of M blocks and m * B candidates at the edges of the instances, all in one launch; NaN and infinite scores, -inf
+    # (dropped), several sequences, queries that see nothing, part of a block or a later part of a stream: bit for bit as in two
+    import torch
+    from paper_2603_28458_amd import hisa
+    from tests.host_rules import f32_one_launch
+
+    assert f32_one_launch(T, M, H, d) and f32_one_launch(T, m * B, H, d)
+    print(f"\n[fp32 rows, specials] T={T} H={H} d={d} M={M} m={m} B={B}", flush=True)
+    rng = np.random.default_rng(T + M)
+    g = torch.Generator().manual_seed(T)
+    n, L, k = 3, M * B, max(1, m * B // 2)
+    q, w, keys = torch.randn((T, H, d), generator=g), torch.rand((T, H), generator=g), torch.randn((n, L, d), generator=g)
+    w[::5] *= -1.0
+    q[3::20, :, 0] = 3e38
+    q[4::20, 0, 1] = float("nan")
+    w[6::20, 0] = float("inf")
+    keys[0, L // 2:: 7, 2], keys[1, L // 3, 0], keys[2, ::3] = float("nan"), float("inf"), keys[2, 0].clone()      # the last: ties
+    pooled = torch.randn((n, M, d), generator=g)
+    pooled[0, M // 2], pooled[1, M // 3, 0], pooled[2, M // 4: M // 2] = float("nan"), float("inf"), pooled[2, 0].clone()
+    lens = np.array([L, max(1, (3 * L) // 4), L - 1])
+    seq = rng.integers(0, n, T)
+    pos = rng.integers(0, lens[seq])
+    pos[::13] = lens[seq[::13]] - 1
+    pos[::97] = -1
+    lo = np.where(np.arange(T) % 4 == 0, rng.integers(0, np.maximum(1, pos + 1)), 0)
+    ints = lambda x: torch.from_numpy(x.astype(np.int32)).cuda()
+    Q = hisa.Queries(q=q.cuda(), w=w.cuda(), dtype=hisa.HISA_F32, q_seq=ints(seq), q_pos=ints(pos), q_lo=ints(lo))
+    K = hisa.Keys(k=keys.cuda(), seq_len=ints(lens), dtype=hisa.HISA_F32)
+    P = pooled.cuda()
+    blocks = hisa.hisa_block_score_topk(Q, K, P, hisa.HISA_F32, B, m)[0]
+    assert torch.equal(blocks, hisa.hisa_block_score_topk(Q, K, P, hisa.HISA_F32, B, m, want_scores=True)[0])
+    ids, sc = hisa.hisa_token_refine_topk(Q, K, B, m, blocks, k, want_topk_scores=True)[:2]
+    want, want_sc = hisa.hisa_token_refine_topk(Q, K, B, m, blocks, k, want_topk_scores=True, want_cand_scores=True)[:2]
+    assert torch.equal(ids, want) and torch.equal(sc.view(torch.int32), want_sc.view(torch.int32))
+    assert torch.equal(hisa.hisa_token_refine_topk(Q, K, B, m, blocks, k)[0], want)
+
+
 @pytest.mark.parametrize("k_dtype,H,L,B,m,k", [
     ("bf16", 64, 16500, 32, 200, 700), ("bf16", 64, 17000, 32, 133, 500), ("bf16", 32, 16400, 32, 128, 512), ("bf16", 32, 20000, 64, 120, 900),
     ("fp8_e4m3", 64, 33000, 32, 256, 1000), ("fp8_e4m3", 32, 33000, 32, 100, 400), ("fp8_e4m3", 64, 34000, 128, 128, 2000),
