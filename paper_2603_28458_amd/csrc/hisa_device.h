@@ -797,6 +797,22 @@ __device__ __forceinline__ int score_slot(int c) {
   return (c & ~31) | ((((c >> 2) ^ (c >> 5)) & 7) << 2) | (c & 3);
 }
 
+// What the lanes of a wave wrote to LDS before this is what all of its lanes read behind it.  LDS serves a wave's
+// accesses in order, so it costs no instruction: it keeps the compiler from moving accesses that it believes to be
+// independent, thread by thread, past each other.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The barrier of a group of THREADS threads: a workgroup, or a single wave, whatever the other waves of its workgroup do.
+template <int THREADS>
+__device__ __forceinline__ void group_sync() {
+  if constexpr (THREADS == 64) wave_lds_order();
+  else __syncthreads();
+}
+
 template <int THREADS, int E>
 struct SelectSmem {
   static constexpr int NW = THREADS / 64;
@@ -838,7 +854,8 @@ __device__ __forceinline__ void find_bin(const uint32_t* hist, uint32_t* bcast, 
   }
 }
 
-// Exact top-k of one row by one workgroup of THREADS threads, n <= THREADS * E elements.
+// Exact top-k of one row by one workgroup of THREADS threads (64: by the first wave of a workgroup of any size), n <=
+// THREADS * E elements.
 //   load4(q) -> keys of elements 4q .. 4q+3 (0: not a candidate); load1(i) -> key of element i.
 //   Thread t holds the E consecutive elements t*E .. t*E+E-1 in registers.
 //   emit(pos, i, key): element i is the pos-th selected, in ascending i.
@@ -855,7 +872,7 @@ __device__ __forceinline__ void find_bin(const uint32_t* hist, uint32_t* bcast, 
 // (if it overflows the list -- many equal keys -- they keep running over the registers); a pass
 // whose bin is taken whole ends the search.  Positions come from one workgroup scan of
 // per-thread counts: output is ascending, ties go to the lower index.
-// Every thread of the workgroup must call it (it contains workgroup barriers).
+// All THREADS threads must call it: with more than 64 it contains workgroup barriers.
 // SAFE: load4(q) may be called for any q < THREADS * E / 4 (it returns anything beyond n); the
 // loads of a thread are then issued back to back instead of one per guarded branch.
 // FORCED: keys equal to 0xffffffff may occur (callers that force rows to the top); without it the
@@ -925,7 +942,7 @@ __device__ __forceinline__ int select_topk(SelectSmem<THREADS, E>& sm, int n, in
     sm.red[4 * NW + wave] = k_max;
   }
   if (tid == 0) sm.n_list = 0u;
-  __syncthreads();
+  group_sync<THREADS>();
   cnt = 0;
   n_top = 0;
   lo_est = 0u;
@@ -955,9 +972,9 @@ __device__ __forceinline__ int select_topk(SelectSmem<THREADS, E>& sm, int n, in
     while (true) {
       const uint32_t width = hi - lo;
       const int s = width ? (32 - __builtin_clz(width) > 8 ? 32 - __builtin_clz(width) - 8 : 0) : 0;
-      __syncthreads();   // list complete / previous result read by everyone
+      group_sync<THREADS>();   // list complete / previous result read by everyone
       for (int b = tid; b < 256; b += THREADS) sm.hist[b] = 0u;
-      __syncthreads();
+      group_sync<THREADS>();
       if (on_list) {
         for (uint32_t p = tid; p < n_listed; p += THREADS) {
           const uint32_t dk = load1((int)sm.list[p]) - lo;   // keys below lo (and 0) wrap far above width
@@ -970,9 +987,9 @@ __device__ __forceinline__ int select_topk(SelectSmem<THREADS, E>& sm, int n, in
           if (dk <= width) atomicAdd(&sm.hist[dk >> s], 1u);
         }
       }
-      __syncthreads();
+      group_sync<THREADS>();
       if (wave == 0) find_bin(sm.hist, sm.bcast, krem, lane);
-      __syncthreads();
+      group_sync<THREADS>();
       const uint32_t D = sm.bcast[0];
       krem = sm.bcast[1];
       const uint32_t n_c = sm.bcast[2];
@@ -1015,9 +1032,9 @@ __device__ __forceinline__ int select_topk(SelectSmem<THREADS, E>& sm, int n, in
 #pragma unroll
     for (int j = 0; j < E; ++j) g_cnt += key[j] > tau;
     const uint32_t g_inc = wave_scan_add(g_cnt);
-    __syncthreads();   // sm.red is free again
+    group_sync<THREADS>();   // sm.red is free again
     if (lane == 63) sm.red[wave] = g_inc;
-    __syncthreads();
+    group_sync<THREADS>();
     uint32_t g_run = g_inc - g_cnt;
 #pragma unroll
     for (int v = 0; v < NW; ++v)
@@ -1038,12 +1055,12 @@ __device__ __forceinline__ int select_topk(SelectSmem<THREADS, E>& sm, int n, in
     e_cnt += key[j] == tau;   // (r > 0 implies tau != 0)
   }
   const uint32_t g_inc = wave_scan_add(g_cnt), e_inc = wave_scan_add(e_cnt);
-  __syncthreads();   // sm.red is free again
+  group_sync<THREADS>();   // sm.red is free again
   if (lane == 63) {
     sm.red[wave] = g_inc;
     sm.red[NW + wave] = e_inc;
   }
-  __syncthreads();
+  group_sync<THREADS>();
   uint32_t g_run = g_inc - g_cnt, e_run = e_inc - e_cnt;
 #pragma unroll
   for (int v = 0; v < NW; ++v) {

@@ -353,7 +353,8 @@ __global__ __launch_bounds__(256) void k_index_iou(const int32_t* __restrict__ a
     if (y < 0 && i < first_b) first_b = i;
   }
   const int na = k - (int)wave_max((uint32_t)(k - first_a)), nb = k - (int)wave_max((uint32_t)(k - first_b));   // wave minima
-  const int32_t* rb = STAGED ? sb : pb;   // (a wave reads only what it wrote itself: no barrier)
+  if (STAGED) wave_lds_order();           // (a wave reads only what it wrote itself: no barrier)
+  const int32_t* rb = STAGED ? sb : pb;
   int inter = 0;
   for (int i = lane; i < na; i += 64) {
     const int x = pa[i];
@@ -1309,7 +1310,7 @@ __global__ __launch_bounds__(THREADS) void k_select(SelectArgs a) {
 // ------------------------------------------------------------------------------------------
 // Eqs. 5-6 / 7-9 on the plain fp32 ALU in one launch, for rows of at most 64 * E candidates (blocks, or GATHER: the
 // tokens of the kept blocks): one workgroup of NW waves scores a query's row into LDS, then its first wave selects k there (the
-// other three end; what is left of the workgroup's barriers costs one wave nothing).
+// others end).
 // Latency bound, and before that bound by the key rows' addresses: one key per thread read straight from memory
 // touches 64 lines per load.  Here a wave brings its 64 keys in pieces of 128 bytes, 8 lanes to a key, and
 // turns them through LDS (row pitch of 9 16-byte chunks: reads and writes free of conflicts); queries and gates are
@@ -1395,7 +1396,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 4) void k_rows_f32(ScoreArgs
           for (int u = 0; u < 8; ++u)
             *reinterpret_cast<u32x4v*>(&mine[(8 * u + (lane >> 3)) * PITCH + (lane & 7)]) = piece[u];
           if (i0 + 8 < dq) request(i0 + 8);
-          // (a wave reads what it wrote itself: in order, no barrier)
+          wave_lds_order();   // (a wave turns its own pieces: no barrier)
           auto chunk = [&](int x) {
             const float4 kv = mine[lane * PITCH + x];
 #pragma unroll
@@ -1415,6 +1416,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 4) void k_rows_f32(ScoreArgs
           } else {
             for (int x = 0; x < dq - i0 && x < 8; ++x) chunk(x);
           }
+          wave_lds_order();   // (read before the next pieces overwrite them)
         }
 #pragma unroll
         for (int h = 0; h < HB; ++h) {
