@@ -1102,6 +1102,10 @@ __device__ __forceinline__ int select_topk(SelectSmem<THREADS, E>& sm, int n, in
 //                            selected elements are those with v[j] >= tau, the first of them is the
 //                            pos-th selected of the row (ascending element index); dump is an LDS
 //                            word of the thread's own that may be overwritten.
+//                            emit_tied, if given: taken instead where scores equal to tau lie on both sides of the
+//                            threshold (otherwise declined; a crowded bin is not, if it holds one score only):
+//                            emit_tied(above, equal, r, v, tau): all of v[j] > tau are selected and, of the scores equal to tau, the first r of the row; `above` and `equal` of
+//                            them lie in front of this thread's.
 template <int NT, int E>
 struct FineSelSmem {
   static constexpr int NBIN = NT <= 512 ? 2048 : 4 * NT, LCAP = 64, NW = NT / 64;   // >= 4 bins per thread
@@ -1155,9 +1159,9 @@ __device__ __forceinline__ void fine_select_range(FineSelSmem<NT, E>& sm, float 
   }
 }
 
-template <int NT, int E, class Vals, class Emit>
+template <int NT, int E, class Vals, class Emit, class EmitTied = std::nullptr_t>
 __device__ __forceinline__ bool select_topk_fine(FineSelSmem<NT, E>& sm, uint32_t* hist, int n, int k, Vals vals,
-                                                 Emit emit) {
+                                                 Emit emit, EmitTied emit_tied = nullptr) {
   static_assert(E % 4 == 0, "elements per thread come in groups of four");
   using S = FineSelSmem<NT, E>;
   constexpr int NW = S::NW, NBIN = S::NBIN, BPT = NBIN / NT;
@@ -1167,6 +1171,7 @@ __device__ __forceinline__ bool select_topk_fine(FineSelSmem<NT, E>& sm, uint32_
   // waves per SIMD are bound by them: 8192 candidates 7.0 -> 5.9 us).
   constexpr bool kByLane = NW > 4;
   static_assert(NW <= 16 && (NW & (NW - 1)) == 0, "the waves of a row fill 16 lanes evenly");
+  constexpr bool kTied = !std::is_same<EmitTied, std::nullptr_t>::value;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int i0 = tid * E;
   const float qnan = __uint_as_float(0xffffffffu);
@@ -1301,7 +1306,7 @@ __device__ __forceinline__ bool select_topk_fine(FineSelSmem<NT, E>& sm, uint32_
   const uint32_t D = (uint32_t)__builtin_amdgcn_readlane((int)f_bin, src);
   const uint32_t krem = (uint32_t)__builtin_amdgcn_readlane((int)f_rem, src);
   const uint32_t n_c = (uint32_t)__builtin_amdgcn_readlane((int)f_cnt, src);
-  if (D == hist_base || n_c > (uint32_t)S::LCAP) return false;  // the k-th among the masked entries, or a crowded bin
+  if (D == hist_base || (!kTied && n_c > (uint32_t)S::LCAP)) return false;  // the k-th among the masked entries, or a crowded bin
   // ---- the scores of that bin (a handful in the whole row): eight compares at a time are OR-ed in
   // scalar registers, and only a wave that holds one of them walks those eight elements
   constexpr int G = E >= 8 ? 8 : 4;
@@ -1323,17 +1328,23 @@ __device__ __forceinline__ bool select_topk_fine(FineSelSmem<NT, E>& sm, uint32_
   __syncthreads();                                             // 3: list complete
   // their krem-th largest is the threshold: every wave ranks the list for itself (lane j takes
   // entry j, the others are handed round from lane to lane)
-  const float x = lane < (int)n_c ? sm.list_v[lane] : qnan;
-  uint32_t gt = 0, ge = 0;
-  for (uint32_t i = 0; i < n_c; ++i) {
-    const float y = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), (int)i));
-    gt += y > x;
-    ge += y >= x;
+  const uint32_t n_l = n_c < (uint32_t)S::LCAP ? n_c : (uint32_t)S::LCAP;
+  const float x = lane < (int)n_l ? sm.list_v[lane] : qnan;
+  float tau = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), 0));
+  // (copies of one score need no ranking; whether a crowded bin holds nothing else is checked below)
+  if (!kTied || __ballot(lane < (int)n_l && x != tau) != 0ull) {
+    if (n_c > (uint32_t)S::LCAP) return false;
+    uint32_t gt = 0, ge = 0;
+    for (uint32_t i = 0; i < n_c; ++i) {
+      const float y = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), (int)i));
+      gt += y > x;
+      ge += y >= x;
+    }
+    const bool is_kth = lane < (int)n_c && gt < krem && krem <= ge;
+    const uint64_t who = __ballot(is_kth);
+    if (who == 0ull) return false;
+    tau = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), __builtin_ctzll(who)));
   }
-  const bool is_kth = lane < (int)n_c && gt < krem && krem <= ge;
-  const uint64_t who = __ballot(is_kth);
-  if (who == 0ull) return false;
-  const float tau = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), __builtin_ctzll(who)));
   // ---- exactly k scores at or above tau?  (the check that makes the result exact)
   uint32_t cnt = 0;
 #pragma unroll
@@ -1356,7 +1367,31 @@ __device__ __forceinline__ bool select_topk_fine(FineSelSmem<NT, E>& sm, uint32_
       if (w < wave) pos += tw;
     }
   }
-  if (taken != (uint32_t)k) return false;                      // ties across the threshold: not this path's case
+  if (taken != (uint32_t)k) {                                  // ties across the threshold
+    if constexpr (!kTied) {
+      return false;
+    } else {
+      // scores above tau in the low half, at tau in the high half (at most NT * E of either)
+      static_assert(NT * E < 65536, "both counts fit a word");
+      uint32_t both = 0;
+#pragma unroll
+      for (int j = 0; j < E; ++j) both += v[j] > tau ? 1u : v[j] == tau ? 0x10000u : 0u;
+      const uint32_t b_incl = wave_scan_add(both);
+      if (lane == 63) sm.tot_a[wave] = b_incl;                 // (last read in front of barrier 3)
+      __syncthreads();                                         // 5: both counts visible
+      uint32_t before = b_incl - both, all = 0;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const uint32_t tw = sm.tot_a[w];
+        all += tw;
+        if (w < wave) before += tw;
+      }
+      const uint32_t above = all & 0xffffu;
+      if (above >= (uint32_t)k || above + (all >> 16) < (uint32_t)k) return false;   // (tau is not the k-th: a crowded bin held others)
+      emit_tied(before & 0xffffu, before >> 16, (uint32_t)k - above, v, tau);
+      return true;
+    }
+  }
   emit(pos, v, tau, reinterpret_cast<int32_t*>(&hist[tid]));
   return true;
 }

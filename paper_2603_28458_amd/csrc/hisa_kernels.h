@@ -1888,7 +1888,17 @@ __device__ __forceinline__ void stage1_in_workgroup(const QFrag<HG>& f, const Sc
           if (v[j] >= tau) blk_lds[p++] = (int)threadIdx.x * E1 + j;
         }
       };
-      if (select_topk_fine<NT, E1>(*fine.sm, fine.hist, n, a.m - 2, vals, emit)) {
+      // (blocks with the same score, copies of each other, are not rare here, and the general select on top costs 3.5 us)
+      auto emit_tied = [&](uint32_t above, uint32_t equal, uint32_t r, const auto& v, float tau) {
+#pragma unroll
+        for (int j = 0; j < E1; ++j) {
+          const bool gt = v[j] > tau, eq = v[j] == tau;
+          if (gt || (eq && equal < r)) blk_lds[1 + above + (equal < r ? equal : r)] = (int)threadIdx.x * E1 + j;
+          above += gt;
+          equal += eq;
+        }
+      };
+      if (select_topk_fine<NT, E1>(*fine.sm, fine.hist, n, a.m - 2, vals, emit, emit_tied)) {
         if (threadIdx.x == 0) {
           blk_lds[0] = b_first;
           blk_lds[a.m - 1] = n_last;
@@ -1929,7 +1939,10 @@ __device__ __forceinline__ void stage1_in_workgroup(const QFrag<HG>& f, const Sc
 // Latency bound: launch, sequence, query and tiles, then the top-m.  The one-pass top-m (five barriers) instead of
 // the range-bracketing one (about sixteen), and the query and first tiles requested before the sequence's length
 // is known: 32 queries of 1024 blocks 10.05 -> 9.1 us, 200 of 157 8.75 -> 7.4, 77 of 1564 11.9 -> 10.8, 4 of 7812
-// 28.7 -> 28.0.  (A row that it declines, one in thousands by a tie, ends with the other select behind it: 9.5 -> 11 us.)
+// 28.7 -> 28.0.  Blocks that share the threshold's score are its case too: 32 queries of 1024 blocks in pairs of copies 11.2 us
+// before it, 12.0 when it declined them, 8.6; 77 of 1564 in twenties 14.2, 17.0, 11.2.  (A row that it declines -- an infinite
+// score, one score throughout, a threshold among more than 64 scores a hair apart -- has the other select behind it: up to 7 % slower
+// than without the attempt.)
 // sc_floats >= the block count rounded up to 32; LDS: the tile rings, sc_floats scores, m ids
 // (rounded up to 4), HG * 8192 bytes for the query fragment.
 template <int HG, int E1, int NB, int NW>

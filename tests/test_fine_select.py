@@ -202,6 +202,38 @@ def test_stage1_of_a_small_batch_against_a_sort(M, m, kind):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("copies", [2, 20, 64, 65, 300])
+@pytest.mark.parametrize("M,m", [(70, 9), (300, 126), (512, 30), (1024, 64), (1025, 7), (2048, 500), (2049, 128), (8192, 1000)])
+def test_stage1_of_a_small_batch_with_ties_across_the_threshold(M, m, copies):
+    # the one-pass top-m takes the first of the blocks that share the threshold's score, also if they crowd their bin alone (more
+    # than 64); with others among them it declines.  Every instance of the one-launch Stage 1, copies side by side, strewn over
+    # the row, and strewn with a quarter of them a hair above the rest
+    from paper_2603_28458_amd import hisa
+
+    B, T, H = 32, 24, 64 if M % 2 == 0 else 32
+    print(f"\n[small stage 1, ties] M={M} m={m} H={H} copies={copies}", flush=True)
+    rng = np.random.default_rng(M + m + copies)
+    K = hisa.Keys(k=None, seq_len=torch.tensor([M * B], dtype=torch.int32).cuda(), dtype=hisa.HISA_BF16, n_seq=1, s_max=M * B, d=128)
+    strewn = rng.permutation(M) // copies
+    beside = strewn.astype(np.float64)
+    beside[rng.permutation(M)[: M // 4]] += 2.0 ** -12              # in the bin of the others; every sum below is a float32 number
+    for level in (rng.permutation(-(-M // copies)).repeat(copies)[:M], strewn, beside):
+        pooled = torch.zeros((1, M, 128))
+        pooled[0, :, 0], pooled[0, :, 1] = torch.from_numpy(level // 1 % 256).float(), torch.from_numpy(level // 256).float()
+        pooled[0, :, 2] = torch.from_numpy(level % 1).float()
+        pos = np.concatenate([rng.integers(m * B, M * B, T - 1), [M * B - 1]])
+        lo = np.where(np.arange(T) % 3 == 0, rng.integers(0, np.maximum(1, pos - m * B)), 0)
+        Q = hisa.Queries(**one_head_queries(H, T, {0: 1.0, 1: 256.0, 2: 1.0}), q_pos=torch.from_numpy(pos.astype(np.int32)).cuda(),
+                         q_lo=torch.from_numpy(lo.astype(np.int32)).cuda())
+        got = hisa.hisa_block_score_topk(Q, K, pooled.bfloat16().cuda(), hisa.HISA_BF16, B, m)[0].cpu().numpy()
+        for t in range(T):
+            ids = np.arange(lo[t] // B, pos[t] // B + 1)
+            s = level[ids].astype(np.float64)
+            s[[0, -1]] = np.inf                      # forced
+            assert np.array_equal(got[t], expected_row(s, ids, m)), t
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("T,H,M,m", [(257, 64, 512, 64), (1024, 64, 511, 500), (1025, 64, 512, 64), (300, 64, 33, 2), (700, 64, 130, 32),
                                      (1536, 32, 512, 128), (1537, 32, 512, 64), (769, 32, 64, 63), (258, 32, 3, 2), (600, 32, 513, 64)])
 def test_stage1_in_one_launch_beyond_a_query_per_cu(T, H, M, m):
