@@ -799,12 +799,14 @@ __global__ __launch_bounds__(256, 2) void k_score_ranges(ScoreArgs a) {
 // workgroup of 4 waves per (group of tiles, query), a wave walking tiles_per_wave (at most 64) tiles of 32 candidates,
 // which lie at out[32 v] for tile v (-inf for slots that are masked).
 // Bound by latency with few queries and by HBM with many (every key is read once).  Nothing waits for what it does not
-// need: the query, the block ids of the wave's tiles and the query's sequence are requested together, the first tiles as
-// soon as ids and sequence are there, and the query's position is looked up behind them: three memory latencies where
-// sequence, length, query, ids and tiles one after the other are five.  That takes LDS for the query beside the rings:
-// 80 KB with 64 heads and bf16 keys, two workgroups per CU as before.
-// Refinement call against the five: 1 query (bf16, m 64) 11.8 -> 11.2 us, 32 22.9 -> 22.1, 200 (fp8) 49.1 -> 45.7, 77 (fp8)
-// 23.7 -> 22.1, 100 of 30K (fp8) 30.4 -> 28.3; 1.0-1.5 us of a kernel alone.
+// need: the query, the block ids of the wave's tiles and the query's sequence and position are requested together, the first
+// tiles as soon as these are there: three memory latencies where sequence, length, query, ids and tiles one after the
+// other are five.  That takes LDS for the query beside the rings: 80 KB with 64 heads and bf16 keys, two workgroups per CU as
+// before (fp8 with 32 heads: 42 KB, three instead of four).
+// Refinement call against the five: 1 query (bf16, m 64) 10.7 -> 9.2 us, 32 18.0 -> 16.4, 200 58.3 -> 55.2, (fp8) 40.3 ->
+// 35.6.  (The position behind the tiles, as it once was, is no faster, and then a query that is kept whole has to
+// wait for tiles nobody reads, 32 queries of 500 to 2000 tokens 5.9 -> 6.6 us, and the tiles of large blocks that hold no
+// visible key are scored: 200 queries, B 4096, m 2, an eighth of the own block visible, 38.1 us, 41.4 with them, 34.4.)
 template <int HG, int KDT>
 constexpr int kGatherLds = 4 * 2 * TileGeom<KDT>::kBufBytes + (KDT == DT_FP8 ? 32 * HG * 260 : HG * 8192);
 
@@ -824,34 +826,17 @@ __global__ __launch_bounds__(256, 2) void k_score_gather(ScoreArgs a) {
   if constexpr (KDT == DT_FP8) split_query_request<HG, 4>(q_share, q_t, w_t, wave);
   else qfrag_shared_request<HG, 4>(fo, q_t, w_t, (long)a.H * kD * 2, lds_address(q_lds), wave);
 
-  // lane j: the first key row of this wave's j-th tile, v = v0 + wave + 4 j, or -1 (an empty slot, a block out of range)
-  const int tpb = a.B >> 5, n_tiles = a.m * tpb, n_blocks = (int)(a.rows_per_seq / a.B);
+  const int pos = query_pos_in(a, t, seq);
+  const int n_vis = pos + 1;
+  const int lo = query_lo(a.q_lo, t, pos);
+  // this wave's tiles are v = v0 + wave + 4 j: lane j asks for the block id of the j-th
+  const int tpb = a.B >> 5, n_tiles = a.m * tpb, n_blocks = (int)a.rows_per_seq / a.B;
   const int v0 = rg.x * 4 * a.tiles_per_wave;
   const int32_t* ids = a.block_idx + (long)t * a.m;
   const int my_v = v0 + wave + 4 * lane;
   const bool mine = lane < a.tiles_per_wave && my_v < n_tiles;
-  int my_row = -1;
-  if (mine) {
-    const int slot = my_v / tpb;
-    const int blk = ids[slot];
-    if (blk >= 0 && blk < n_blocks) my_row = blk * a.B + (my_v - slot * tpb) * 32;
-  }
-  const uint64_t used = __ballot(my_row >= 0);
-  const int nj = used ? 64 - __builtin_clzll(used) : 0;   // the tiles behind the last used one hold nothing
-  auto row_at = [&](int j) {
-    const int r = __builtin_amdgcn_readlane(my_row, j);
-    return r < 0 ? 0 : r;   // a tile without a block flows through and is masked below
-  };
-  __amdgpu_buffer_rsrc_t krsrc, srsrc;
-  key_buffers<KDT>(a, seq, krsrc, srsrc);
-  const uint32_t ring_addr = lds_address(smem) + wave * NB * BB;
-#pragma unroll
-  for (int b = 0; b < NB; ++b)
-    if (b < nj) tile_dma<KDT>(krsrc, srsrc, ring_addr + b * BB, row_at(b));
-
-  const int pos = query_pos_in(a, t, seq);
-  const int n_vis = pos + 1;
-  const int lo = query_lo(a.q_lo, t, pos);
+  const int slot = my_v / tpb;
+  const int blk = mine ? ids[slot] : -1;
   if (n_vis - lo <= a.whole_rows) {
     BlockList list;
     if (never_neg_inf(w_t, a.H, a.k_scale ? a.k_scale + (long)seq * a.rows_per_seq : nullptr, lo, pos) &&
@@ -861,17 +846,37 @@ __global__ __launch_bounds__(256, 2) void k_score_gather(ScoreArgs a) {
       return;
     }
   }
+  // its first key row, or -1: an empty slot, a block out of range, no visible key
+  int my_row = -1;
+  if (blk >= 0 && blk < n_blocks) {
+    const int r = blk * a.B + (my_v - slot * tpb) * 32;
+    if (r < n_vis && r + 32 > lo) my_row = r;
+  }
+  const uint64_t used = __ballot(my_row >= 0);
+  const int j0 = used ? __builtin_ctzll(used) : 0;             // in front of the first used one and behind the last there is
+  const int nj = used ? 64 - __builtin_clzll(used) - j0 : 0;   //   nothing to score
+  auto row_at = [&](int j) {
+    const int r = __builtin_amdgcn_readlane(my_row, j0 + j);
+    return r < 0 ? 0 : r;   // a tile without a block flows through and is masked below
+  };
+  __amdgpu_buffer_rsrc_t krsrc, srsrc;
+  key_buffers<KDT>(a, seq, krsrc, srsrc);
+  const uint32_t ring_addr = lds_address(smem) + wave * NB * BB;
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+    if (b < nj) tile_dma<KDT>(krsrc, srsrc, ring_addr + b * BB, row_at(b));
+
   float* out = a.out + (long)rg.row * a.ld;
-  if (mine && lane >= nj)
+  if (mine && (lane < j0 || lane >= j0 + nj))
     for (int x = 0; x < 32; ++x) out[my_v * 32 + x] = neg_inf();
   if constexpr (KDT == DT_FP8) split_query_complete<HG, 4>(q_share, q_lds, wave, fo);
   else qfrag_shared_complete<HG>(fo, lds_address(q_lds));
   auto finish = [&](int j, bool both, float s) {
-    const int r0 = __builtin_amdgcn_readlane(my_row, j), r1 = __builtin_amdgcn_readlane(my_row, both ? j + 1 : j);
+    const int r0 = __builtin_amdgcn_readlane(my_row, j0 + j), r1 = __builtin_amdgcn_readlane(my_row, j0 + (both ? j + 1 : j));
     const int r = lane < 32 ? r0 : r1;
     const int row = r + (lane & 31);
     if (r < 0 || row >= n_vis || row < lo) s = neg_inf();
-    if (both || lane < 32) out[(v0 + wave + 4 * j) * 32 + (lane < 32 ? lane : 96 + lane)] = s;
+    if (both || lane < 32) out[(v0 + wave + 4 * (j0 + j)) * 32 + (lane < 32 ? lane : 96 + lane)] = s;
   };
   wave_pipeline<HG, KDT, NB>(fo, krsrc, srsrc, ring_addr, nj, row_at, finish, NB);
 }

@@ -350,6 +350,44 @@ def test_fp32_rows_in_one_launch_with_scores_that_are_no_numbers(T, H, d, M, m, 
     assert torch.equal(hisa.hisa_token_refine_topk(Q, K, B, m, blocks, k)[0], want)
 
 
+@pytest.mark.parametrize("k_dtype,H,T,B,m", [
+    ("bf16", 64, 200, 4096, 2), ("bf16", 32, 130, 1024, 5), ("fp8_e4m3", 64, 255, 512, 9), ("fp8_e4m3", 32, 200, 2048, 3), ("bf16", 64, 3, 4096, 3),
+    ("fp8_e4m3", 64, 1, 128, 64), ("bf16", 64, 40, 32, 65), ("bf16", 32, 300, 128, 130)])
+def test_candidates_in_front_of_and_behind_the_visible_ones(k_dtype, H, T, B, m):
+    # large blocks of which a query sees a few tiles, or none, at either end; slots that are empty or name no block, at both ends
+    # and between: every candidate's score, -inf where it is masked, against sums in 64 bits
+    import torch
+    from paper_2603_28458_amd import hisa
+
+    n_blocks = m + 3
+    L = n_blocks * B
+    print(f"\n[gather] {k_dtype} H={H} T={T} B={B} m={m}", flush=True)
+    rng = np.random.default_rng(T + B)
+    wl = W.make_workload(f"gather_{T}_{B}", seq_len=L - B // 3, T=T, H=H, d=128, B=B, m=m, k=8, q_dtype="bf16", k_dtype=k_dtype, seed=520)
+    pos = rng.integers(0, L, T).astype(np.int32)
+    lo = np.where(np.arange(T) % 3 == 0, 0, rng.integers(0, pos + 1)).astype(np.int32)
+    lists = np.stack([rng.permutation(np.concatenate([rng.permutation(n_blocks)[: max(1, m - 2)], [-1, n_blocks + 5]]))[:m] for _ in range(T)])
+    lists[::4].sort(1)
+    lists = np.ascontiguousarray(lists, np.int32)
+    Q, K = hisa.to_device(wl)
+    Q = hisa.Queries(q=Q.q, w=Q.w, dtype=Q.dtype, q_pos=torch.from_numpy(pos).cuda(), q_lo=torch.from_numpy(lo).cuda())
+    got = hisa.hisa_token_refine_topk(Q, K, B, m, torch.from_numpy(lists).cuda(), 8, want_cand_scores=True)[2].cpu().numpy()
+    if k_dtype == "bf16":
+        keys = K.k[0].double().cpu().numpy()
+    else:
+        keys = K.k[0].view(torch.float8_e4m3fn).double().cpu().numpy() * K.k_scale[0].double().cpu().numpy()[:, None]
+    q, w = Q.q.double().cpu().numpy(), Q.w.double().cpu().numpy()
+    n_keys = int(K.seq_len[0])
+    for t in range(T):
+        tok = (lists[t].astype(np.int64)[:, None] * B + np.arange(B)).reshape(-1)
+        seen = np.repeat((lists[t] >= 0) & (lists[t] < n_blocks), B) & (tok <= min(pos[t], n_keys - 1)) & (tok >= lo[t])
+        assert np.array_equal(got[t] == -np.inf, ~seen), t
+        if t % 16 == 0:
+            want = np.maximum(keys[tok[seen]] @ q[t].T, 0.0) @ w[t]
+            # fp32 sums of 64 gated heads of 128 products (fp8: the matrix instruction's own accumulation), on the scores' scale
+            assert np.abs(got[t][seen] - want).max(initial=0.0) <= (1e-5 if k_dtype == "bf16" else 3e-4) * np.abs(want).max(initial=1.0), t
+
+
 @pytest.mark.parametrize("k_dtype,H,L,B,m,k", [
     ("bf16", 64, 16500, 32, 200, 700), ("bf16", 64, 17000, 32, 133, 500), ("bf16", 32, 16400, 32, 128, 512), ("bf16", 32, 20000, 64, 120, 900),
     ("fp8_e4m3", 64, 33000, 32, 256, 1000), ("fp8_e4m3", 32, 33000, 32, 100, 400), ("fp8_e4m3", 64, 34000, 128, 128, 2000),
