@@ -1941,11 +1941,10 @@ __device__ __forceinline__ void stage1_in_workgroup(const QFrag<HG>& f, const Sc
 // there are more queries than CUs two or three workgroups share a CU and cover each other's waits.  Against 8 waves with a
 // ring of two, 64 heads: 1 query of 512 blocks 6.9 -> 6.65 us, 32 of 1024 8.75 -> 8.3, 200 of 157 6.65 -> 6.35, 256 of 1024 9.8 -> 9.4;
 // 32 heads 0-3 %; against two launches: 512 queries of 512 blocks 12.4 (consecutive: 16.4) -> 8.9, 1024 17.5 (19.4) -> 16.0.
-// Latency bound: launch, sequence, query and tiles, then the top-m.  The one-pass top-m (five barriers) instead of
-// the range-bracketing one (about sixteen), and the query and first tiles requested before the sequence's length
-// is known: 32 queries of 1024 blocks 10.05 -> 9.1 us, 200 of 157 8.75 -> 7.4, 77 of 1564 11.9 -> 10.8, 4 of 7812
-// 28.7 -> 28.0.  Blocks that share the threshold's score are its case too: 32 queries of 1024 blocks in pairs of copies 11.2 us
-// before it, 12.0 when it declined them, 8.6; 77 of 1564 in twenties 14.2, 17.0, 11.2.  (A row that it declines -- an infinite
+// Latency bound: launch, sequence, query and tiles, then the top-m.  The one-pass top-m (five barriers)
+// instead of the range-bracketing one (about sixteen), with the 4 waves: 32 queries of 1024 blocks 10.3 -> 8.4 us, 200 of 157
+// 8.2 -> 6.5, 77 of 1564 (8 waves) 11.7 -> 10.6, 4 of 7812 28.8 -> 27.1.
+// Blocks that share the threshold's score are its case too: 32 queries of 1024 blocks in pairs of copies 11.2 us before it, 12.0 when it declined them, 8.6; 77 of 1564 in twenties 14.2, 17.0, 11.2.  (A row that it declines -- an infinite
 // score, one score throughout, a threshold among more than 64 scores a hair apart -- has the other select behind it: up to 7 % slower
 // than without the attempt.)
 // sc_floats >= the block count rounded up to 32; LDS: the tile rings, sc_floats scores, m ids
@@ -1966,21 +1965,27 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_stage1_query(Score
   const int t = a.t_begin + blockIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int seq = query_seq(a, t);
-  const int n_blocks = (int)(a.rows_per_seq / a.B);
-  // The query fragment is staged in an area of its own, so that every wave's first tile of pooled keys can be
-  // requested right behind it, and both as soon as the sequence is known: one memory latency for the query, the
-  // tiles and the sequence's length (rows past its end, or of a query that is not scored, are not used).
+  const int n_blocks = (int)a.rows_per_seq / a.B;
+  // The query fragment is staged in an area of its own and requested at once, every wave's first tile of pooled keys
+  // as soon as the sequence is known: one memory latency for the query, the tiles and the sequence's length (rows past
+  // its end are not used).  A query that may keep all its blocks waits for the length before it asks for a tile: what it was
+  // given as its position, which is there with the sequence, says so, unless the sequence is shorter than that.
+  // (Tiles for all: 32 that keep all their blocks 2.9 us instead of 2.6, 1000 6.0 instead of 4.75.  The query, too, behind the
+  // position: 2.2 and 3.1 us, but a pass over 32 queries at 128K 0.5 us longer, 36.3 -> 36.9.)
   QFrag<HG> f;
   qfrag_shared_request<HG, NW>(f, (const uint16_t*)a.q + (long)t * a.H * kD, a.w + (long)t * a.H,
                                (long)a.H * kD * 2, lds_address(q_lds), wave);
-  {
+  auto request_tile = [&] {
     const __amdgpu_buffer_rsrc_t prsrc =
         key_buffer((const char*)pooled + (long)seq * n_blocks * kD * 2, (long)n_blocks * kD * 2);
     tile_dma<DT_BF16>(prsrc, prsrc, lds_address(smem) + wave * NB * TILE, wave * 32);
-  }
+  };
+  const long most = (long)a.m * a.B;   // a query that sees this many positions or more has more than m blocks
+  const bool scored = (long)(a.q_pos ? a.q_pos[t] : a.q_pos0 + t) - query_lo(a.q_lo, t, 0x7ffffffe) >= most;
+  if (scored) request_tile();
   const int pos = query_pos_in(a, t, seq);
   const int lo = query_lo(a.q_lo, t, pos);
-  {
+  if (pos - lo < most) {
     const int b_first = lo > 0 ? lo / a.B : 0, n_bvis = pos < 0 ? 0 : pos / a.B + 1;
     if (n_bvis - b_first <= a.m && never_neg_inf(a.w + (long)t * a.H, a.H, nullptr, 0, 0)) {   // nothing to score
       for (int p = threadIdx.x; p < a.m; p += NT) block_idx_out[(long)t * a.m + p] = p < n_bvis - b_first ? b_first + p : -1;
@@ -1988,6 +1993,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_stage1_query(Score
       return;
     }
   }
+  if (!scored) request_tile();
   qfrag_shared_complete<HG>(f, lds_address(q_lds));
   qfrag_ready<HG>(f);
   uint32_t* hist = reinterpret_cast<uint32_t*>(q_lds);
