@@ -2139,9 +2139,12 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_refine_fused(Score
   // 3834 -> 2591, 8000 at 500K 1857 -> 1689; 32 heads, prefill of 60K 6132 -> 5446; fp8 keys, 64K 6443 -> 6343, 12000 at 128K (32 heads) 961 -> 854, 16384 at 1M
   // 4233 -> 4085; 1024 queries at 64K and 16K prefill +-0.5 %.  (By the launch order instead of the clock: 128K 3040, but
   // 1024 queries at 64K, which all start at once, 151 -> 198.)
+  // All waves of a workgroup or none: where only those with an even number of tiles took part (and the others kept
+  // beginning at their first tile), the tiles of a workgroup came from two places of the array at once, and walks of 124
+  // to 126 tiles were 4 % slower than without on average, 20 % at most (walk_in_step).
   int j0 = 0;
-  if (E1 == 0 && a.walk != 0u && nj > 0 && (nj & 1) == 0)   // (pairs of tiles are finished together: an odd walk starts at 0)
-    j0 = (int)(((uint32_t)__builtin_amdgcn_s_memrealtime() / a.walk) % ((uint32_t)nj >> 1)) * 2;
+  if (E1 == 0 && a.walk != 0u && walk_in_step(n_active, NW))
+    j0 = walk_start(n_active, NW, (uint32_t)__builtin_amdgcn_s_memrealtime(), a.walk);
   rows.lo = row_of(walk_tile(lane, nj, j0, wave, NW));
   rows.hi = (E > 32 && nj > 64) ? row_of(walk_tile(lane + 64, nj, j0, wave, NW)) : -1;
   __amdgpu_buffer_rsrc_t krsrc, srsrc;

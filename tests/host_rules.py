@@ -20,6 +20,12 @@ extern "C" int tile_of_walk(long j, long nj, long j0, long wave, long n_waves) {
 }
 extern "C" int f32_one_launch(long T, long n, long H, long d) { return hisa::rows_f32_one_launch(T, n, H, d); }
 extern "C" int f32_waves(long T, long n) { return hisa::rows_f32_waves(T, n); }
+extern "C" int in_step(long n_tiles, long n_waves) { return hisa::walk_in_step(n_tiles, n_waves); }
+extern "C" int start_of_walk(long n_tiles, long n_waves, long now, long ticks) {
+  return hisa::walk_start(n_tiles, n_waves, (uint32_t)now, ticks);
+}
+extern "C" int ticks_of_walk(long key_bytes, long fp8) { return hisa::walk_ticks(key_bytes, fp8); }
+extern "C" int one_launch(long T, long M, long H) { return hisa::stage1_one_launch(T, M, H); }
 extern "C" int tiles_per_wave(long T, long n_tiles) { return hisa::gather_tiles_per_wave(T, n_tiles); }
 """
 
@@ -62,3 +68,16 @@ def f32_one_launch(T, n, H, d):
 
 def f32_waves(T, n):
     return _call("f32_waves", T, n)
+
+
+def walk_start(n_tiles, n_waves, now, ticks):
+    """First tile of the walks, as the kernel has it: 0 unless they may begin elsewhere."""
+    return _call("start_of_walk", n_tiles, n_waves, now, ticks) if _call("in_step", n_tiles, n_waves) else 0
+
+
+def walk_ticks(key_bytes, fp8):
+    return _call("ticks_of_walk", key_bytes, fp8)
+
+
+def stage1_one_launch(T, M, H):
+    return bool(_call("one_launch", T, M, H))

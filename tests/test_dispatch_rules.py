@@ -1,5 +1,5 @@
 """The rules that cut a launch into workgroups, over the sizes they are asked for."""
-from tests.host_rules import f32_one_launch, f32_waves, in_ring, key_ranges, tile_of_walk, tiles_per_wave
+from tests.host_rules import f32_one_launch, f32_waves, in_ring, key_ranges, tile_of_walk, tiles_per_wave, walk_start
 
 
 def _cost(T, n_tiles, tpw):
@@ -87,3 +87,15 @@ def test_fp32_rows_in_one_launch_only_where_it_is_the_faster():
         for n in (1, 63, 64, 65, 128, 129, 256, 257, 512):
             waves = f32_waves(T, n)
             assert waves in (1, 2, 4, 8) and (waves == 1 or 64 * waves // 2 < n), (T, n, waves)   # no wave without a candidate of its own
+
+
+def test_walks_begin_in_step():
+    # the waves of a workgroup begin at the same one of their tiles, at an even one, and never in a walk that is odd
+    for n_waves in (4, 8):
+        for n_tiles in list(range(1, 140)) + [244, 256, 500, 512]:
+            njs = {max(0, -(-(n_tiles - w) // n_waves)) for w in range(n_waves)}
+            seen = {walk_start(n_tiles, n_waves, now, 200) for now in [0, 199, 200, 12345, 0xffffffff] + [200 * i for i in range(70)]}
+            if len(njs) > 1 or min(njs) % 2:
+                assert seen == {0}, (n_tiles, n_waves)
+            else:
+                assert seen == set(range(0, min(njs), 2)), (n_tiles, n_waves)
