@@ -1,5 +1,6 @@
 """The rules that cut a launch into workgroups, over the sizes they are asked for."""
-from tests.host_rules import f32_one_launch, f32_waves, in_ring, key_ranges, tile_of_walk, tiles_per_wave, walk_start
+from tests.host_rules import (f32_one_launch, f32_waves, in_ring, key_ranges, stage1_one_launch, tile_of_walk, tiles_per_wave,
+                              walk_start, walk_ticks)
 
 
 def _cost(T, n_tiles, tpw):
@@ -99,3 +100,17 @@ def test_walks_begin_in_step():
                 assert seen == {0}, (n_tiles, n_waves)
             else:
                 assert seen == set(range(0, min(njs), 2)), (n_tiles, n_waves)
+
+
+def test_walks_only_over_more_keys_than_an_l2_holds():
+    assert walk_ticks(4 << 20, 0) == 0 and walk_ticks(4 << 20, 1) == 0
+    assert walk_ticks((4 << 20) + 1, 0) == 200 and walk_ticks((1 << 31) - 1, 1) == 160
+
+
+def test_stage1_in_one_launch():
+    # up to a query per CU: whatever the select holds; beyond: two rounds of 512 (64 heads) or 768 (32), rows of a one-wave select
+    for H, two_rounds in ((64, 1024), (32, 1536)):
+        assert stage1_one_launch(1, 1, H) and stage1_one_launch(256, 8192, H) and not stage1_one_launch(256, 8193, H)
+        assert stage1_one_launch(257, 512, H) and not stage1_one_launch(257, 513, H)
+        assert stage1_one_launch(two_rounds, 512, H) and not stage1_one_launch(two_rounds + 1, 512, H)
+        assert not stage1_one_launch(1 << 22, 1, H)
