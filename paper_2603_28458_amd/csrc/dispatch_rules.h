@@ -112,8 +112,8 @@ inline bool rows_f32_one_launch(long T, long n_max, int H, int d) {
 // own / consecutive), 512 blocks, 64 heads: 257 queries 8.4 (11.7 / 14.6), 512 8.9 (12.4 / 16.4), 640 13.5 (15.9 / 17.6), 1024
 // 16.0 (17.5 / 19.4), 1300 22.5 (22.4 / 22.6), 2047 31.3 (30.2 / 26.2); 32 heads: 768 9.1 (14.3 / 14.2), 1024 13.8 (15.8 /
 // 14.6), 1536 15.9 (19.7 / 18.0), 2047 21.6 (23.7 / 18.5); 128 blocks, 64 heads: 512 6.8 (10.1 / 14.8), 1024 12.0 (13.3 / 15.9),
-// 1300 16.7 (16.0 / 16.4).  So: two rounds.  Over 512 blocks the two launches' select is another one, which places a NaN
-// score elsewhere.
+// 1300 16.7 (16.0 / 16.4).  So: two rounds.  Over 512 blocks the two launches' select is another one,
+// with workgroups of its own for a row, and one launch is not measured against it.
 inline bool stage1_one_launch(long T, long M, int H) {
   return T <= kCUs ? M <= 8192 : M <= 512 && T <= 2 * kCUs * (H == 64 ? 2 : 3);
 }

@@ -1868,7 +1868,7 @@ __device__ __forceinline__ void stage1_in_workgroup(const QFrag<HG>& f, const Sc
         if (both || lane < 32) sc[b] = visible ? s : neg_inf();
       },
       primed && nj1 > 0 ? 1 : 0);
-  // (an infinite range makes the one-pass top-k decline: the select below takes a NaN score first)
+  // (an infinite range makes the one-pass top-k decline: to the select below a NaN score is a candidate, by its bits)
   if constexpr (kFine) fine_select_range<NT, E1>(*fine.sm, any_nan ? __builtin_inff() : s_max, s_min, wave);
   __syncthreads();   // block scores complete, rings dead
   const int n = b_first <= n_last ? n_bvis : 0;   // (a first visible block past the query's own: it sees nothing)
