@@ -802,19 +802,26 @@ __global__ __launch_bounds__(256, 2) void k_score_ranges(ScoreArgs a) {
 // need: the query, the block ids of the wave's tiles and the query's sequence and position are requested together, the first
 // tiles as soon as these are there: three memory latencies where sequence, length, query, ids and tiles one after the
 // other are five.  That takes LDS for the query beside the rings: 80 KB with 64 heads and bf16 keys, two workgroups per CU as
-// before (fp8 with 32 heads: 42 KB, three instead of four).
+// before.  With 32 heads and fp8 keys that would be 42 KB and three workgroups instead of four, so there the query lies over the last wave's
+// second tile, which that wave requests once the query is in registers: 38 KB.  200 queries of 2000 tokens (kept whole) 11.9 us without
+// an area for the query, 15.9 with one of 42 KB, 12.0; 2000 queries, m 256, 952 -> 933, decode batches (1 to 255 queries, m 4 to 128) the same
+// on average, 0.97 (130 of m 64) to 1.04 (77 of m 128, still 0.97 of the time without).
 // Refinement call against the five: 1 query (bf16, m 64) 10.7 -> 9.2 us, 32 18.0 -> 16.4, 200 58.3 -> 55.2, (fp8) 40.3 ->
 // 35.6.  (The position behind the tiles, as it once was, is no faster, and then a query that is kept whole has to
 // wait for tiles nobody reads, 32 queries of 500 to 2000 tokens 5.9 -> 6.6 us, and the tiles of large blocks that hold no
 // visible key are scored: 200 queries, B 4096, m 2, an eighth of the own block visible, 38.1 us, 41.4 with them, 34.4.)
 template <int HG, int KDT>
-constexpr int kGatherLds = 4 * 2 * TileGeom<KDT>::kBufBytes + (KDT == DT_FP8 ? 32 * HG * 260 : HG * 8192);
+constexpr bool kQueryOverTile = HG == 1 && KDT == DT_FP8;
+template <int HG, int KDT>
+constexpr int kGatherQuery = (kQueryOverTile<HG, KDT> ? 7 : 8) * TileGeom<KDT>::kBufBytes;   // where the query lies
+template <int HG, int KDT>
+constexpr int kGatherLds = kGatherQuery<HG, KDT> + (KDT == DT_FP8 ? 32 * HG * 260 : HG * 8192);
 
 template <int HG, int KDT>
 __global__ __launch_bounds__(256, 2) void k_score_gather(ScoreArgs a) {
   constexpr int NB = 2, BB = TileGeom<KDT>::kBufBytes;
   extern __shared__ __align__(16) unsigned char smem[];   // [wave][NB] tile rings, then the query: kGatherLds
-  unsigned char* q_lds = smem + 4 * NB * BB;
+  unsigned char* q_lds = smem + kGatherQuery<HG, KDT>;
   const RowGroup rg = row_group(a.groups);
   const int t = a.t_begin + rg.row;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -862,9 +869,10 @@ __global__ __launch_bounds__(256, 2) void k_score_gather(ScoreArgs a) {
   __amdgpu_buffer_rsrc_t krsrc, srsrc;
   key_buffers<KDT>(a, seq, krsrc, srsrc);
   const uint32_t ring_addr = lds_address(smem) + wave * NB * BB;
+  const int primed = kQueryOverTile<HG, KDT> && wave == 3 ? 1 : NB;
 #pragma unroll
   for (int b = 0; b < NB; ++b)
-    if (b < nj) tile_dma<KDT>(krsrc, srsrc, ring_addr + b * BB, row_at(b));
+    if (b < nj && b < primed) tile_dma<KDT>(krsrc, srsrc, ring_addr + b * BB, row_at(b));
 
   float* out = a.out + (long)rg.row * a.ld;
   if (mine && (lane < j0 || lane >= j0 + nj))
@@ -878,7 +886,7 @@ __global__ __launch_bounds__(256, 2) void k_score_gather(ScoreArgs a) {
     if (r < 0 || row >= n_vis || row < lo) s = neg_inf();
     if (both || lane < 32) out[(v0 + wave + 4 * (j0 + j)) * 32 + (lane < 32 ? lane : 96 + lane)] = s;
   };
-  wave_pipeline<HG, KDT, NB>(fo, krsrc, srsrc, ring_addr, nj, row_at, finish, NB);
+  wave_pipeline<HG, KDT, NB>(fo, krsrc, srsrc, ring_addr, nj, row_at, finish, primed);
 }
 
 // Eq. 1 / Eq. 5 on MFMA for a causal prefill of ONE sequence with consecutive positions: one

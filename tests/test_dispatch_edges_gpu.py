@@ -352,7 +352,8 @@ def test_fp32_rows_in_one_launch_with_scores_that_are_no_numbers(T, H, d, M, m, 
 
 @pytest.mark.parametrize("k_dtype,H,T,B,m", [
     ("bf16", 64, 200, 4096, 2), ("bf16", 32, 130, 1024, 5), ("fp8_e4m3", 64, 255, 512, 9), ("fp8_e4m3", 32, 200, 2048, 3), ("bf16", 64, 3, 4096, 3),
-    ("fp8_e4m3", 64, 1, 128, 64), ("bf16", 64, 40, 32, 65), ("bf16", 32, 300, 128, 130)])
+    ("fp8_e4m3", 64, 1, 128, 64), ("bf16", 64, 40, 32, 65), ("bf16", 32, 300, 128, 130),
+    ("fp8_e4m3", 32, 1, 32, 7), ("fp8_e4m3", 32, 130, 32, 9), ("fp8_e4m3", 32, 255, 128, 64)])
 def test_candidates_in_front_of_and_behind_the_visible_ones(k_dtype, H, T, B, m):
     # large blocks of which a query sees a few tiles, or none, at either end; slots that are empty or name no block, at both ends
     # and between: every candidate's score, -inf where it is masked, against sums in 64 bits
