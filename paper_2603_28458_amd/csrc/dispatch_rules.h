@@ -39,17 +39,17 @@ inline int prefill_split(long q_groups, long rows_first, long rows_last) {
   return best;
 }
 
-// Tiles per wave of a gathering k_score_ranges launch (Stage 2 of a decode batch).  A workgroup's four waves
+// Tiles per wave of k_score_gather (Stage 2 of a decode batch).  A workgroup's four waves
 // walk tpw tiles each behind a set-up (query, position, block list) worth about six tiles.  Two workgroups on
 // a CU take twice as long as their share of it, one alone three quarters of that (nothing covers its waits):
 // a full round of 2 * kCUs workgroups counts 4, a last round 4 or, with at most one per CU, 3.
 // One wave per tile keeps a single query's latency short, a wide batch wants full rounds of long workgroups.
-// Refinement calls, us at the value picked here (in brackets at 4, which every batch below 1024 queries used to
-// get): bf16 keys, 64 heads, B 128: 1 query, m 64 1: 11.6 (13.1); 32, m 64 4: 23.4; 130, m 64 10: 52.8 (60.1);
-// 200, m 32 16: 39.4 (49.6); 200, m 64 13: 72.7 (81.3); 255, m 128 16: 171.7 (179.0); fp8 keys: 32, m 64 4: 17.7;
-// 200, m 64 13: 45.6 (58.6).  Over 432 such calls (1 to 255 queries, 8 to 512 tiles, both key types, 32 and 64
-// heads) the rule is 0.6 % from the best of 1 .. 16 on average and 8 % at most; against 4 tiles it is 3 %
-// slower at most.
+// Refinement calls, us at the value picked here (in brackets at 4), B 128: bf16 keys, 64 heads: 1 query, m 64 1: 10.3 (11.9);
+// 32, m 64 4: 21.0; 77, m 32 6: 22.3 (23.9); 130, m 64 10: 52.9 (53.2); 200, m 32 16: 39.3 (43.4); 200, m 64 13: 88.6 (90.9);
+// 255, m 128 16: 221.5 (217.4); fp8 keys: 32, m 64 4: 16.6; 130, m 32 11: 21.1 (27.3); 200, m 64 13: 44.9 (50.8).  Over 140 such
+// calls (1 to 255 queries, 16 to 512 tiles, both key types, 32 and 64 heads) the rule is 1.1 % from the best of 1 .. 16 on average
+// and 12 % at most (255 queries of 64 tiles, fp8); against 4 tiles it is 6 % faster on average and 5 % slower at
+// most.
 inline int gather_tiles_per_wave(long T, long n_tiles) {
   int best = 1;
   long best_cost = 0;
@@ -125,10 +125,29 @@ inline int wgs_per_cu(long lds, int max_wgs) {
 }
 
 // Fused Stage 2: ticks (10 ns) that a wave takes for two tiles of 32 keys, by which the walks of all workgroups are laid
-// over each other (k_refine_fused); 0 where the keys of a sequence fit an XCD's L2 anyway.  Measured per tile, us:
-// 0.8-1.1 with bf16 keys, 0.65-1.1 with fp8.  Too long costs little, too short a lot (20000 bf16 queries at 128K with
-// 0.65 / 0.8 / 0.95 / 1.1 / 1.3: 3921 / 2749 / 2778 / 2854 / 2964 us, 4166 without; 16000 at 256K: 3825 / 3462 / 2591 / 2662 /
-// 2828, 3834; 16000 fp8 at 500K: 1858 / 1874 / 1892 / 1902 / 1906, 1917), so bf16 has the long end of its range.
+// over each other (k_refine_fused); 0 where the key array of a sequence fits an XCD's L2 anyway.  What they take depends on how
+// often the tiles miss the L2, so on the ticks themselves.  us of a launch, two cards within 1 %, m 64 unless stated:
+//   bf16 keys                       no walk   140   160   180   200   220   240   280 ticks
+//   64 heads, 20000 at 128K           4094   3354  2799  2794  2857  2922  2944  3025
+//             16000 at 256K           3824   3686  3471  3193  2617  2682  2763  2894
+//             8000 at 500K            1987   1956  1888  1806  1762  1731  1731  1730
+//             prefill of 64K          8247   7954  7974  8004  7980  8016  8051  8053
+//             16000 at 256K, m 128    7515   7323  6446  5643  5171  5209  5284  5463
+//   32 heads, 20000 at 128K           4284   2415  2414  2508  2604  2746  2904  3032
+//             16000 at 256K           3885   3856  3568  3373  3163  3107  3114  3044
+//   fp8 keys                        no walk   110   130   145   160   175   200   230 ticks
+//   64 heads, 20000 at 256K           2326   2315  2282  2296  2300  2295  2315  2332
+//             16384 at 1M, m 128      4283   4209  4170  4161  4173  4151  4181  4192
+//   32 heads, 12000 at 128K            970    874   861   855   895   884   905   904
+//             16000 at 500K           1939   1880  1760  1677  1426  1453  1503  1550
+//             16384 at 500K, m 128    3740   3125  3142  3199  3228  3252  3290  3349
+// Too long costs little, too short a lot: 10 % below these two values 16000 queries at 256K and at 500K lose 22 and 17 %, 10 % above
+// 2 %; so a card that is 10 % slower would lose that (no value in the table is slower than no walk by more than it is uncertain,
+// 0.5 %).  32 heads share the durations: they wait for the same tiles.
+// By the length of the key array, not by what the queries see (which the host need not know): queries that see little of a
+// long array walk for nothing, and lose nothing by it: prefills of 9000 to 20000 tokens in an array of 128K 622 to 2029 us
+// (624 to 2027 without), 8 sequences of 16000 tokens in arrays of 64K 2059 (2057), 32 of 12000 1652 (1654), fp8 keys, 8 of
+// 30000 1700 (1692), 24K packed prefill 411 (408).
 inline unsigned walk_ticks(long key_bytes, bool fp8) {
   return key_bytes <= 4l << 20 ? 0u : fp8 ? 160u : 200u;
 }

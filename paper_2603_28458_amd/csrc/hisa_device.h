@@ -1102,10 +1102,10 @@ __device__ __forceinline__ int select_topk(SelectSmem<THREADS, E>& sm, int n, in
 //                            selected elements are those with v[j] >= tau, the first of them is the
 //                            pos-th selected of the row (ascending element index); dump is an LDS
 //                            word of the thread's own that may be overwritten.
-//                            emit_tied, if given: taken instead where scores equal to tau lie on both sides of the
-//                            threshold (otherwise declined; a crowded bin is not, if it holds one score only):
-//                            emit_tied(above, equal, r, v, tau): all of v[j] > tau are selected and, of the scores equal to tau, the first r of the row; `above` and `equal` of
-//                            them lie in front of this thread's.
+//                            emit_tied(above, equal, r, v, tau), if given: taken instead where scores equal to tau lie on
+//                            both sides of the threshold (otherwise declined; a crowded bin is not, if it holds one
+//                            score only): all of v[j] > tau are selected and, of the scores equal to tau, the first r
+//                            of the row; `above` and `equal` of them lie in front of this thread's.
 template <int NT, int E>
 struct FineSelSmem {
   static constexpr int NBIN = NT <= 512 ? 2048 : 4 * NT, LCAP = 64, NW = NT / 64;   // >= 4 bins per thread

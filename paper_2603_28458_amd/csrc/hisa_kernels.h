@@ -1831,8 +1831,8 @@ __global__ __launch_bounds__(StreamSelect::kThreads, 8) void k_select_stream(Sel
 // by the select).  Ends with a barrier: ids visible, score area and rings free again.
 // primed: every wave has already issued the DMA of its first tile (blocks 32 * wave ..) into its
 // ring slot 0, and that DMA has completed.
-// fine: scratch of the one-pass top-k, tried first when given (shared with nothing; its bins cleared and a barrier
-// passed by the caller), or null.
+// fine: scratch of the one-pass top-k, tried first when given, or null.  Every wave has cleared its share of the bins before
+// the call (the barrier that ends the scoring is the one they need), and rings, scores, ids and figures lie elsewhere.
 template <int NT, int E1>
 struct Stage1Fine {
   FineSelSmem<NT, E1>* sm;
@@ -2143,9 +2143,9 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_refine_fused(Score
   // order, so a walk that begins at (time / duration of a walk) of its tiles and wraps round meets the walks of its
   // neighbours on the same keys, whenever each of them began; a duration that is 20 % off lets them drift apart by 20 % of
   // the array within a walk.  Where a walk starts changes nothing in its results (a tile's scores have their own place).
-  // Stage 2, us: bf16 keys, 64 heads, prefill of 64K 8067 -> 7761, 20000 queries at 128K 4166 -> 2749, 16000 at 256K
-  // 3834 -> 2591, 8000 at 500K 1857 -> 1689; 32 heads, prefill of 60K 6132 -> 5446; fp8 keys, 64K 6443 -> 6343, 12000 at 128K (32 heads) 961 -> 854, 16384 at 1M
-  // 4233 -> 4085; 1024 queries at 64K and 16K prefill +-0.5 %.  (By the launch order instead of the clock: 128K 3040, but
+  // Stage 2, us: bf16 keys, 64 heads, prefill of 64K 8247 -> 7980, 20000 queries at 128K 4094 -> 2857, 16000 at 256K
+  // 3824 -> 2617, 8000 at 500K 1987 -> 1762; 32 heads, prefill of 60K 6239 -> 5681; fp8 keys, 64K 6575 -> 6555, 12000 at 128K (32 heads) 970 -> 895, 16384 at 1M
+  // 4283 -> 4173; 1024 queries at 64K 149 -> 147.  (By the launch order instead of the clock: 128K 3040, but
   // 1024 queries at 64K, which all start at once, 151 -> 198.)
   // All waves of a workgroup or none: where only those with an even number of tiles took part (and the others kept
   // beginning at their first tile), the tiles of a workgroup came from two places of the array at once, and walks of 124
