@@ -340,19 +340,23 @@ int launch_indexer(const ScoreArgs& a, const void* pooled, int k, int32_t* block
 }
 
 // Stage 1 of a small batch in one launch (k_stage1_query): M blocks per sequence (NW * 64 * E1 at most), E1 per thread.
-template <int HG, int E1, int NW>
+template <int HG, int E1, int NW, bool SHORT = false>
 int launch_stage1_query_e(const ScoreArgs& a, const void* pooled, int M, int32_t* block_idx, hipStream_t st) {
   const int sc_floats = (int)round_up(M, 32);
   // 4 waves: a ring of one; 8: up to 2048 blocks a ring of two tiles per wave fits beside the scores, above that a ring of one
   constexpr int NB = NW == 8 && E1 <= 4 ? 2 : 1;
   const size_t sh = (size_t)NW * NB * 8192 + (size_t)sc_floats * 4 + (size_t)round_up(a.m, 4) * 4 + (size_t)HG * 8192;
-  constexpr auto kern = k_stage1_query<HG, E1, NB, NW>;
+  constexpr auto kern = k_stage1_query<HG, E1, NB, NW, SHORT>;
   if (raise_lds_limit<kern>(sh)) return HISA_ERR_LAUNCH;
   hipLaunchKernelGGL(kern, dim3(a.t_count), dim3(NW * 64), sh, st, a, pooled, block_idx, sc_floats);
   return HISA_OK;
 }
 
 int launch_stage1_query(const ScoreArgs& a, const void* pooled, int M, int32_t* block_idx, hipStream_t st) {
+  static_assert(kMaxM <= 1024, "a short array's blocks fit 4 waves");
+  if (M <= a.m && a.t_count <= 1024)   // (SHORT: k_stage1_query)
+    return a.H == 64 ? launch_stage1_query_e<2, 4, 4, true>(a, pooled, M, block_idx, st)
+                     : launch_stage1_query_e<1, 4, 4, true>(a, pooled, M, block_idx, st);
   if (a.t_count > kCUs || M <= 1024)   // (4 waves: k_stage1_query)
     return a.H == 64 ? launch_stage1_query_e<2, 4, 4>(a, pooled, M, block_idx, st)
                      : launch_stage1_query_e<1, 4, 4>(a, pooled, M, block_idx, st);

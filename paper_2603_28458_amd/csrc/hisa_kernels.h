@@ -1957,7 +1957,12 @@ __device__ __forceinline__ void stage1_in_workgroup(const QFrag<HG>& f, const Sc
 // than without the attempt.)
 // sc_floats >= the block count rounded up to 32; LDS: the tile rings, sc_floats scores, m ids
 // (rounded up to 4), HG * 8192 bytes for the query fragment.
-template <int HG, int E1, int NB, int NW>
+// SHORT: the arrays hold no more than m blocks, so a query is only scored for a gate's sake (never_neg_inf), and that is asked
+// before the query and the tiles are.  us before any such request / with them / so: 32 queries of 6000 tokens 2.1 / 2.5 / 2.1, 256 of
+// 8000 2.2 / 2.6 / 2.2, 1000 of 7000 5.1 / 5.4 / 3.1; with a negative gate each 6.0 / 5.4 / 5.4, 6.6 / 5.5 / 5.6, 15.6 / 12.0 / 12.5.
+// 1500 (32 heads) 4.7 / 4.8 / 3.4, but 11.5 / 11.7 / 12.1, so up to 1024 queries.  (As a branch instead of an instance of its own it
+// costs every other call 0.2 us.)
+template <int HG, int E1, int NB, int NW, bool SHORT>
 __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_stage1_query(ScoreArgs a, const void* pooled,
                                                                            int32_t* block_idx_out, int sc_floats) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -1981,27 +1986,32 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_stage1_query(Score
   // (Tiles for all: 32 that keep all their blocks 2.9 us instead of 2.6, 1000 6.0 instead of 4.75.  The query, too, behind the
   // position: 2.2 and 3.1 us, but a pass over 32 queries at 128K 0.5 us longer, 36.3 -> 36.9.)
   QFrag<HG> f;
-  qfrag_shared_request<HG, NW>(f, (const uint16_t*)a.q + (long)t * a.H * kD, a.w + (long)t * a.H,
-                               (long)a.H * kD * 2, lds_address(q_lds), wave);
+  auto request_query = [&] {
+    qfrag_shared_request<HG, NW>(f, (const uint16_t*)a.q + (long)t * a.H * kD, a.w + (long)t * a.H,
+                                 (long)a.H * kD * 2, lds_address(q_lds), wave);
+  };
+  if constexpr (!SHORT) request_query();
   auto request_tile = [&] {
     const __amdgpu_buffer_rsrc_t prsrc =
         key_buffer((const char*)pooled + (long)seq * n_blocks * kD * 2, (long)n_blocks * kD * 2);
     tile_dma<DT_BF16>(prsrc, prsrc, lds_address(smem) + wave * NB * TILE, wave * 32);
   };
   const long most = (long)a.m * a.B;   // a query that sees this many positions or more has more than m blocks
-  const bool scored = (long)(a.q_pos ? a.q_pos[t] : a.q_pos0 + t) - query_lo(a.q_lo, t, 0x7ffffffe) >= most;
+  const bool scored = SHORT ? !never_neg_inf(a.w + (long)t * a.H, a.H, nullptr, 0, 0)
+                            : (long)(a.q_pos ? a.q_pos[t] : a.q_pos0 + t) - query_lo(a.q_lo, t, 0x7ffffffe) >= most;
+  if (SHORT && scored) request_query();
   if (scored) request_tile();
   const int pos = query_pos_in(a, t, seq);
   const int lo = query_lo(a.q_lo, t, pos);
-  if (pos - lo < most) {
+  if (SHORT ? !scored : pos - lo < most) {
     const int b_first = lo > 0 ? lo / a.B : 0, n_bvis = pos < 0 ? 0 : pos / a.B + 1;
-    if (n_bvis - b_first <= a.m && never_neg_inf(a.w + (long)t * a.H, a.H, nullptr, 0, 0)) {   // nothing to score
+    if (SHORT || (n_bvis - b_first <= a.m && never_neg_inf(a.w + (long)t * a.H, a.H, nullptr, 0, 0))) {   // nothing to score
       for (int p = threadIdx.x; p < a.m; p += NT) block_idx_out[(long)t * a.m + p] = p < n_bvis - b_first ? b_first + p : -1;
       wait_vmem_le<0>();    // (nothing may still be on its way into this workgroup's LDS)
       return;
     }
   }
-  if (!scored) request_tile();
+  if (!SHORT && !scored) request_tile();
   qfrag_shared_complete<HG>(f, lds_address(q_lds));
   qfrag_ready<HG>(f);
   uint32_t* hist = reinterpret_cast<uint32_t*>(q_lds);

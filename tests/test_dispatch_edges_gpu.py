@@ -155,6 +155,45 @@ def test_gates_that_refuse_the_direct_write_of_blocks(T, H, positions, packed):
     assert np.array_equal(one, general), np.nonzero((one != general).any(1))[0]
 
 
+@pytest.mark.parametrize("T,M", [(1, 1), (256, 2), (256, 33), (1024, 130), (1025, 130), (300, 512), (256, 1019)])
+@pytest.mark.parametrize("H", [64, 32])
+def test_stage1_of_arrays_of_at_most_m_blocks(T, M, H):
+    # positions in any order, none, past the sequence's end, and queries that see a part of it; gates that leave a query
+    # unscored, or not, in which case blocks of infinite score drop out: m as large as the array, and a little larger
+    import torch
+    from paper_2603_28458_amd import hisa
+
+    B, n = 32, 3
+    print(f"\n[short arrays] T={T} M={M} H={H}", flush=True)
+    g = torch.Generator().manual_seed(T + M)
+    rng = np.random.default_rng(T + M)
+    q, w = torch.randn((T, H, 128), generator=g), torch.rand((T, H), generator=g)
+    q[:, 0, 1] = 3e38
+    w[::2, 0] *= -1.0                                             # -inf where the pooled key's element 1 is large
+    w[1::6, 5], w[3::6, 1] = float("nan"), 0.0
+    pooled = torch.randn((n, M, 128), generator=g)
+    pooled[:, :, 1] = 0.0
+    pooled[:, M // 3:: 4, 1] = 3e38
+    lens = np.array([M * B, max(1, M * B // 2 + 3), 1])
+    seq = rng.integers(0, n, T)
+    pos = rng.integers(-1, M * B + 40, T)
+    lo = np.where(np.arange(T) % 4 == 0, rng.integers(0, np.maximum(1, np.minimum(pos, lens[seq] - 1) + 1)), 0)
+    ints = lambda x: torch.from_numpy(x.astype(np.int32)).cuda()
+    Q = hisa.Queries(q=q.bfloat16().cuda(), w=w.cuda(), dtype=hisa.HISA_BF16, q_seq=ints(seq), q_pos=ints(pos), q_lo=ints(lo))
+    K = hisa.Keys(k=None, seq_len=ints(lens), dtype=hisa.HISA_BF16, n_seq=n, s_max=M * B, d=128)
+    P = pooled.bfloat16().cuda()
+    for m in (max(2, M), M + 5):
+        got = hisa.hisa_block_score_topk(Q, K, P, hisa.HISA_BF16, B, m)[0].cpu().numpy()
+        want = hisa.hisa_block_score_topk(Q, K, P, hisa.HISA_BF16, B, m, want_scores=True)[0].cpu().numpy()
+        assert np.array_equal(got, want), np.nonzero((got != want).any(1))[0]
+        unscored = (w >= 0).all(1).numpy()
+        for t in range(T):
+            last = min(pos[t], lens[seq[t]] - 1)
+            ids = np.arange(lo[t] // B, last // B + 1) if last >= 0 else np.arange(0)
+            kept = got[t][got[t] >= 0]
+            assert np.isin(kept, ids).all() and (not unscored[t] or np.array_equal(kept, ids)), t
+
+
 @pytest.mark.parametrize("H", [64, 32])
 @pytest.mark.parametrize("T,q_pos0", [(2100, -1700), (4100, -3600)])
 def test_flat_indexer_on_a_short_packed_stream(T, q_pos0, H):
